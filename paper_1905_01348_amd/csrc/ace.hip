@@ -191,10 +191,18 @@ fx_status ace_apply_impl(fx_ctx* ctx, Workspace* ws, const fx_ace* ac, const voi
     }
     void* C = nullptr;
     FX_TRY(ws_get(ctx, ws, "acea_C", zsz * n * nphi, &C));
-    // split count fixed by N_r alone: results do not depend on n_phi
-    const int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(64, nr / 8192));
-    FX_TRY(zgemm(ctx, ws, st, 1, 0, n, nphi, (int)nr, cpx<double>{1, 0}, a->xi, nr, p64, ldp, cpx<double>{0, 0}, C, n,
-                 1, 0, 0, 0, nsplit));
+    // Split count fixed by N_r and n alone, so that a right-hand side's result
+    // does not depend on how many share the call: one workgroup per CU for a
+    // single tile column (chunks of at least 128).  A split per 8192 points
+    // left 26 workgroups for 128 factors x 100 right-hand sides at 48^3 (4.8
+    // ms).  Right-hand sides go in blocks that keep the partial sums near 64
+    // MiB, at least two tile columns each.
+    const int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(nr / 128, std::max(1, 256 / ((n + 127) / 128))));
+    const int rb = (int)std::max<int64_t>(128, ((int64_t)64 << 20) / (zsz * (int64_t)n * nsplit) / 64 * 64);
+    for (int r0 = 0; r0 < nphi; r0 += rb)
+      FX_TRY(zgemm(ctx, ws, st, 1, 0, n, std::min(rb, nphi - r0), (int)nr, cpx<double>{1, 0}, a->xi, nr,
+                   (const cpx<double>*)p64 + r0 * ldp, ldp, cpx<double>{0, 0}, (cpx<double>*)C + (int64_t)r0 * n, n, 1,
+                   0, 0, 0, nsplit));
     void* y = out;
     int64_t ldy = ld_out;
     if (out_dtype == FX_C64) {

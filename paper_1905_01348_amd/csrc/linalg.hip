@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cmath>
 #include <cstdio>
+#include <type_traits>
 #include <vector>
 
 #include "common.hpp"
@@ -32,150 +33,202 @@ FX_HD z zfma(z acc, z a, z b) {
 }
 
 // ---------------------------------------------------------------------------
-// zgemm: 128x64 output tile per 256-thread workgroup, K steps of 8; each
-// thread owns an 8x4 block of outputs (rows tx + 16 i, cols ty + 16 j), so
-// one LDS read feeds 2.7 complex multiply-adds.  The next K step's tiles are
-// loaded into registers while the current one is multiplied out of the other
-// half of a double-buffered LDS, one barrier per step.
-// Split over K: blockIdx.z = batch * nsplit + split; split s covers
-// K range [s*kchunk, min(K, (s+1)*kchunk)).  With a partial buffer the raw
-// sum of split s goes to partial[(batch*nsplit + s) * M*N] (ld M); without
-// one (nsplit == 1) the result C = alpha*sum + beta*C is written directly.
+// zgemm on the FP64 matrix cores (v_mfma_f64_16x16x4: 68-73 TFLOP/s in a loop
+// of its own on this GPU, about the vector FMA rate, but its operands feed
+// 16x16 outputs each, so the LDS reads that held a vector-FMA kernel to 49-52
+// TFLOP/s are a tenth of the time here).  256 threads = 4 waves in a 2x2
+// arrangement, output tile (32 WM) x (32 WN), K steps of 8 through a
+// double-buffered LDS with one barrier per step; the next step's global loads
+// are in registers while the current one is multiplied.  A wave owns the
+// 16x16 tiles (wm + 2 i, wn + 2 j), so that the columns left over at an edge
+// are shared by both waves of a row, and skips those that lie outside.
+// The matrix instruction is given B's columns as its rows and A's rows as its
+// columns: lane l then holds C(m = l % 16, n = 4 e + l / 16) of a tile, so
+// stores run along m.  A complex product is four real ones (re: b.x a.x, then
+// -b.y a.y; im: b.y a.x, then b.x a.y).  The sum of an element runs over k in
+// order, whatever the tile, so results do not depend on the tile chosen.
+//
+// Split over K: split s covers [s*kchunk, min(K, (s+1)*kchunk)).  With a
+// partial buffer the raw sum of split s goes to partial[(batch*nsplit + s) *
+// M*N] (ld M); without one (nsplit == 1) C = alpha*sum + beta*C is written
+// directly.  Blocks are dealt so that each XCD works on neighbouring tiles
+// (n fastest) of the same split and shares their operands in its L2.
 // ---------------------------------------------------------------------------
-constexpr int ZBM = 128, ZBN = 64, ZK = 8;
+constexpr int ZK = 8;
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-template <int OPA, int OPB>
-__global__ void __launch_bounds__(256, 2) k_zgemm(int M, int N, int K, const z* __restrict__ A, int64_t lda,
-                                               int64_t sA, const z* __restrict__ B, int64_t ldb, int64_t sB,
-                                               z* C, int64_t ldc, int64_t sC, z alpha, z beta, int nsplit,
-                                               int kchunk, z* __restrict__ partial) {
-  __shared__ z As[2][ZK][ZBM + 1];
-  __shared__ z Bs[2][ZK][ZBN + 1];
-  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  const int m0 = blockIdx.x * ZBM, n0 = blockIdx.y * ZBN;
-  const int bz = blockIdx.z, batch = bz / nsplit, split = bz % nsplit;
-  A += batch * sA;
-  B += batch * sB;
-  const int kbeg = split * kchunk, kend = min(K, kbeg + kchunk);
-  // staged loads: the A tile (128 x 8) is 4 elements per thread, the B tile
-  // (8 x 64) 2; op C reads along k (column of the stored matrix).  Element
-  // u of this thread sits at (row a_m(u), step a_k(u)) of the A tile and at
-  // (step b_k(u), column b_n(u)) of the B tile.
-  const auto a_m = [tid](int u) { return OPA == 0 ? (tid + 256 * u) % ZBM : (tid + 256 * u) / ZK; };
-  const auto a_k = [tid](int u) { return OPA == 0 ? (tid + 256 * u) / ZBM : (tid + 256 * u) % ZK; };
-  const auto b_n = [tid](int u) { return OPB == 0 ? (tid + 256 * u) / ZK : (tid + 256 * u) % ZBN; };
-  const auto b_k = [tid](int u) { return OPB == 0 ? (tid + 256 * u) % ZK : (tid + 256 * u) / ZBN; };
-  z ra0, ra1, ra2, ra3, rb0, rb1;
-#define FX_ZG_LOAD_A(u, dst)                                                                     \
-  {                                                                                              \
-    const int m = m0 + a_m(u), k = k0n + a_k(u);                                                \
-    dst = z{0.0, 0.0};                                                                           \
-    if (m < M && k < kend) dst = OPA == 0 ? A[m + (int64_t)k * lda] : zconj(A[k + (int64_t)m * lda]); \
-  }
-#define FX_ZG_LOAD_B(u, dst)                                                                     \
-  {                                                                                              \
-    const int n = n0 + b_n(u), k = k0n + b_k(u);                                                \
-    dst = z{0.0, 0.0};                                                                           \
-    if (n < N && k < kend) dst = OPB == 0 ? B[k + (int64_t)n * ldb] : zconj(B[n + (int64_t)k * ldb]); \
-  }
-#define FX_ZG_GLOAD()      \
-  FX_ZG_LOAD_A(0, ra0);    \
-  FX_ZG_LOAD_A(1, ra1);    \
-  FX_ZG_LOAD_A(2, ra2);    \
-  FX_ZG_LOAD_A(3, ra3);    \
-  FX_ZG_LOAD_B(0, rb0);    \
-  FX_ZG_LOAD_B(1, rb1);
-#define FX_ZG_SSTORE(bf)                  \
-  As[bf][a_k(0)][a_m(0)] = ra0;           \
-  As[bf][a_k(1)][a_m(1)] = ra1;           \
-  As[bf][a_k(2)][a_m(2)] = ra2;           \
-  As[bf][a_k(3)][a_m(3)] = ra3;           \
-  Bs[bf][b_k(0)][b_n(0)] = rb0;           \
-  Bs[bf][b_k(1)][b_n(1)] = rb1;
-  z acc[8][4];
+struct ZgArgs {
+  int M, N, K;
+  const z* A;
+  int64_t lda, sA;
+  const z* B;
+  int64_t ldb, sB;
+  z* C;
+  int64_t ldc, sC;
+  z alpha, beta;
+  int nsplit, kchunk, tiles_m, tiles_n;
+  z* partial;
+};
+
+template <int OPA, int OPB, int WM, int WN>
+__global__ void __launch_bounds__(256, 2) k_zgemm(const ZgArgs g) {
+  constexpr int BM = 32 * WM, BN = 32 * WN;
+  // rows of BM + 2: the eight k of one m that op C stores from neighbouring
+  // lanes then fall on distinct banks
+  __shared__ z As[2][ZK][BM + 2];
+  __shared__ z Bs[2][ZK][BN + 2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave & 1, wn = wave >> 1;
+  const int nblk = gridDim.x, bid = blockIdx.x;
+  const int lid = nblk % 8 == 0 ? (bid % 8) * (nblk / 8) + bid / 8 : bid;
+  const int tn = lid % g.tiles_n, r1 = lid / g.tiles_n;
+  const int tm = r1 % g.tiles_m, bz = r1 / g.tiles_m;
+  const int batch = bz / g.nsplit, split = bz - batch * g.nsplit;
+  const int m0 = tm * BM, n0 = tn * BN, M = g.M, N = g.N;
+  const z* A = g.A + batch * g.sA;
+  const z* B = g.B + batch * g.sB;
+  const int kbeg = split * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
+  // staged loads: WM elements of the A tile and WN of the B tile per thread;
+  // op C reads along k (the stored matrix's column)
+  const auto a_m = [tid](int u) { return OPA == 0 ? (tid + 256 * u) % BM : (tid + 256 * u) / ZK; };
+  const auto a_k = [tid](int u) { return OPA == 0 ? (tid + 256 * u) / BM : (tid + 256 * u) % ZK; };
+  const auto b_n = [tid](int u) { return OPB == 0 ? (tid + 256 * u) / ZK : (tid + 256 * u) % BN; };
+  const auto b_k = [tid](int u) { return OPB == 0 ? (tid + 256 * u) % ZK : (tid + 256 * u) / BN; };
+  z ra[WM], rb[WN];
+  const auto gload = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+    for (int u = 0; u < WM; ++u) {
+      const int m = m0 + a_m(u), k = k0 + a_k(u);
+      ra[u] = z{0.0, 0.0};
+      if (m < M && k < kend) ra[u] = OPA == 0 ? A[m + (int64_t)k * g.lda] : zconj(A[k + (int64_t)m * g.lda]);
+    }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = z{0.0, 0.0};
+    for (int u = 0; u < WN; ++u) {
+      const int n = n0 + b_n(u), k = k0 + b_k(u);
+      rb[u] = z{0.0, 0.0};
+      if (n < N && k < kend) rb[u] = OPB == 0 ? B[k + (int64_t)n * g.ldb] : zconj(B[n + (int64_t)k * g.ldb]);
+    }
+  };
+  const auto sstore = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < WM; ++u) As[b][a_k(u)][a_m(u)] = ra[u];
+#pragma unroll
+    for (int u = 0; u < WN; ++u) Bs[b][b_k(u)][b_n(u)] = rb[u];
+  };
+  doublex4 cr[WM][WN], ci[WM][WN];
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      cr[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+      ci[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+    }
+  // 16-wide tiles of this wave that hold any output
+  const int nti = min(WM, max(0, ((M - m0 + 15) / 16 - wm + 1) / 2));
+  const int ntj = min(WN, max(0, ((N - n0 + 15) / 16 - wn + 1) / 2));
+  const int l16 = lane & 15, lk = lane >> 4;
+  const auto mac = [&](int buf, auto full) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < ZK; kk += 4) {
+      z a[WM], b[WN];
+#pragma unroll
+      for (int i = 0; i < WM; ++i) a[i] = As[buf][kk + lk][(wm + 2 * i) * 16 + l16];
+#pragma unroll
+      for (int j = 0; j < WN; ++j) b[j] = Bs[buf][kk + lk][(wn + 2 * j) * 16 + l16];
+#pragma unroll
+      for (int i = 0; i < WM; ++i) {
+        if (!full.value && i >= nti) break;
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+          if (!full.value && j >= ntj) break;
+          cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[j].x, a[i].x, cr[i][j], 0, 0, 0);
+          ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[j].y, a[i].x, ci[i][j], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < WM; ++i) {
+        if (!full.value && i >= nti) break;
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+          if (!full.value && j >= ntj) break;
+          cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-b[j].y, a[i].y, cr[i][j], 0, 0, 0);
+          ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[j].x, a[i].y, ci[i][j], 0, 0, 0);
+        }
+      }
+    }
+  };
   if (kbeg < kend) {
-    const int k0n = kbeg;
-    FX_ZG_GLOAD();
-    FX_ZG_SSTORE(0);
+    gload(kbeg);
+    sstore(0);
   }
   __syncthreads();
   int buf = 0;
+  const bool whole = nti == WM && ntj == WN;
   for (int k0 = kbeg; k0 < kend; k0 += ZK) {
     const bool more = k0 + ZK < kend;
-    if (more) {
-      const int k0n = k0 + ZK;
-      FX_ZG_GLOAD();
-    }
-#pragma unroll 2
-    for (int kk = 0; kk < ZK; ++kk) {
-      // the step's operands are read before its multiply-adds, so that the
-      // LDS reads overlap
-      z b[4], a[8];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[buf][kk][ty + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) a[i] = As[buf][kk][tx + 16 * i];
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = zfma(acc[i][j], a[i], b[j]);
-    }
-    if (more) {
-      FX_ZG_SSTORE(buf ^ 1);
-    }
+    if (more) gload(k0 + ZK);
+    if (whole)
+      mac(buf, std::true_type{});
+    else
+      mac(buf, std::false_type{});
+    if (more) sstore(buf ^ 1);
     __syncthreads();
     buf ^= 1;
   }
-#undef FX_ZG_SSTORE
-#undef FX_ZG_GLOAD
-#undef FX_ZG_LOAD_B
-#undef FX_ZG_LOAD_A
-  if (partial) {
-    z* P = partial + (int64_t)bz * M * N;
+  z* P = g.partial ? g.partial + (int64_t)bz * M * N : nullptr;
+  z* Cb = g.C + batch * g.sC;
+  const bool bz0 = g.beta.x == 0.0 && g.beta.y == 0.0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < WM; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int m = m0 + tx + 16 * i, n = n0 + ty + 16 * j;
-        if (m < M && n < N) P[m + (int64_t)n * M] = acc[i][j];
-      }
-  } else {
-    z* Cb = C + batch * sC;
-    const bool bz0 = beta.x == 0.0 && beta.y == 0.0;
+    for (int j = 0; j < WN; ++j)
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int m = m0 + tx + 16 * i, n = n0 + ty + 16 * j;
-        if (m < M && n < N) {
-          z r = cmul(alpha, acc[i][j]);
-          if (!bz0) r = cadd(r, cmul(beta, Cb[m + (int64_t)n * ldc]));
-          Cb[m + (int64_t)n * ldc] = r;
+      for (int e = 0; e < 4; ++e) {
+        const int m = m0 + (wm + 2 * i) * 16 + l16, n = n0 + (wn + 2 * j) * 16 + 4 * e + lk;
+        if (m >= M || n >= N) continue;
+        const z s = {cr[i][j][e], ci[i][j][e]};
+        if (P) {
+          P[m + (int64_t)n * M] = s;
+        } else {
+          z r = cmul(g.alpha, s);
+          if (!bz0) r = cadd(r, cmul(g.beta, Cb[m + (int64_t)n * g.ldc]));
+          Cb[m + (int64_t)n * g.ldc] = r;
         }
       }
+}
+
+// C = alpha * sum_s partial_s + beta * C.  A block adds the splits of 16
+// neighbouring elements: group q of 16 threads takes splits q, q + 16, ... in
+// ascending order, then the 16 sums are added in order of q.  (One thread per
+// element left a 128 x 100 result on 50 workgroups.)
+__global__ void __launch_bounds__(256) k_split_reduce(int M, int N, int nsplit, int nbatch,
+                                                      const z* __restrict__ partial, z* C, int64_t ldc, int64_t sC,
+                                                      z alpha, z beta) {
+  __shared__ z red[16][17];
+  const int64_t MN = (int64_t)M * N;
+  const int el = threadIdx.x & 15, q = threadIdx.x >> 4;
+  for (int64_t base = (int64_t)blockIdx.x * 16; base < MN * nbatch; base += (int64_t)gridDim.x * 16) {
+    const int64_t i = base + el;
+    const int64_t b = i / MN, e = i - b * MN;
+    z s = {0.0, 0.0};
+    if (b < nbatch) {
+#pragma unroll 4
+      for (int t = q; t < nsplit; t += 16) s = cadd(s, partial[(b * nsplit + t) * MN + e]);
+    }
+    red[q][el] = s;
+    __syncthreads();
+    if (q == 0 && b < nbatch) {
+      for (int t = 1; t < 16; ++t) s = cadd(s, red[t][el]);
+      z r = cmul(alpha, s);
+      z* c = C + b * sC + e % M + (e / M) * ldc;
+      if (!(beta.x == 0.0 && beta.y == 0.0)) r = cadd(r, cmul(beta, *c));
+      *c = r;
+    }
+    __syncthreads();
   }
 }
 
-// C = alpha * sum_s partial_s + beta * C, summing splits in ascending order.
-__global__ void k_split_reduce(int M, int N, int nsplit, int nbatch, const z* __restrict__ partial, z* C,
-                               int64_t ldc, int64_t sC, z alpha, z beta) {
-  const int64_t MN = (int64_t)M * N;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < MN * nbatch;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t b = i / MN, e = i - b * MN;
-    const int64_t m = e % M, n = e / M;
-    z s = {0.0, 0.0};
-    for (int q = 0; q < nsplit; ++q) s = cadd(s, partial[(b * nsplit + q) * MN + e]);
-    z r = cmul(alpha, s);
-    z* c = C + b * sC + m + n * ldc;
-    if (!(beta.x == 0.0 && beta.y == 0.0)) r = cadd(r, cmul(beta, *c));
-    *c = r;
-  }
-}
+static unsigned reduce_blocks(int64_t elems) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((elems + 15) / 16, 16384)); }
 
 fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, int M, int N, int K, z alpha,
                 const void* A, int64_t lda, const void* B, int64_t ldb, z beta, void* C, int64_t ldc, int batch,
@@ -183,21 +236,22 @@ fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, in
   if (M <= 0 || N <= 0) return FX_OK;
   if (K <= 0) {
     // empty sum: C = beta C (no splits to add)
-    hipLaunchKernelGGL(k_split_reduce, dim3(std::min<int64_t>(((int64_t)M * N * batch + 255) / 256, 4096)),
-                       dim3(256), 0, st, M, N, 0, batch, (const z*)nullptr, (z*)C, ldc, sC, alpha, beta);
+    hipLaunchKernelGGL(k_split_reduce, dim3(reduce_blocks((int64_t)M * N * batch)), dim3(256), 0, st, M, N, 0, batch,
+                       (const z*)nullptr, (z*)C, ldc, sC, alpha, beta);
     FX_LAUNCH_CHECK();
     return FX_OK;
   }
-  const int tiles = ((M + ZBM - 1) / ZBM) * ((N + ZBN - 1) / ZBN) * batch;
+  const int n_cu = std::max(ctx->n_cu, 1);
+  const auto tiles_of = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * batch; };
   int nsplit = nsplit_hint;
   if (nsplit <= 0) {
     // enough workgroups to fill the chip (per_cu per CU: 16 measured 2-4%
     // faster than 4 for the 1024 x 1024 overlaps at 96^3), each with at least
-    // 512 K-steps
+    // 16 K-steps
     int per_cu = 16;
     if (const char* e = getenv("FX_ZGEMM_PER_CU")) per_cu = std::max(1, std::min(64, atoi(e)));
-    const int want = std::max(1, (per_cu * std::max(ctx->n_cu, 1)) / std::max(tiles, 1));
-    nsplit = std::max(1, std::min(want, K / 4096));
+    const int64_t want = std::max<int64_t>(1, per_cu * n_cu / tiles_of(128, 64));
+    nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(want, K / 128));
   }
   int kchunk = (K + nsplit - 1) / nsplit;
   kchunk = (kchunk + ZK - 1) / ZK * ZK;
@@ -208,27 +262,37 @@ fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, in
     FX_TRY(ws_get(ctx, ws, "zgemm_part", sizeof(z) * (size_t)M * N * nsplit * batch, &p));
     part = (z*)p;
   }
-  dim3 grid((M + ZBM - 1) / ZBM, (N + ZBN - 1) / ZBN, nsplit * batch);
+  // 128 x 64 tiles where they occupy the chip; below that 32 x 32, whose
+  // workgroups are an eighth of the work each (N x N products of the
+  // factorisations)
+  const bool big = tiles_of(128, 64) * nsplit >= n_cu;
+  const int bm = big ? 128 : 32, bn = big ? 64 : 32;
+  ZgArgs g{M, N, K, (const z*)A, lda, sA, (const z*)B, ldb, sB, (z*)C, ldc, sC, alpha, beta, nsplit, kchunk,
+           (M + bm - 1) / bm, (N + bn - 1) / bn, part};
+  const dim3 grid((unsigned)(tiles_of(bm, bn) * nsplit));
   int slot;
   FX_TRY(prof_begin(ctx, st, opa ? FX_K_GEMM_CN : FX_K_GEMM_NN, 8.0 * M * N * (double)K * batch, &slot));
-#define FX_ZG(a, b)                                                                                                 \
-  hipLaunchKernelGGL((k_zgemm<a, b>), grid, dim3(256), 0, st, M, N, K, (const z*)A, lda, sA, (const z*)B, ldb, sB, \
-                     (z*)C, ldc, sC, alpha, beta, nsplit, kchunk, part)
-  if (opa == 0 && opb == 0)
-    FX_ZG(0, 0);
-  else if (opa == 0)
-    FX_ZG(0, 1);
-  else if (opb == 0)
-    FX_ZG(1, 0);
-  else
-    FX_ZG(1, 1);
+#define FX_ZG(a, b)                                                                    \
+  if (big)                                                                             \
+    hipLaunchKernelGGL((k_zgemm<a, b, 4, 2>), grid, dim3(256), 0, st, g);              \
+  else                                                                                 \
+    hipLaunchKernelGGL((k_zgemm<a, b, 1, 1>), grid, dim3(256), 0, st, g);
+  if (opa == 0 && opb == 0) {
+    FX_ZG(0, 0)
+  } else if (opa == 0) {
+    FX_ZG(0, 1)
+  } else if (opb == 0) {
+    FX_ZG(1, 0)
+  } else {
+    FX_ZG(1, 1)
+  }
 #undef FX_ZG
   FX_LAUNCH_CHECK();
   FX_TRY(prof_end(ctx, st, slot));
   if (nsplit > 1) {
     FX_TRY(prof_begin(ctx, st, FX_K_REDUCE, 16.0 * M * N * batch * (nsplit + 2.0), &slot));
-    hipLaunchKernelGGL(k_split_reduce, dim3(std::min<int64_t>(((int64_t)M * N * batch + 255) / 256, 4096)),
-                       dim3(256), 0, st, M, N, nsplit, batch, (const z*)part, (z*)C, ldc, sC, alpha, beta);
+    hipLaunchKernelGGL(k_split_reduce, dim3(reduce_blocks((int64_t)M * N * batch)), dim3(256), 0, st, M, N, nsplit,
+                       batch, (const z*)part, (z*)C, ldc, sC, alpha, beta);
     FX_LAUNCH_CHECK();
     FX_TRY(prof_end(ctx, st, slot));
   }
