@@ -192,8 +192,8 @@ fx_status ace_apply_impl(fx_ctx* ctx, Workspace* ws, const fx_ace* ac, const voi
     void* C = nullptr;
     FX_TRY(ws_get(ctx, ws, "acea_C", zsz * n * nphi, &C));
     // Split count fixed by N_r and n alone, so that a right-hand side's result
-    // does not depend on how many share the call: one workgroup per CU for a
-    // single tile column (chunks of at least 128).  A split per 8192 points
+    // does not depend on how many share the call: two workgroups per CU
+    // for a single tile column (chunks of at least 128).  A split per 8192 points
     // left 26 workgroups for 128 factors x 100 right-hand sides at 48^3 (4.8
     // ms).  Right-hand sides go in blocks that keep the partial sums near 64
     // MiB, at least two tile columns each.

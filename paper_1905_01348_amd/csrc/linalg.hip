@@ -36,12 +36,17 @@ FX_HD z zfma(z acc, z a, z b) {
 // zgemm on the FP64 matrix cores (v_mfma_f64_16x16x4: 68-73 TFLOP/s in a loop
 // of its own on this GPU, about the vector FMA rate, but its operands feed
 // 16x16 outputs each, so the LDS reads that held a vector-FMA kernel to 49-52
-// TFLOP/s are a tenth of the time here).  256 threads = 4 waves in a 2x2
-// arrangement, output tile (32 WM) x (32 WN), K steps of 8 through a
-// double-buffered LDS with one barrier per step; the next step's global loads
-// are in registers while the current one is multiplied.  A wave owns the
-// 16x16 tiles (wm + 2 i, wn + 2 j), so that the columns left over at an edge
-// are shared by both waves of a row, and skips those that lie outside.
+// TFLOP/s are a tenth of the time here).  2 x WNW waves; output tile (32 WM) x
+// (16 WN WNW), K steps of 8 through a double-buffered LDS with one barrier
+// per step; the next step's global loads are in registers while the current
+// one is multiplied.  A wave owns the 16x16 tiles (wm + 2 i, wn + WNW j), so
+// that the columns left over at an edge are shared by the waves of a row, and
+// skips those that lie outside.
+// 64 x 64 tiles at four waves per SIMD: 58-61 TFLOP/s of executed products
+// (N = 432 at 72^3: Psi^H H Psi 15.0 -> 10.3 ms, Psi S 12.2 -> 9.3 ms against
+// the vector-FMA kernel).  128 x 64 at two waves per SIMD measured 2-6%
+// slower, 128 x 128 with steps of 16 at one workgroup per CU 14-20% (the
+// barriers are exposed).
 // The matrix instruction is given B's columns as its rows and A's rows as its
 // columns: lane l then holds C(m = l % 16, n = 4 e + l / 16) of a tile, so
 // stores run along m.  A complex product is four real ones (re: b.x a.x, then
@@ -70,14 +75,25 @@ struct ZgArgs {
   z* partial;
 };
 
-template <int OPA, int OPB, int WM, int WN>
-__global__ void __launch_bounds__(256, 2) k_zgemm(const ZgArgs g) {
-  constexpr int BM = 32 * WM, BN = 32 * WN;
-  // rows of BM + 2: the eight k of one m that op C stores from neighbouring
-  // lanes then fall on distinct banks
-  __shared__ z As[2][ZK][BM + 2];
-  __shared__ z Bs[2][ZK][BN + 2];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+template <int WM, int WN, int WNW>
+struct ZgTile {
+  static constexpr int BM = 32 * WM, BN = 16 * WN * WNW, NT = 128 * WNW;
+  // rows of BM + 1 (BN + T::PAD) values: the k of one m that op C stores from
+  // neighbouring lanes fall on distinct banks
+  static constexpr int PAD = 16 / ZK;
+  static constexpr int LA = ZK * (BM + PAD), LB = ZK * (BN + PAD);
+  static constexpr size_t kLds = 2 * (LA + LB) * sizeof(z);
+};
+
+template <int OPA, int OPB, int WM, int WN, int WNW>
+__global__ void __launch_bounds__(128 * WNW, WM * WN <= 4 ? 4 : 2) k_zgemm(const ZgArgs g) {
+  using T = ZgTile<WM, WN, WNW>;
+  constexpr int BM = T::BM, BN = T::BN, NT = T::NT;
+  constexpr int UA = BM * ZK / NT, UB = BN * ZK / NT;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  z* const As = reinterpret_cast<z*>(smem_raw);
+  z* const Bs = As + 2 * T::LA;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 1, wn = wave >> 1;
   const int nblk = gridDim.x, bid = blockIdx.x;
   const int lid = nblk % 8 == 0 ? (bid % 8) * (nblk / 8) + bid / 8 : bid;
@@ -88,32 +104,43 @@ __global__ void __launch_bounds__(256, 2) k_zgemm(const ZgArgs g) {
   const z* A = g.A + batch * g.sA;
   const z* B = g.B + batch * g.sB;
   const int kbeg = split * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
-  // staged loads: WM elements of the A tile and WN of the B tile per thread;
+  // staged loads: UA elements of the A tile and UB of the B tile per thread;
   // op C reads along k (the stored matrix's column)
-  const auto a_m = [tid](int u) { return OPA == 0 ? (tid + 256 * u) % BM : (tid + 256 * u) / ZK; };
-  const auto a_k = [tid](int u) { return OPA == 0 ? (tid + 256 * u) / BM : (tid + 256 * u) % ZK; };
-  const auto b_n = [tid](int u) { return OPB == 0 ? (tid + 256 * u) / ZK : (tid + 256 * u) % BN; };
-  const auto b_k = [tid](int u) { return OPB == 0 ? (tid + 256 * u) % ZK : (tid + 256 * u) / BN; };
-  z ra[WM], rb[WN];
+  const auto a_m = [tid](int u) { return OPA == 0 ? (tid + NT * u) % BM : (tid + NT * u) / ZK; };
+  const auto a_k = [tid](int u) { return OPA == 0 ? (tid + NT * u) / BM : (tid + NT * u) % ZK; };
+  const auto b_n = [tid](int u) { return OPB == 0 ? (tid + NT * u) / ZK : (tid + NT * u) % BN; };
+  const auto b_k = [tid](int u) { return OPB == 0 ? (tid + NT * u) % ZK : (tid + NT * u) / BN; };
+  // Out-of-range rows and columns load a clamped one (they only reach outputs
+  // that are not written); k past the end is set to zero on the way to LDS.
+  // Loads stand outside branches and op C's sign is applied after them, so
+  // that nothing waits for a load before its step is stored.
+  z ra[UA], rb[UB];
+  const z *pa[UA], *pb[UB];
+  const int64_t da = OPA == 0 ? g.lda : 1, db = OPB == 0 ? 1 : g.ldb;
+#pragma unroll
+  for (int u = 0; u < UA; ++u) pa[u] = A + (int64_t)min(m0 + a_m(u), M - 1) * (OPA == 0 ? 1 : g.lda);
+#pragma unroll
+  for (int u = 0; u < UB; ++u) pb[u] = B + (int64_t)min(n0 + b_n(u), N - 1) * (OPB == 0 ? g.ldb : 1);
   const auto gload = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < WM; ++u) {
-      const int m = m0 + a_m(u), k = k0 + a_k(u);
-      ra[u] = z{0.0, 0.0};
-      if (m < M && k < kend) ra[u] = OPA == 0 ? A[m + (int64_t)k * g.lda] : zconj(A[k + (int64_t)m * g.lda]);
-    }
+    for (int u = 0; u < UA; ++u) ra[u] = pa[u][min(k0 + a_k(u), kend - 1) * da];
 #pragma unroll
-    for (int u = 0; u < WN; ++u) {
-      const int n = n0 + b_n(u), k = k0 + b_k(u);
-      rb[u] = z{0.0, 0.0};
-      if (n < N && k < kend) rb[u] = OPB == 0 ? B[k + (int64_t)n * g.ldb] : zconj(B[n + (int64_t)k * g.ldb]);
-    }
+    for (int u = 0; u < UB; ++u) rb[u] = pb[u][min(k0 + b_k(u), kend - 1) * db];
   };
-  const auto sstore = [&](int b) __attribute__((always_inline)) {
+  const auto sstore = [&](int b, int k0) __attribute__((always_inline)) {
+    const bool tail = k0 + ZK > kend;
 #pragma unroll
-    for (int u = 0; u < WM; ++u) As[b][a_k(u)][a_m(u)] = ra[u];
+    for (int u = 0; u < UA; ++u) {
+      z v = OPA == 0 ? ra[u] : zconj(ra[u]);
+      if (tail && k0 + a_k(u) >= kend) v = z{0.0, 0.0};
+      As[b * T::LA + a_k(u) * (BM + T::PAD) + a_m(u)] = v;
+    }
 #pragma unroll
-    for (int u = 0; u < WN; ++u) Bs[b][b_k(u)][b_n(u)] = rb[u];
+    for (int u = 0; u < UB; ++u) {
+      z v = OPB == 0 ? rb[u] : zconj(rb[u]);
+      if (tail && k0 + b_k(u) >= kend) v = z{0.0, 0.0};
+      Bs[b * T::LB + b_k(u) * (BN + T::PAD) + b_n(u)] = v;
+    }
   };
   doublex4 cr[WM][WN], ci[WM][WN];
 #pragma unroll
@@ -125,56 +152,61 @@ __global__ void __launch_bounds__(256, 2) k_zgemm(const ZgArgs g) {
     }
   // 16-wide tiles of this wave that hold any output
   const int nti = min(WM, max(0, ((M - m0 + 15) / 16 - wm + 1) / 2));
-  const int ntj = min(WN, max(0, ((N - n0 + 15) / 16 - wn + 1) / 2));
+  const int ntj = min(WN, max(0, ((N - n0 + 15) / 16 - wn + WNW - 1) / WNW));
   const int l16 = lane & 15, lk = lane >> 4;
   const auto mac = [&](int buf, auto full) __attribute__((always_inline)) {
+    const z* as = As + buf * T::LA + lk * (BM + T::PAD) + wm * 16 + l16;
+    const z* bs = Bs + buf * T::LB + lk * (BN + T::PAD) + wn * 16 + l16;
 #pragma unroll
-    for (int kk = 0; kk < ZK; kk += 4) {
+    for (int kk = 0; kk < ZK / 4; ++kk) {
       z a[WM], b[WN];
 #pragma unroll
-      for (int i = 0; i < WM; ++i) a[i] = As[buf][kk + lk][(wm + 2 * i) * 16 + l16];
+      for (int i = 0; i < WM; ++i) a[i] = as[4 * kk * (BM + T::PAD) + 32 * i];
 #pragma unroll
-      for (int j = 0; j < WN; ++j) b[j] = Bs[buf][kk + lk][(wn + 2 * j) * 16 + l16];
+      for (int j = 0; j < WN; ++j) b[j] = bs[4 * kk * (BN + T::PAD) + 16 * WNW * j];
 #pragma unroll
-      for (int i = 0; i < WM; ++i) {
-        if (!full.value && i >= nti) break;
+      for (int i = 0; i < WM; ++i)
 #pragma unroll
-        for (int j = 0; j < WN; ++j) {
-          if (!full.value && j >= ntj) break;
-          cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[j].x, a[i].x, cr[i][j], 0, 0, 0);
-          ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[j].y, a[i].x, ci[i][j], 0, 0, 0);
-        }
-      }
+        for (int j = 0; j < WN; ++j)
+          if (full.value || (i < nti && j < ntj)) {
+            cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[j].x, a[i].x, cr[i][j], 0, 0, 0);
+            ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[j].y, a[i].x, ci[i][j], 0, 0, 0);
+            if (!full.value) {
+              cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-b[j].y, a[i].y, cr[i][j], 0, 0, 0);
+              ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[j].x, a[i].y, ci[i][j], 0, 0, 0);
+            }
+          }
+      if (full.value) {
 #pragma unroll
-      for (int i = 0; i < WM; ++i) {
-        if (!full.value && i >= nti) break;
+        for (int i = 0; i < WM; ++i)
 #pragma unroll
-        for (int j = 0; j < WN; ++j) {
-          if (!full.value && j >= ntj) break;
-          cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-b[j].y, a[i].y, cr[i][j], 0, 0, 0);
-          ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[j].x, a[i].y, ci[i][j], 0, 0, 0);
-        }
+          for (int j = 0; j < WN; ++j) {
+            cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-b[j].y, a[i].y, cr[i][j], 0, 0, 0);
+            ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[j].x, a[i].y, ci[i][j], 0, 0, 0);
+          }
       }
     }
   };
-  if (kbeg < kend) {
-    gload(kbeg);
-    sstore(0);
-  }
-  __syncthreads();
-  int buf = 0;
-  const bool whole = nti == WM && ntj == WN;
-  for (int k0 = kbeg; k0 < kend; k0 += ZK) {
-    const bool more = k0 + ZK < kend;
-    if (more) gload(k0 + ZK);
-    if (whole)
-      mac(buf, std::true_type{});
-    else
-      mac(buf, std::false_type{});
-    if (more) sstore(buf ^ 1);
+  const auto kloop = [&](auto full) __attribute__((always_inline)) {
+    if (kbeg < kend) {
+      gload(kbeg);
+      sstore(0, kbeg);
+    }
     __syncthreads();
-    buf ^= 1;
-  }
+    int buf = 0;
+    for (int k0 = kbeg; k0 < kend; k0 += ZK) {
+      const bool more = k0 + ZK < kend;
+      if (more) gload(k0 + ZK);
+      mac(buf, full);
+      if (more) sstore(buf ^ 1, k0 + ZK);
+      __syncthreads();
+      buf ^= 1;
+    }
+  };
+  if (m0 + BM <= M && n0 + BN <= N)
+    kloop(std::true_type{});
+  else
+    kloop(std::false_type{});
   z* P = g.partial ? g.partial + (int64_t)bz * M * N : nullptr;
   z* Cb = g.C + batch * g.sC;
   const bool bz0 = g.beta.x == 0.0 && g.beta.y == 0.0;
@@ -184,7 +216,7 @@ __global__ void __launch_bounds__(256, 2) k_zgemm(const ZgArgs g) {
     for (int j = 0; j < WN; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int m = m0 + (wm + 2 * i) * 16 + l16, n = n0 + (wn + 2 * j) * 16 + 4 * e + lk;
+        const int m = m0 + (wm + 2 * i) * 16 + l16, n = n0 + (wn + WNW * j) * 16 + 4 * e + lk;
         if (m >= M || n >= N) continue;
         const z s = {cr[i][j][e], ci[i][j][e]};
         if (P) {
@@ -245,12 +277,11 @@ fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, in
   const auto tiles_of = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * batch; };
   int nsplit = nsplit_hint;
   if (nsplit <= 0) {
-    // enough workgroups to fill the chip (per_cu per CU: 16 measured 2-4%
-    // faster than 4 for the 1024 x 1024 overlaps at 96^3), each with at least
-    // 16 K-steps
-    int per_cu = 16;
+    // enough workgroups to fill the chip twice (four 64 x 64 tiles are resident
+    // per CU), each with at least 16 K steps
+    int per_cu = 8;
     if (const char* e = getenv("FX_ZGEMM_PER_CU")) per_cu = std::max(1, std::min(64, atoi(e)));
-    const int64_t want = std::max<int64_t>(1, per_cu * n_cu / tiles_of(128, 64));
+    const int64_t want = std::max<int64_t>(1, per_cu * n_cu / tiles_of(64, 64));
     nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(want, K / 128));
   }
   int kchunk = (K + nsplit - 1) / nsplit;
@@ -262,21 +293,25 @@ fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, in
     FX_TRY(ws_get(ctx, ws, "zgemm_part", sizeof(z) * (size_t)M * N * nsplit * batch, &p));
     part = (z*)p;
   }
-  // 128 x 64 tiles where they occupy the chip; below that 32 x 32, whose
-  // workgroups are an eighth of the work each (N x N products of the
+  // 64 x 64 tiles where they occupy the chip; below that 32 x 32, whose
+  // workgroups are a quarter of the work each (N x N products of the
   // factorisations)
-  const bool big = tiles_of(128, 64) * nsplit >= n_cu;
-  const int bm = big ? 128 : 32, bn = big ? 64 : 32;
+  const bool big = tiles_of(64, 64) * nsplit >= n_cu;
+  const int bm = big ? 64 : 32, bn = bm;
   ZgArgs g{M, N, K, (const z*)A, lda, sA, (const z*)B, ldb, sB, (z*)C, ldc, sC, alpha, beta, nsplit, kchunk,
            (M + bm - 1) / bm, (N + bn - 1) / bn, part};
   const dim3 grid((unsigned)(tiles_of(bm, bn) * nsplit));
   int slot;
   FX_TRY(prof_begin(ctx, st, opa ? FX_K_GEMM_CN : FX_K_GEMM_NN, 8.0 * M * N * (double)K * batch, &slot));
-#define FX_ZG(a, b)                                                                    \
-  if (big)                                                                             \
-    hipLaunchKernelGGL((k_zgemm<a, b, 4, 2>), grid, dim3(256), 0, st, g);              \
-  else                                                                                 \
-    hipLaunchKernelGGL((k_zgemm<a, b, 1, 1>), grid, dim3(256), 0, st, g);
+#define FX_ZG(a, b)                                                                     \
+  if (big) {                                                                            \
+    const auto kern = k_zgemm<a, b, 2, 2, 2>;                                           \
+    FX_TRY(allow_dynamic_lds((const void*)kern, ZgTile<2, 2, 2>::kLds));                \
+    hipLaunchKernelGGL(kern, grid, dim3(ZgTile<2, 2, 2>::NT), (ZgTile<2, 2, 2>::kLds), st, g);          \
+  } else {                                                                              \
+    const auto kern = k_zgemm<a, b, 1, 1, 2>;                                           \
+    hipLaunchKernelGGL(kern, grid, dim3(256), (ZgTile<1, 1, 2>::kLds), st, g);          \
+  }
   if (opa == 0 && opb == 0) {
     FX_ZG(0, 0)
   } else if (opa == 0) {
