@@ -114,7 +114,9 @@ fx_status ace_build_impl(fx_ctx* ctx, Workspace* ws, const fx_cell* cell, const 
   if (ex_dev_out && hipMemcpyAsync(ex_dev_out, ex_dev, sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess)
     return fail(FX_ERR_DEVICE);
   // -M = L L^H
-  if ((s = zpotrf(ctx, ws, st, n, a->L, n, info_dev)) != FX_OK) return fail(s);
+  void* dinv = nullptr;
+  if ((s = ws_get(ctx, ws, "chol_dinv", chol_dinv_bytes(n), &dinv)) != FX_OK) return fail(s);
+  if ((s = zpotrf(ctx, ws, st, n, a->L, n, dinv, info_dev)) != FX_OK) return fail(s);
   double ex = 0.0;
   int info = 0;
   if (hipMemcpyAsync(&ex, ex_dev, sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -134,7 +136,7 @@ fx_status ace_build_impl(fx_ctx* ctx, Workspace* ws, const fx_cell* cell, const 
   if ((s = ws_get(ctx, ws, "ace_Linv", zsz * n * n, &Linv)) != FX_OK) return fail(s);
   if ((s = ws_get(ctx, ws, "ace_LinvH", zsz * n * n, &LinvH)) != FX_OK) return fail(s);
   if (hipMemcpyAsync(Linv, a->L, zsz * n * n, hipMemcpyDeviceToDevice, st) != hipSuccess) return fail(FX_ERR_DEVICE);
-  if ((s = ztrinv(ctx, ws, st, n, Linv, n)) != FX_OK) return fail(s);
+  if ((s = ztrinv(ctx, ws, st, n, Linv, n, dinv)) != FX_OK) return fail(s);
   if ((s = zconj_transpose(st, n, Linv, n, LinvH, n)) != FX_OK) return fail(s);
   if ((s = ace_alloc(a, zsz * nr * n, &a->xi)) != FX_OK) return fail(s);
   if ((s = zgemm(ctx, ws, st, 0, 0, (int)nr, n, n, cpx<double>{1, 0}, W, nr, LinvH, n, cpx<double>{0, 0}, a->xi, nr,

@@ -73,6 +73,7 @@ struct ZgArgs {
   z alpha, beta;
   int nsplit, kchunk, tiles_m, tiles_n;
   z* partial;
+  ZgShape shape;
 };
 
 template <int WM, int WN, int WNW>
@@ -100,10 +101,15 @@ __global__ void __launch_bounds__(128 * WNW, WM * WN <= 4 ? 4 : 2) k_zgemm(const
   const int tn = lid % g.tiles_n, r1 = lid / g.tiles_n;
   const int tm = r1 % g.tiles_m, bz = r1 / g.tiles_m;
   const int batch = bz / g.nsplit, split = bz - batch * g.nsplit;
-  const int m0 = tm * BM, n0 = tn * BN, M = g.M, N = g.N;
+  const int m0 = tm * BM, n0 = tn * BN, N = g.N;
+  const int M = g.shape.mlim > 0 ? min(g.M, g.shape.mlim - batch * g.shape.mstep) : g.M;
+  if (m0 >= M || ((g.shape.flags & kZgHermitian) && m0 + BM <= n0)) return;
   const z* A = g.A + batch * g.sA;
   const z* B = g.B + batch * g.sB;
-  const int kbeg = split * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
+  int kbeg = split * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
+  if (g.shape.flags & kZgBUpper) kend = min(kend, n0 + BN);
+  if (g.shape.flags & kZgALower) kend = min(kend, min(M, m0 + BM));
+  if (g.shape.flags & kZgBLower) kbeg = max(kbeg, n0);
   // staged loads: UA elements of the A tile and UB of the B tile per thread;
   // op C reads along k (the stored matrix's column)
   const auto a_m = [tid](int u) { return OPA == 0 ? (tid + NT * u) % BM : (tid + NT * u) / ZK; };
@@ -264,7 +270,7 @@ static unsigned reduce_blocks(int64_t elems) { return (unsigned)std::max<int64_t
 
 fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, int M, int N, int K, z alpha,
                 const void* A, int64_t lda, const void* B, int64_t ldb, z beta, void* C, int64_t ldc, int batch,
-                int64_t sA, int64_t sB, int64_t sC, int nsplit_hint) {
+                int64_t sA, int64_t sB, int64_t sC, int nsplit_hint, ZgShape shape) {
   if (M <= 0 || N <= 0) return FX_OK;
   if (K <= 0) {
     // empty sum: C = beta C (no splits to add)
@@ -299,7 +305,7 @@ fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, in
   const bool big = tiles_of(64, 64) * nsplit >= n_cu;
   const int bm = big ? 64 : 32, bn = bm;
   ZgArgs g{M, N, K, (const z*)A, lda, sA, (const z*)B, ldb, sB, (z*)C, ldc, sC, alpha, beta, nsplit, kchunk,
-           (M + bm - 1) / bm, (N + bn - 1) / bn, part};
+           (M + bm - 1) / bm, (N + bn - 1) / bn, part, shape};
   const dim3 grid((unsigned)(tiles_of(bm, bn) * nsplit));
   int slot;
   FX_TRY(prof_begin(ctx, st, opa ? FX_K_GEMM_CN : FX_K_GEMM_NN, 8.0 * M * N * (double)K * batch, &slot));
@@ -349,87 +355,104 @@ __global__ void k_herm(int n, const z* __restrict__ M, int64_t ldm, z* __restric
   }
 }
 
-__global__ void k_half_trace(int n, const z* __restrict__ H, double* out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < n; ++i) s += H[i + (int64_t)i * n].x;
+// half the trace: 64 strided sums in ascending order, added in order of the lane
+__global__ void __launch_bounds__(64) k_half_trace(int n, const z* __restrict__ H, double* out) {
+  __shared__ double red[64];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < n; i += 64) s += H[i + (int64_t)i * n].x;
+  red[threadIdx.x] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int t = 1; t < 64; ++t) s += red[t];
     *out = 0.5 * s;
   }
 }
 
 // ---------------------------------------------------------------------------
-// Blocked Cholesky, lower: A = L L^H, block size CB.
+// Blocked Cholesky, lower: A = L L^H, in blocks of CB columns.  Three launches
+// per block: the diagonal block (factor and inverse, one workgroup), the rows
+// below it (times the inverse) and the trailing update; the inverses are kept
+// for ztrinv.  What bounds it is the chain of small launches, so a block is
+// as large as one workgroup holds in registers: with 32-wide blocks solved by
+// one thread per row, factor and inverse of 432 columns took 2.1 ms in 70
+// launches (now 0.5 ms in 29).
 // ---------------------------------------------------------------------------
-constexpr int CB = 32;
+constexpr int CB = kCholBlock;
 
-// Unblocked factorisation of the nb x nb diagonal block at (k, k), in LDS.
-// A non-positive or non-finite pivot records column+1 in *info (first one
+// Diagonal block (nb <= CB columns at (k, k)): right-looking elimination with
+// the 4 x 4 elements (tr + 16 i, ts + 16 j) of a thread in registers, column
+// by column.  S becomes U D U^H with U unit lower: column c publishes S(:, c)
+// (not yet scaled) and row c of X = U^{-1}, each element then takes its
+// update, and one barrier per column suffices with two buffers.  At the end
+// L = U D^{1/2} and L^{-1} = D^{-1/2} X.  Past nb the block is the identity.
+// A non-positive or non-finite pivot records column + 1 in *info (first one
 // wins) and is replaced by 1 so the rest stays finite.
-__global__ void __launch_bounds__(256) k_potrf_diag(int n, z* A, int64_t lda, int k, int* info) {
-  __shared__ z S[CB][CB + 1];
-  __shared__ double piv;
+__global__ void __launch_bounds__(256) k_potrf_diag(int n, z* A, int64_t lda, int k, z* __restrict__ dinv, int* info) {
+  __shared__ z col[2][CB], row[2][CB];
+  __shared__ double piv[CB];
   const int nb = min(CB, n - k);
-  const int tid = threadIdx.x;
-  for (int e = tid; e < nb * nb; e += 256) {
-    const int i = e % nb, j = e / nb;
-    S[i][j] = A[(k + i) + (int64_t)(k + j) * lda];
-  }
-  __syncthreads();
-  for (int c = 0; c < nb; ++c) {
-    if (tid == 0) {
-      double d = S[c][c].x;
+  const int tr = threadIdx.x & 15, ts = threadIdx.x >> 4;
+  z S[4][4], X[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int r = tr + 16 * i, s = ts + 16 * j;
+      X[i][j] = z{r == s ? 1.0 : 0.0, 0.0};
+      S[i][j] = X[i][j];
+      if (r < nb && s <= r) S[i][j] = A[(k + r) + (int64_t)(k + s) * lda];
+    }
+#pragma unroll
+  for (int cj = 0; cj < 4; ++cj) {
+    for (int cc = 0; cc < 16; ++cc) {
+      const int c = 16 * cj + cc, buf = c & 1;
+      if (ts == cc) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) col[buf][tr + 16 * i] = S[i][cj];
+      }
+      if (tr == cc) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) row[buf][ts + 16 * j] = X[cj][j];
+      }
+      __syncthreads();
+      double d = col[buf][c].x;
       if (!(d > 0.0) || !isfinite(d)) {
-        if (*info == 0) *info = k + c + 1;
+        if (threadIdx.x == 0 && *info == 0) *info = k + c + 1;
         d = 1.0;
       }
-      piv = sqrt(d);
-      S[c][c] = z{piv, 0.0};
-    }
-    __syncthreads();
-    const double inv = 1.0 / piv;
-    for (int r = c + 1 + tid; r < nb; r += 256) S[r][c] = z{S[r][c].x * inv, S[r][c].y * inv};
-    __syncthreads();
-    const int rem = nb - c - 1;
-    for (int e = tid; e < rem * rem; e += 256) {
-      const int r = c + 1 + e % rem, s = c + 1 + e / rem;
-      if (s <= r) {
-        const z a = S[r][c], b = S[s][c];
-        S[r][s] = z{S[r][s].x - (a.x * b.x + a.y * b.y), S[r][s].y - (a.y * b.x - a.x * b.y)};
+      if (threadIdx.x == 0) piv[c] = d;
+      const double inv = 1.0 / d;
+      z m[4], x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int s = ts + 16 * j;
+        m[j] = s > c ? zconj(col[buf][s]) : z{0.0, 0.0};
+        x[j] = row[buf][s];
+      }
+#pragma unroll
+      for (int i = cj; i < 4; ++i) {
+        const int r = tr + 16 * i;
+        const z v = col[buf][r];
+        const z l = r > c ? z{-v.x * inv, -v.y * inv} : z{0.0, 0.0};
+#pragma unroll
+        for (int j = cj; j < 4; ++j) S[i][j] = zfma(S[i][j], l, m[j]);
+#pragma unroll
+        for (int j = 0; j <= cj; ++j) X[i][j] = zfma(X[i][j], l, x[j]);
       }
     }
-    __syncthreads();
-  }
-  for (int e = tid; e < nb * nb; e += 256) {
-    const int i = e % nb, j = e / nb;
-    A[(k + i) + (int64_t)(k + j) * lda] = i >= j ? S[i][j] : z{0.0, 0.0};
-  }
-}
-
-// Rows below the diagonal block: L[r, k:k+nb] = A[r, k:k+nb] L_kk^{-H}.
-// One thread per row; x L_kk^H = a solved by forward substitution.
-__global__ void __launch_bounds__(256) k_potrf_panel(int n, z* A, int64_t lda, int k) {
-  __shared__ z Lk[CB][CB + 1];
-  const int nb = min(CB, n - k);
-  for (int e = threadIdx.x; e < nb * nb; e += 256) {
-    const int i = e % nb, j = e / nb;
-    Lk[i][j] = A[(k + i) + (int64_t)(k + j) * lda];
   }
   __syncthreads();
-  const int r = k + nb + blockIdx.x * 256 + threadIdx.x;
-  if (r >= n) return;
-  z x[CB];
-  for (int c = 0; c < nb; ++c) {
-    z a = A[r + (int64_t)(k + c) * lda];
-    for (int s = 0; s < c; ++s) {
-      // a -= x_s * conj(L[c][s])
-      const z l = Lk[c][s];
-      a.x -= x[s].x * l.x + x[s].y * l.y;
-      a.y -= x[s].y * l.x - x[s].x * l.y;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int r = tr + 16 * i, s = ts + 16 * j;
+      const double ir = 1.0 / sqrt(piv[r]), is = 1.0 / sqrt(piv[s]);
+      dinv[r + CB * s] = z{X[i][j].x * ir, X[i][j].y * ir};
+      if (r < nb && s < nb)
+        A[(k + r) + (int64_t)(k + s) * lda] =
+            r > s ? z{S[i][j].x * is, S[i][j].y * is} : z{r == s ? sqrt(piv[s]) : 0.0, 0.0};
     }
-    const double d = Lk[c][c].x;
-    x[c] = z{a.x / d, a.y / d};
-  }
-  for (int c = 0; c < nb; ++c) A[r + (int64_t)(k + c) * lda] = x[c];
 }
 
 __global__ void k_zero_upper(int n, z* A, int64_t lda) {
@@ -440,21 +463,28 @@ __global__ void k_zero_upper(int n, z* A, int64_t lda) {
   }
 }
 
-fx_status zpotrf(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int64_t lda, int* info_dev) {
+fx_status zpotrf(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int64_t lda, void* dinv, int* info_dev) {
   z* a = (z*)A;
   for (int k = 0; k < n; k += CB) {
     const int nb = std::min(CB, n - k);
-    hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, st, n, a, lda, k, info_dev);
+    z* di = (z*)dinv + (int64_t)k * CB;
+    hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, st, n, a, lda, k, di, info_dev);
     FX_LAUNCH_CHECK();
     const int rest = n - k - nb;
     if (rest <= 0) break;
-    hipLaunchKernelGGL(k_potrf_panel, dim3((rest + 255) / 256), dim3(256), 0, st, n, a, lda, k);
-    FX_LAUNCH_CHECK();
-    // trailing update A22 -= L21 L21^H
     z* L21 = a + (k + nb) + (int64_t)k * lda;
     z* A22 = a + (k + nb) + (int64_t)(k + nb) * lda;
+    // rows below: L21 = A21 L_kk^{-H}, in place (a workgroup holds all CB
+    // columns of its rows and stores them after its last read)
+    ZgArgs g{rest, nb, nb, L21, lda, 0, di, CB, 0, L21, lda, 0, z{1.0, 0.0}, z{0.0, 0.0}, 1, (nb + ZK - 1) / ZK * ZK,
+             (rest + 31) / 32, 1, nullptr, ZgShape{}};
+    using T = ZgTile<1, 2, 2>;
+    static_assert(T::BN == CB, "a panel row's columns must be one tile");
+    hipLaunchKernelGGL((k_zgemm<0, 1, 1, 2, 2>), dim3((unsigned)g.tiles_m), dim3(T::NT), T::kLds, st, g);
+    FX_LAUNCH_CHECK();
+    // trailing update A22 -= L21 L21^H, lower part
     FX_TRY(zgemm(ctx, ws, st, 0, 1, rest, rest, nb, z{-1.0, 0.0}, L21, lda, L21, lda, z{1.0, 0.0}, A22, lda, 1, 0,
-                 0, 0, 1));
+                 0, 0, 1, ZgShape{kZgHermitian}));
   }
   hipLaunchKernelGGL(k_zero_upper, dim3(std::min(((int64_t)n * n + 255) / 256, (int64_t)4096)), dim3(256), 0, st, n,
                      a, lda);
@@ -463,66 +493,38 @@ fx_status zpotrf(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int
 }
 
 // ---------------------------------------------------------------------------
-// Inverse of a lower triangular matrix, in place.
+// Inverse of a lower triangular matrix, in place, from the inverses of its CB x
+// CB diagonal blocks: neighbouring blocks of s = CB, 2 CB, ... are joined by
+// inv([[P, 0], [Q, R]]) = [[inv P, 0], [-inv R Q inv P, inv R]], all pairs of a
+// level in one batched product each (two launches per level).
 // ---------------------------------------------------------------------------
-// Diagonal block (nb <= CB) at (k, k) inverted by forward substitution, one
-// thread per column.
-__global__ void __launch_bounds__(64) k_trinv_diag(z* A, int64_t lda, int k, int nb) {
-  __shared__ z S[CB][CB + 1];
-  __shared__ z X[CB][CB + 1];
-  for (int e = threadIdx.x; e < nb * nb; e += 64) {
-    const int i = e % nb, j = e / nb;
-    S[i][j] = A[(k + i) + (int64_t)(k + j) * lda];
-  }
-  __syncthreads();
-  const int c = threadIdx.x;
-  if (c < nb) {
-    for (int r = 0; r < nb; ++r) X[r][c] = z{0.0, 0.0};
-    const z d = S[c][c];
-    const double dd = d.x * d.x + d.y * d.y;
-    X[c][c] = z{d.x / dd, -d.y / dd};
-    for (int r = c + 1; r < nb; ++r) {
-      z s = {0.0, 0.0};
-      for (int q = c; q < r; ++q) s = zfma(s, S[r][q], X[q][c]);
-      const z l = S[r][r];
-      const double ll = l.x * l.x + l.y * l.y;
-      // X[r][c] = -s / l
-      X[r][c] = z{-(s.x * l.x + s.y * l.y) / ll, -(s.y * l.x - s.x * l.y) / ll};
-    }
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < nb * nb; e += 64) {
-    const int i = e % nb, j = e / nb;
-    A[(k + i) + (int64_t)(k + j) * lda] = X[i][j];
+__global__ void __launch_bounds__(256) k_place_diag(int n, z* A, int64_t lda, const z* __restrict__ dinv) {
+  const int k = blockIdx.x * CB, nb = min(CB, n - k);
+  for (int e = threadIdx.x; e < CB * CB; e += 256) {
+    const int i = e % CB, j = e / CB;
+    if (i < nb && j < nb) A[(k + i) + (int64_t)(k + j) * lda] = dinv[(int64_t)k * CB + e];
   }
 }
 
-// inv([[P, 0], [Q, R]]) = [[inv P, 0], [-inv R Q inv P, inv R]] on rows/cols
-// [k, k+n), split at n1.
-static fx_status trinv_rec(fx_ctx* ctx, Workspace* ws, hipStream_t st, z* A, int64_t lda, int k, int n, z* T) {
-  if (n <= CB) {
-    hipLaunchKernelGGL(k_trinv_diag, dim3(1), dim3(64), 0, st, A, lda, k, n);
-    FX_LAUNCH_CHECK();
-    return FX_OK;
-  }
-  int n1 = (n / 2 + CB - 1) / CB * CB;
-  if (n1 >= n) n1 = n - CB;
-  const int n2 = n - n1;
-  FX_TRY(trinv_rec(ctx, ws, st, A, lda, k, n1, T));
-  FX_TRY(trinv_rec(ctx, ws, st, A, lda, k + n1, n2, T));
-  z* P = A + k + (int64_t)k * lda;
-  z* Q = A + (k + n1) + (int64_t)k * lda;
-  z* R = A + (k + n1) + (int64_t)(k + n1) * lda;
-  // T = Q inv(P)   (n2 x n1), then Q = -inv(R) T
-  FX_TRY(zgemm(ctx, ws, st, 0, 0, n2, n1, n1, z{1.0, 0.0}, Q, lda, P, lda, z{0.0, 0.0}, T, n2, 1, 0, 0, 0, 1));
-  FX_TRY(zgemm(ctx, ws, st, 0, 0, n2, n1, n2, z{-1.0, 0.0}, R, lda, T, n2, z{0.0, 0.0}, Q, lda, 1, 0, 0, 0, 1));
-  return FX_OK;
-}
-
-fx_status ztrinv(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int64_t lda) {
-  void* T = nullptr;
+fx_status ztrinv(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* Av, int64_t lda, const void* dinv) {
+  z* A = (z*)Av;
+  hipLaunchKernelGGL(k_place_diag, dim3((n + CB - 1) / CB), dim3(256), 0, st, n, A, lda, (const z*)dinv);
+  FX_LAUNCH_CHECK();
+  if (n <= CB) return FX_OK;
+  void* T = nullptr;  // the pairs of a level hold s x s each: never more than n x n together
   FX_TRY(ws_get(ctx, ws, "trinv_T", sizeof(z) * (size_t)n * n, &T));
-  return trinv_rec(ctx, ws, st, (z*)A, lda, 0, n, (z*)T);
+  for (int s = CB; s < n; s *= 2) {
+    const int pairs = (n - s + 2 * s - 1) / (2 * s);
+    const int64_t step = (int64_t)2 * s * (1 + lda);
+    // rows of Q and R of pair p: min(s, n - s - 2 s p)
+    z* Q = A + s;
+    z* R = A + s + (int64_t)s * lda;
+    FX_TRY(zgemm(ctx, ws, st, 0, 0, s, s, s, z{1.0, 0.0}, Q, lda, A, lda, z{0.0, 0.0}, T, s, pairs, step, step,
+                 (int64_t)s * s, 1, ZgShape{kZgBLower, n - s, 2 * s}));
+    FX_TRY(zgemm(ctx, ws, st, 0, 0, s, s, s, z{-1.0, 0.0}, R, lda, T, s, z{0.0, 0.0}, Q, lda, pairs, step,
+                 (int64_t)s * s, step, 1, ZgShape{kZgALower, n - s, 2 * s}));
+  }
+  return FX_OK;
 }
 
 fx_status zherm(hipStream_t st, int n, const void* M, int64_t ldm, void* H, void* Aneg, double* ex_dev) {

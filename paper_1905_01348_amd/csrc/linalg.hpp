@@ -5,21 +5,37 @@
 
 namespace fx {
 
+// What a product may leave out: output tiles strictly above the diagonal of a
+// Hermitian C (the strict upper part is then undefined), and the zeros of a
+// triangular operand (B upper: B(k, n) = 0 for k > n; B lower, A lower).  With
+// mlim > 0, product b of the batch has min(M, mlim - b * mstep) rows (and, with
+// A lower, as many k).
+constexpr int kZgHermitian = 1, kZgBUpper = 2, kZgALower = 4, kZgBLower = 8;
+struct ZgShape {
+  int flags = 0, mlim = 0, mstep = 0;
+};
+
 // C = alpha op(A) op(B) + beta C (complex double, column-major), op 0 = N,
 // 1 = conjugate transpose; `batch` independent products with element strides
 // sA, sB, sC.  nsplit_hint > 0 fixes the number of K splits (1 = none);
 // 0 chooses one.  Split partial sums are reduced in FP64 in a fixed order.
 fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, int M, int N, int K, cpx<double> alpha,
                 const void* A, int64_t lda, const void* B, int64_t ldb, cpx<double> beta, void* C, int64_t ldc,
-                int batch, int64_t sA, int64_t sB, int64_t sC, int nsplit_hint);
+                int batch, int64_t sA, int64_t sB, int64_t sC, int nsplit_hint, ZgShape shape = {});
 
-// In-place blocked Cholesky A = L L^H (lower; the strict upper part is
-// zeroed).  *info_dev (device int, must start at 0) receives 1 + the first
+// In-place blocked Cholesky A = L L^H (lower; reads the lower part only, the
+// strict upper part is zeroed).  dinv (kCholBlock values per column, n rounded
+// up to a whole block) receives the inverses of L's diagonal blocks for
+// ztrinv.  *info_dev (device int, must start at 0) receives 1 + the first
 // column whose pivot was not positive, or stays 0.
-fx_status zpotrf(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int64_t lda, int* info_dev);
+constexpr int kCholBlock = 64;
+inline size_t chol_dinv_bytes(int n) {
+  return (size_t)16 * kCholBlock * ((n + kCholBlock - 1) / kCholBlock * kCholBlock);
+}
+fx_status zpotrf(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int64_t lda, void* dinv, int* info_dev);
 
-// In-place inverse of a lower triangular n x n matrix.
-fx_status ztrinv(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int64_t lda);
+// In-place inverse of the lower triangular n x n factor of zpotrf.
+fx_status ztrinv(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int64_t lda, const void* dinv);
 
 // H = (M + M^H)/2 (n x n, ld n), Aneg = -H, *ex_dev = 1/2 Re tr H (nullable).
 fx_status zherm(hipStream_t st, int n, const void* M, int64_t ldm, void* H, void* Aneg, double* ex_dev);

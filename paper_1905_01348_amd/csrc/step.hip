@@ -226,7 +226,9 @@ static fx_status orthonormalize(fx_ctx* ctx, void* psi, int n, int64_t ld, int64
   // the info flag must start at zero; this call waits on the host below and
   // is never captured
   FX_HIP(hipMemsetAsync(info_dev, 0, sizeof(int), st));
-  FX_TRY(zpotrf(ctx, ws, st, n, L, n, info_dev));
+  void* dinv = nullptr;
+  FX_TRY(ws_get(ctx, ws, "chol_dinv", chol_dinv_bytes(n), &dinv));
+  FX_TRY(zpotrf(ctx, ws, st, n, L, n, dinv, info_dev));
   int info = 0;
   FX_HIP(hipMemcpyAsync(&info, info_dev, sizeof(int), hipMemcpyDeviceToHost, st));
   FX_HIP(hipStreamSynchronize(st));
@@ -234,7 +236,7 @@ static fx_status orthonormalize(fx_ctx* ctx, void* psi, int n, int64_t ld, int64
     FX_FAIL(FX_ERR_NOT_POSDEF, "the overlap Psi^H Psi is not positive definite (pivot %d of %d): the orbitals are "
             "linearly dependent", info, n);
   // Q = Psi L^{-H}, then back into psi
-  FX_TRY(ztrinv(ctx, ws, st, n, L, n));
+  FX_TRY(ztrinv(ctx, ws, st, n, L, n, dinv));
   FX_TRY(zconj_transpose(st, n, L, n, LinvH, n));
   FX_TRY(zgemm(ctx, ws, st, 0, 0, (int)nr, n, n, cpx<double>{1, 0}, p64, ldp, LinvH, n, cpx<double>{0, 0}, Q, nr, 1,
                0, 0, 0, 1));

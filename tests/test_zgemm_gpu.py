@@ -41,3 +41,27 @@ def test_fp64_apply_at_tile_edges(ctx, N, R):
     assert np.array_equal(one[0], got[R - 1])
     torch.cuda.synchronize()
     ace.free()
+
+
+@pytest.mark.parametrize("N", [1, 63, 64, 65, 129, 192, 300])
+def test_cholesky_qr_at_block_edges(ctx, N):
+    """Blocks of 64 columns, joined in pairs by level: below, at and above one block, a level whose last
+    pair is short, three levels.  Against numpy's Cholesky factor; the overlap of random vectors has a
+    condition number below 100, so N eps cond stays under 1e-11."""
+    import torch
+
+    n3 = (16, 12, 18)
+    psi = synth.random_grid_vectors(5, n3, N)
+    say("cholesky-qr", N)
+    p = psi.reshape(N, -1)
+    low = np.linalg.cholesky(p.conj() @ p.T)
+    ref = np.linalg.solve(low.conj(), p)
+    got = host(ctx.orthonormalize(dev(psi))).reshape(N, -1)
+    torch.cuda.synchronize()
+    assert rel_err(got, ref) <= 1e-11
+    # a zero column (pivot exactly 0) is found, and the block is left as it was
+    psi[N - 1] = 0.0
+    q = dev(psi)
+    with pytest.raises(Exception, match=f"pivot {N} of {N}"):
+        ctx.orthonormalize(q)
+    assert np.array_equal(host(q), psi)
