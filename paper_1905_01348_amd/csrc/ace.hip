@@ -131,25 +131,15 @@ fx_status ace_build_impl(fx_ctx* ctx, Workspace* ws, const fx_cell* cell, const 
     set_error("-M is not positive definite (pivot %d of %d); ACE needs a negative definite Psi^H V_X Psi", info, n);
     return fail(FX_ERR_NOT_POSDEF);
   }
-  // xi = W L^{-H}: Linv = L^{-1}, LinvH = Linv^H, xi = W LinvH
-  void *Linv = nullptr, *LinvH = nullptr;
+  // xi = W Linv^H in place of W: the handle keeps that array
+  void* Linv = nullptr;
   if ((s = ws_get(ctx, ws, "ace_Linv", zsz * n * n, &Linv)) != FX_OK) return fail(s);
-  if ((s = ws_get(ctx, ws, "ace_LinvH", zsz * n * n, &LinvH)) != FX_OK) return fail(s);
   if (hipMemcpyAsync(Linv, a->L, zsz * n * n, hipMemcpyDeviceToDevice, st) != hipSuccess) return fail(FX_ERR_DEVICE);
   if ((s = ztrinv(ctx, ws, st, n, Linv, n, dinv)) != FX_OK) return fail(s);
-  if ((s = zconj_transpose(st, n, Linv, n, LinvH, n)) != FX_OK) return fail(s);
-  if ((s = ace_alloc(a, zsz * nr * n, &a->xi)) != FX_OK) return fail(s);
-  if ((s = zgemm(ctx, ws, st, 0, 0, (int)nr, n, n, cpx<double>{1, 0}, W, nr, LinvH, n, cpx<double>{0, 0}, a->xi, nr,
-                 1, 0, 0, 0, 1)) != FX_OK)
-    return fail(s);
-  // W is no longer needed
+  if ((s = zmul_upper_inplace(ctx, st, (int)nr, n, W, nr, Linv, n)) != FX_OK) return fail(s);
+  a->xi = W;
+  // the factors are complete when the call returns, for applies on any stream
   if (hipStreamSynchronize(st) != hipSuccess) return fail(FX_ERR_DEVICE);
-  for (auto it = a->owned.begin(); it != a->owned.end(); ++it)
-    if (it->first == W) {
-      ctx_free(ctx, it->first, it->second);
-      a->owned.erase(it);
-      break;
-    }
   // split forms for the requested precision
   if (ace_prec != FX_PREC_ACE_FP64) {
     if ((s = ace_prepare_split(a, ace_prec, st)) != FX_OK) return fail(s);

@@ -40,7 +40,8 @@ fx_status ztrinv(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int
 // H = (M + M^H)/2 (n x n, ld n), Aneg = -H, *ex_dev = 1/2 Re tr H (nullable).
 fx_status zherm(hipStream_t st, int n, const void* M, int64_t ldm, void* H, void* Aneg, double* ex_dev);
 
-// B = A^H (n x n).
-fx_status zconj_transpose(hipStream_t st, int n, const void* A, int64_t lda, void* B, int64_t ldb);
+// X <- X Linv^H in place: X is M x n (ldx), Linv lower triangular n x n.
+fx_status zmul_upper_inplace(fx_ctx* ctx, hipStream_t st, int M, int n, void* X, int64_t ldx, const void* Linv,
+                             int64_t ldl);
 
 }  // namespace fx

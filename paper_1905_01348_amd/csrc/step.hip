@@ -211,17 +211,12 @@ static fx_status orthonormalize(fx_ctx* ctx, void* psi, int n, int64_t ld, int64
   const void* p64;
   int64_t ldp;
   FX_TRY(as_c128(ctx, ws, "on_psi", psi, ld, dt, nr, n, st, &p64, &ldp));
-  void *S = nullptr, *L = nullptr, *scratch = nullptr, *LinvH = nullptr, *Q = nullptr, *scal = nullptr;
-  FX_TRY(ws_get(ctx, ws, "on_S", zsz * n * n, &S));
+  void *L = nullptr, *scal = nullptr;
   FX_TRY(ws_get(ctx, ws, "on_L", zsz * n * n, &L));
-  FX_TRY(ws_get(ctx, ws, "on_neg", zsz * n * n, &scratch));
-  FX_TRY(ws_get(ctx, ws, "on_LinvH", zsz * n * n, &LinvH));
-  FX_TRY(ws_get(ctx, ws, "on_Q", zsz * nr * n, &Q));
   FX_TRY(ws_get(ctx, ws, "on_scal", 64, &scal));
-  // S = Psi^H Psi, Hermitised into L, Cholesky S = L L^H in place
-  FX_TRY(zgemm(ctx, ws, st, 1, 0, n, n, (int)nr, cpx<double>{1, 0}, p64, ldp, p64, ldp, cpx<double>{0, 0}, S, n, 1, 0,
-               0, 0, 0));
-  FX_TRY(zherm(st, n, S, n, L, scratch, nullptr));
+  // S = Psi^H Psi: its lower tiles, factored in place (S = L L^H)
+  FX_TRY(zgemm(ctx, ws, st, 1, 0, n, n, (int)nr, cpx<double>{1, 0}, p64, ldp, p64, ldp, cpx<double>{0, 0}, L, n, 1, 0,
+               0, 0, 0, ZgShape{kZgHermitian}));
   int* info_dev = (int*)scal;
   // the info flag must start at zero; this call waits on the host below and
   // is never captured
@@ -235,12 +230,10 @@ static fx_status orthonormalize(fx_ctx* ctx, void* psi, int n, int64_t ld, int64
   if (info != 0)
     FX_FAIL(FX_ERR_NOT_POSDEF, "the overlap Psi^H Psi is not positive definite (pivot %d of %d): the orbitals are "
             "linearly dependent", info, n);
-  // Q = Psi L^{-H}, then back into psi
+  // Psi <- Psi L^{-H} in place
   FX_TRY(ztrinv(ctx, ws, st, n, L, n, dinv));
-  FX_TRY(zconj_transpose(st, n, L, n, LinvH, n));
-  FX_TRY(zgemm(ctx, ws, st, 0, 0, (int)nr, n, n, cpx<double>{1, 0}, p64, ldp, LinvH, n, cpx<double>{0, 0}, Q, nr, 1,
-               0, 0, 0, 1));
-  FX_TRY(convert_cols(Q, FX_C128, nr, psi, dt, ld, nr, n, st));
+  FX_TRY(zmul_upper_inplace(ctx, st, (int)nr, n, const_cast<void*>(p64), ldp, L, n));
+  if (dt == FX_C64) FX_TRY(convert_cols(p64, FX_C128, ldp, psi, dt, ld, nr, n, st));
   return FX_OK;
 }
 
