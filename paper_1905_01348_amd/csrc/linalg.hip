@@ -74,6 +74,7 @@ struct ZgArgs {
   int nsplit, kchunk, tiles_m, tiles_n;
   z* partial;
   ZgShape shape;
+  ZgResidual res;
 };
 
 template <int WM, int WN, int WNW>
@@ -227,6 +228,11 @@ __global__ void __launch_bounds__(128 * WNW, WM * WN <= 4 ? 4 : 2) k_zgemm(const
         const z s = {cr[i][j][e], ci[i][j][e]};
         if (P) {
           P[m + (int64_t)n * M] = s;
+        } else if (g.res.psi) {
+          // psi - half + i hdt (h - s), s = (Psi S)(m, n)
+          const z p = g.res.psi[m + (int64_t)n * g.res.ldp], f = g.res.half[m + (int64_t)n * g.res.ldf];
+          const z h = g.res.h[m + (int64_t)n * g.res.ldh];
+          Cb[m + (int64_t)n * g.ldc] = z{p.x - f.x - g.res.hdt * (h.y - s.y), p.y - f.y + g.res.hdt * (h.x - s.x)};
         } else {
           z r = cmul(g.alpha, s);
           if (!bz0) r = cadd(r, cmul(g.beta, Cb[m + (int64_t)n * g.ldc]));
@@ -270,7 +276,7 @@ static unsigned reduce_blocks(int64_t elems) { return (unsigned)std::max<int64_t
 
 fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, int M, int N, int K, z alpha,
                 const void* A, int64_t lda, const void* B, int64_t ldb, z beta, void* C, int64_t ldc, int batch,
-                int64_t sA, int64_t sB, int64_t sC, int nsplit_hint, ZgShape shape) {
+                int64_t sA, int64_t sB, int64_t sC, int nsplit_hint, ZgShape shape, ZgResidual res) {
   if (M <= 0 || N <= 0) return FX_OK;
   if (K <= 0) {
     // empty sum: C = beta C (no splits to add)
@@ -305,7 +311,7 @@ fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, in
   const bool big = tiles_of(64, 64) * nsplit >= n_cu;
   const int bm = big ? 64 : 32, bn = bm;
   ZgArgs g{M, N, K, (const z*)A, lda, sA, (const z*)B, ldb, sB, (z*)C, ldc, sC, alpha, beta, nsplit, kchunk,
-           (M + bm - 1) / bm, (N + bn - 1) / bn, part, shape};
+           (M + bm - 1) / bm, (N + bn - 1) / bn, part, shape, res};
   const dim3 grid((unsigned)(tiles_of(bm, bn) * nsplit));
   int slot;
   FX_TRY(prof_begin(ctx, st, opa ? FX_K_GEMM_CN : FX_K_GEMM_NN, 8.0 * M * N * (double)K * batch, &slot));

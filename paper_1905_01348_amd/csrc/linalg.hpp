@@ -15,13 +15,23 @@ struct ZgShape {
   int flags = 0, mlim = 0, mstep = 0;
 };
 
+// With psi set, C = psi - half + i hdt (h - op(A) op(B)) instead (alpha and beta
+// unused, nsplit 1): the residual of the PT-CN step formed where its last
+// product ends.  Columns at psi + c*ldp, and so on.
+struct ZgResidual {
+  const cpx<double>*psi = nullptr, *half = nullptr, *h = nullptr;
+  int64_t ldp = 0, ldf = 0, ldh = 0;
+  double hdt = 0.0;
+};
+
 // C = alpha op(A) op(B) + beta C (complex double, column-major), op 0 = N,
 // 1 = conjugate transpose; `batch` independent products with element strides
 // sA, sB, sC.  nsplit_hint > 0 fixes the number of K splits (1 = none);
 // 0 chooses one.  Split partial sums are reduced in FP64 in a fixed order.
 fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, int M, int N, int K, cpx<double> alpha,
                 const void* A, int64_t lda, const void* B, int64_t ldb, cpx<double> beta, void* C, int64_t ldc,
-                int batch, int64_t sA, int64_t sB, int64_t sC, int nsplit_hint, ZgShape shape = {});
+                int batch, int64_t sA, int64_t sB, int64_t sC, int nsplit_hint, ZgShape shape = {},
+                ZgResidual res = {});
 
 // In-place blocked Cholesky A = L L^H (lower; reads the lower part only, the
 // strict upper part is zeroed).  dinv (kCholBlock values per column, n rounded

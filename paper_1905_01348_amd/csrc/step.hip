@@ -12,31 +12,6 @@
 
 namespace fx {
 
-// r = psi - half + (i hdt) hpsi, all FP64, column c at base + c*ld.
-__global__ void __launch_bounds__(256) k_residual_init(const cpx<double>* __restrict__ psi, int64_t ldp,
-                                                       const cpx<double>* __restrict__ hpsi, int64_t ldh,
-                                                       const cpx<double>* __restrict__ half, int64_t ldf,
-                                                       cpx<double>* __restrict__ r, int64_t ldr, int64_t nr, int n,
-                                                       double hdt) {
-  const int64_t total = nr * n;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t c = i / nr, e = i - c * nr;
-    const cpx<double> p = psi[c * ldp + e], h = hpsi[c * ldh + e], f = half[c * ldf + e];
-    r[c * ldr + e] = cpx<double>{p.x - f.x - hdt * h.y, p.y - f.y + hdt * h.x};
-  }
-}
-
-// dst += src, n columns of nr FP64 complex values.
-__global__ void __launch_bounds__(256) k_add_cols(cpx<double>* __restrict__ dst, int64_t ldd,
-                                                  const cpx<double>* __restrict__ src, int64_t lds, int64_t nr, int n) {
-  const int64_t total = nr * n;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t c = i / nr, e = i - c * nr;
-    const cpx<double> a = dst[c * ldd + e], b = src[c * lds + e];
-    dst[c * ldd + e] = cpx<double>{a.x + b.x, a.y + b.y};
-  }
-}
-
 // the constant 1 at nr points
 template <typename T>
 __global__ void __launch_bounds__(256) k_fill_one(cpx<T>* __restrict__ p, int64_t nr) {
@@ -96,9 +71,11 @@ static bool overlaps(const void* a, int n, int64_t lda, const void* b, int m, in
 // out = -(1/2) Laplacian phi on the periodic grid: each planewave coefficient
 // times |G|^2/2 (Sec. 2).  It is the pair path with the constant orbital 1 as
 // its only psi and |G|^2/(2 N_r) as its kernel, in FP64: conj(1) phi = phi,
-// the FFT, the symbol, the inverse FFT, times 1.
+// the FFT, the symbol, the inverse FFT, times 1.  With `add` (complex128
+// columns) the sum starts from it: out = add + T phi.
 static fx_status apply_kinetic(fx_ctx* ctx, Workspace* ws, const fx_cell* cell, const void* phi, int n,
-                               int64_t ld, fx_dtype din, void* out, int64_t ld_out, fx_dtype dout, hipStream_t st) {
+                               int64_t ld, fx_dtype din, void* out, int64_t ld_out, fx_dtype dout, hipStream_t st,
+                               const void* add = nullptr, int64_t ld_add = 0) {
   FX_TRY(check_cell(cell));
   if (din != FX_C128 && din != FX_C64) FX_FAIL(FX_ERR_UNSUPPORTED, "unknown in_dtype %d", din);
   const int64_t nr = (int64_t)cell->n[0] * cell->n[1] * cell->n[2];
@@ -125,6 +102,8 @@ static fx_status apply_kinetic(fx_ctx* ctx, Workspace* ws, const fx_cell* cell, 
   va.in_dtype = din;
   va.out_dtype = dout;
   va.prec = FX_PREC_FP64;
+  va.add = add;
+  va.ld_add = ld_add;
   return vx_apply(ctx, ws, va, st, nullptr);
 }
 
@@ -175,10 +154,7 @@ static fx_status pt_residual(fx_ctx* ctx, const fx_cell* cell, const fx_kernel* 
     // H Psi + T Psi in a buffer of the library's (hpsi may be the caller's)
     void* kin = nullptr;
     FX_TRY(ws_get(ctx, ws, "pt_kin", (size_t)16 * nr * n, &kin));
-    FX_TRY(apply_kinetic(ctx, ws, cell, psi, n, ld, dt, kin, nr, FX_C128, st));
-    hipLaunchKernelGGL(k_add_cols, dim3(grid_for(nr * n)), dim3(256), 0, st, (cpx<double>*)kin, nr,
-                       (const cpx<double>*)h64, ldh, nr, n);
-    FX_LAUNCH_CHECK();
+    FX_TRY(apply_kinetic(ctx, ws, cell, psi, n, ld, dt, kin, nr, FX_C128, st, h64, ldh));
     h64 = kin;
     ldh = nr;
   }
@@ -187,19 +163,17 @@ static fx_status pt_residual(fx_ctx* ctx, const fx_cell* cell, const fx_kernel* 
   if (!S) FX_TRY(ws_get(ctx, ws, "pt_S", (size_t)16 * n * n, &S));
   FX_TRY(zgemm(ctx, ws, st, 1, 0, n, n, (int)nr, cpx<double>{1, 0}, p64, ldp, h64, ldh, cpx<double>{0, 0}, S, n, 1, 0,
                0, 0, 0));
-  // R = Psi - Psi_half + (i dt/2) H Psi, then R += (-i dt/2) Psi S
+  // R = Psi - Psi_half + (i dt/2) (H Psi - Psi S), formed where Psi S ends
   void* r64 = r;
   int64_t ldr64 = ldr;
   if (dt == FX_C64) {
     FX_TRY(ws_get(ctx, ws, "pt_r64", (size_t)16 * nr * n, &r64));
     ldr64 = nr;
   }
-  const double hdt = 0.5 * dtime;
-  hipLaunchKernelGGL(k_residual_init, dim3(grid_for(nr * n)), dim3(256), 0, st, (const cpx<double>*)p64, ldp,
-                     (const cpx<double>*)h64, ldh, (const cpx<double>*)f64, ldf, (cpx<double>*)r64, ldr64, nr, n, hdt);
-  FX_LAUNCH_CHECK();
-  FX_TRY(zgemm(ctx, ws, st, 0, 0, (int)nr, n, n, cpx<double>{0, -hdt}, p64, ldp, S, n, cpx<double>{1, 0}, r64, ldr64,
-               1, 0, 0, 0, 1));
+  const ZgResidual res{(const cpx<double>*)p64, (const cpx<double>*)f64, (const cpx<double>*)h64, ldp, ldf, ldh,
+                       0.5 * dtime};
+  FX_TRY(zgemm(ctx, ws, st, 0, 0, (int)nr, n, n, cpx<double>{1, 0}, p64, ldp, S, n, cpx<double>{0, 0}, r64, ldr64, 1,
+               0, 0, 0, 1, ZgShape{}, res));
   if (dt == FX_C64) FX_TRY(convert_cols(r64, FX_C128, ldr64, r, FX_C64, ldr, nr, n, st));
   return FX_OK;
 }

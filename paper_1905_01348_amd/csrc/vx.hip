@@ -399,7 +399,7 @@ static int ct_c_variant(const VxArgs& a) {
 // S = 1 (automatic) keeps one running sum per target; the allocation-free
 // form always does.
 static int ct_jsplit(const VxArgs& a) {
-  if (a.no_alloc) return 1;
+  if (a.no_alloc || a.add) return 1;
   return a.c_split == 2 || a.c_split == 4 || a.c_split == 8 ? a.c_split : 1;
 }
 
@@ -588,6 +588,11 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
     acc = reinterpret_cast<cpx<A>*>(p);
     ld_acc = nr;
     gstride = (int64_t)a.n_phi * nr;
+  } else if (a.add) {
+    // the one batch of each target starts from the caller's columns
+    if (multi_j || sizeof(A) != 8) FX_FAIL(FX_ERR_INVALID, "a start value needs one orbital and FP64 sums");
+    acc = reinterpret_cast<cpx<A>*>(const_cast<void*>(a.add));
+    ld_acc = a.ld_add;
   } else if (multi_j) {
     if (out_is_A) {
       acc = reinterpret_cast<cpx<A>*>(a.out);
@@ -623,7 +628,7 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
     const int kb = std::min(nk, a.n_phi - k0);
     for (int j0 = 0; j0 < a.n_psi; j0 += nj) {
       const int jb = std::min(nj, a.n_psi - j0);
-      const int first = j0 == 0, last = j0 + jb >= a.n_psi;
+      const int first = j0 == 0 && !a.add, last = j0 + jb >= a.n_psi;
       const int npairs = kb * jb;
       // algorithmic bytes of each pass, per pair and grid point: plane-forward
       // psi_j + T (phi_k is reused from cache across the batch's orbitals),

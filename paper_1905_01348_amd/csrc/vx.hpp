@@ -43,6 +43,9 @@ struct VxArgs {
   fx_dtype out_dtype = FX_C128;
   fx_prec prec = FX_PREC_FP64;
   double* ex_dev = nullptr;
+  // one orbital, out and precision FP64: complex128 columns the sums start from
+  const void* add = nullptr;
+  int64_t ld_add = 0;
   bool internal_kernel = false;  // kern may be the library's own kinetic kind
   // launch configuration (0 / -1 = automatic: the context's tuned
   // configuration for this grid and form if there is one, else defaults)
