@@ -148,7 +148,8 @@ fx_status fx_memory(const fx_ctx* ctx, size_t* in_use, size_t* peak);
  *       ascending j in the accumulation precision, so results are bitwise
  *       repeatable and independent of how the pairs are batched.
  * When phi == psi with n_phi == n_psi and ld_phi == ld_psi on a cubic grid of
- *       edge 24, 48, 72 or 96, each unordered pair is solved once (the kernel
+ *       edge 24, 48, 72 or 96 (and, for FP64 and FP32, on other grids with
+ *       enough orbitals), each unordered pair is solved once (the kernel
  *       is real and even, so the (k,j) solve is the conjugate of the (j,k)
  *       one): N(N+1)/2 solves instead of N^2.  Term j of column k is then taken
  *       from the solve of (min(j,k), max(j,k)); the result is still bitwise
@@ -238,8 +239,10 @@ typedef struct fx_vx_config {
   int32_t radix[3][4]; /* generic: radix schedule of each axis (x, y, z), stages in
                           order, 0-terminated; radices from {2,3,4,6,8,9,12} with
                           product n; an all-zero row is the default schedule */
-  int32_t c_split;     /* specialised plane-inverse pass: S sum groups per target (1, 2,
-                          4 or 8; 0 automatic = 1).  The terms of orbital j go to group
+  int32_t c_split;     /* plane-inverse pass: S sum groups per target (1, 2, 4 or 8;
+                          0 automatic: 1 for phi == psi, else as many as give eight
+                          targets on this grid the resident workgroups, at least four
+                          orbitals each; 1 if the budget cannot hold the sums).  The terms of orbital j go to group
                           j mod S, each group summed in ascending j, the groups added in
                           order at the end: S times the pass's work items for calls with
                           few targets, at S partial sums per target of device memory.

@@ -199,73 +199,154 @@ struct Dft {
   }
 };
 
-// ---- one radix-R stage over `count` transforms held in LDS -----------------
-// Element i of transform f is s[f*fs + i*es].  L is the current sub-transform
-// length and span = L/R.  tw[t] = exp(-2 pi i t/n), t < n.
+// ---- global accesses with a non-temporal hint --------------------------------
+// Data read or written once (the pair volume) need not displace data that is
+// reused from the caches (the orbital and target planes the workgroups of an
+// XCD share).  At 96^3 the hint took the three passes from 10.5 to 9.5 ms per
+// launch of 1170 pairs.
+template <typename T>
+struct Vec2;
+template <>
+struct Vec2<float> {
+  typedef float type __attribute__((ext_vector_type(2)));
+};
+template <>
+struct Vec2<double> {
+  typedef double type __attribute__((ext_vector_type(2)));
+};
+// The components of a run-time-plan stage's input as two loads (merged into one
+// by the backend): with one vector load the optimiser orders the sums of two
+// products in the butterflies differently, and so fuses the other product.
+template <bool NTS, typename T>
+FX_HD cpx<T> g_load2(const cpx<T>* p) {
+  if (!NTS) return *p;
+  const T* f = reinterpret_cast<const T*>(p);
+  return cpx<T>{__builtin_nontemporal_load(f), __builtin_nontemporal_load(f + 1)};
+}
+template <bool NTS, typename T>
+FX_HD cpx<T> g_load(const cpx<T>* p) {
+  if (!NTS) return *p;
+  const typename Vec2<T>::type v = __builtin_nontemporal_load(reinterpret_cast<const typename Vec2<T>::type*>(p));
+  return cpx<T>{v.x, v.y};
+}
+template <bool NTS, typename T>
+FX_HD void g_store(cpx<T>* p, cpx<T> a) {
+  if (!NTS) {
+    *p = a;
+    return;
+  }
+  typename Vec2<T>::type v;
+  v.x = a.x;
+  v.y = a.y;
+  __builtin_nontemporal_store(v, reinterpret_cast<typename Vec2<T>::type*>(p));
+}
+
+// ---- division by a run-time constant -----------------------------------------
+// floor(n / d) as one high multiply, exact for n d < 2^31 (m d exceeds 2^31 by
+// less than d); the hardware has no integer divide and the compiler's
+// sequence for it is about 25 instructions.
+struct FastDiv {
+  unsigned d, m;
+};
+FX_HD FastDiv fast_div(int d) { return {(unsigned)d, (unsigned)((0x80000000ull + d - 1) / d)}; }
+FX_HD int fdiv(int n, FastDiv f) { return (int)(((unsigned long long)(2u * (unsigned)n) * f.m) >> 32); }
+
+// ---- one radix-R stage over `count` transforms --------------------------------
+// Plan of an axis in kernel-argument form.  Stage st works on sub-transforms of
+// length L (n for the first) and has nb = n / R butterflies per transform;
+// span = L / R.
+struct AxisStage {
+  int R, L, span, tstep, nb;
+  FastDiv dspan;
+};
+struct AxisArg {
+  int n, nst;
+  AxisStage st[4];
+};
+
+// The transforms of a stage: f < count, those at or past lim are left out.
+struct Lines {
+  int count, lim;
+  FastDiv dcount;
+};
+
+// Where the elements of the transforms lie: element i of transform f at
+// p[f*fs + i*es] (LDS or global memory).
+template <typename T>
+struct Span {
+  cpx<T>* p;
+  int es, fs;
+};
+
+// Butterfly b of a stage, from `in` to `out`.  tw[t] = exp(-2 pi i t/n), t < n.
 // FWD: gather R points at stride span, DFT (sign -), multiply output k by
 //      w_L^{i2 k}, scatter back.  INV: the adjoint (conjugate twiddles first,
 //      DFT with sign +).
 // Butterflies are dealt to threads with consecutive threads on consecutive
-// transforms f.
-template <int R, bool FWD, typename T>
-FX_HD void stage_bfly(cpx<T>* s, int n, int L, int count, int es, int fs, const cpx<T>* tw, int b) {
-  const int span = L / R;
-  const int f = b % count;
-  const int q = b / count;
-  const int blk = q / span;
-  const int i2 = q - blk * span;
-  const int tstep = n / L;
-  const int base = f * fs + (blk * L + i2) * es;
-  const int step = span * es;
+// transforms f.  NTI / NTO: non-temporal reads / writes (global memory).
+template <int R, bool FWD, bool NTI, bool NTO, typename T>
+FX_HD void stage_bfly(Span<T> in, Span<T> out, const AxisStage& st, const Lines& ln, const cpx<T>* tw, int b) {
+  const int q = fdiv(b, ln.dcount);
+  const int f = b - q * ln.count;
+  if (f >= ln.lim) return;
+  const int blk = fdiv(q, st.dspan);
+  const int i2 = q - blk * st.span;
+  const int pos = blk * st.L + i2;
+  const cpx<T>* pi = in.p + (f * in.fs + pos * in.es);
+  const int si = st.span * in.es;
   cpx<T> x[R];
 #pragma unroll
-  for (int m = 0; m < R; ++m) x[m] = s[base + m * step];
+  for (int m = 0; m < R; ++m) x[m] = g_load2<NTI>(pi + m * si);
   // the last forward stage (first inverse stage) has span 1: i2 = 0 and
   // every twiddle is 1
+  const int t = i2 * st.tstep;
   if (FWD) {
     Dft<R, -1, T>::run(x);
-    if (span > 1) {
+    if (st.span > 1) {
 #pragma unroll
-      for (int k = 1; k < R; ++k) x[k] = cmul(x[k], tw[i2 * k * tstep]);
+      for (int k = 1; k < R; ++k) x[k] = cmul(x[k], tw[t * k]);
     }
   } else {
-    if (span > 1) {
+    if (st.span > 1) {
 #pragma unroll
-      for (int k = 1; k < R; ++k) x[k] = cmulc(x[k], tw[i2 * k * tstep]);
+      for (int k = 1; k < R; ++k) x[k] = cmulc(x[k], tw[t * k]);
     }
     Dft<R, 1, T>::run(x);
   }
+  cpx<T>* po = out.p + (f * out.fs + pos * out.es);
+  const int so = st.span * out.es;
 #pragma unroll
-  for (int m = 0; m < R; ++m) s[base + m * step] = x[m];
+  for (int m = 0; m < R; ++m) g_store<NTO>(po + m * so, x[m]);
 }
 
 // All butterflies of one stage, dealt round-robin to threads tid, tid+nthr, ...
-template <int R, bool FWD, typename T>
-FX_HD void stage_loop(cpx<T>* s, int n, int L, int count, int es, int fs, const cpx<T>* tw, int tid, int nthr) {
-  const int total = count * (n / R);
-  for (int b = tid; b < total; b += nthr) stage_bfly<R, FWD, T>(s, n, L, count, es, fs, tw, b);
+template <int R, bool FWD, bool NTI, bool NTO, typename T>
+FX_HD void stage_loop(Span<T> in, Span<T> out, const AxisStage& st, const Lines& ln, const cpx<T>* tw, int tid,
+                      int nthr) {
+  const int total = ln.count * st.nb;
+  for (int b = tid; b < total; b += nthr) stage_bfly<R, FWD, NTI, NTO, T>(in, out, st, ln, tw, b);
 }
 
-template <bool FWD, typename T>
-FX_HD void stage_dispatch(int R, cpx<T>* s, int n, int L, int count, int es, int fs, const cpx<T>* tw, int tid,
-                          int nthr) {
-  switch (R) {
-    case 2: stage_loop<2, FWD, T>(s, n, L, count, es, fs, tw, tid, nthr); break;
-    case 3: stage_loop<3, FWD, T>(s, n, L, count, es, fs, tw, tid, nthr); break;
-    case 4: stage_loop<4, FWD, T>(s, n, L, count, es, fs, tw, tid, nthr); break;
-    case 6: stage_loop<6, FWD, T>(s, n, L, count, es, fs, tw, tid, nthr); break;
-    case 8: stage_loop<8, FWD, T>(s, n, L, count, es, fs, tw, tid, nthr); break;
-    case 9: stage_loop<9, FWD, T>(s, n, L, count, es, fs, tw, tid, nthr); break;
-    case 12: stage_loop<12, FWD, T>(s, n, L, count, es, fs, tw, tid, nthr); break;
+// RMAX: no stage of the caller's plans has a larger radix (8 or 12; the wider
+// butterflies' registers then do not count against the kernel's).
+template <bool FWD, bool NTI, bool NTO, typename T, int RMAX = 12>
+FX_HD void run_stage(Span<T> in, Span<T> out, const AxisStage& st, const Lines& ln, const cpx<T>* tw, int tid,
+                     int nthr) {
+  switch (st.R) {
+    case 2: stage_loop<2, FWD, NTI, NTO, T>(in, out, st, ln, tw, tid, nthr); break;
+    case 3: stage_loop<3, FWD, NTI, NTO, T>(in, out, st, ln, tw, tid, nthr); break;
+    case 4: stage_loop<4, FWD, NTI, NTO, T>(in, out, st, ln, tw, tid, nthr); break;
+    case 6: stage_loop<6, FWD, NTI, NTO, T>(in, out, st, ln, tw, tid, nthr); break;
+    case 8: stage_loop<8, FWD, NTI, NTO, T>(in, out, st, ln, tw, tid, nthr); break;
+    case 9:
+      if constexpr (RMAX >= 9) stage_loop<9, FWD, NTI, NTO, T>(in, out, st, ln, tw, tid, nthr);
+      break;
+    case 12:
+      if constexpr (RMAX >= 12) stage_loop<12, FWD, NTI, NTO, T>(in, out, st, ln, tw, tid, nthr);
+      break;
     default: break;
   }
 }
-
-// Plan in kernel-argument form.
-struct AxisArg {
-  int n, nst;
-  int R[4];
-};
 
 // Barrier policies: the device one is the workgroup barrier; the host one is
 // empty, used when a single host "thread" (tid 0, nthr 1) runs every
@@ -277,88 +358,44 @@ struct HostSync {
   __host__ void operator()() const {}
 };
 
-// Forward or inverse transform along one axis of an LDS-resident block,
-// executed by threads tid < nthr of the workgroup with a barrier after every
-// stage.  Every thread of the workgroup must call it.
-template <bool FWD, typename T, class Sync>
-FX_HD void lds_fft(cpx<T>* s, const AxisArg& a, int count, int es, int fs, const cpx<T>* tw, int tid, int nthr,
-                   Sync sync) {
-  if (FWD) {
-    int L = a.n;
-    for (int st = 0; st < a.nst; ++st) {
-      stage_dispatch<true, T>(a.R[st], s, a.n, L, count, es, fs, tw, tid, nthr);
-      sync();
-      L /= a.R[st];
-    }
-  } else {
-    // stage st of the forward run had L_st = n / (R_0 ... R_{st-1})
-    for (int st = a.nst - 1; st >= 0; --st) {
-      int L = a.n;
-      for (int u = 0; u < st; ++u) L /= a.R[u];
-      stage_dispatch<false, T>(a.R[st], s, a.n, L, count, es, fs, tw, tid, nthr);
-      sync();
-    }
-  }
-}
-
 // ---- convolution along one axis: forward FFT, pointwise factor, inverse ----
 // The last forward stage has span 1, so each of its butterflies owns R
 // consecutive positions — exactly the points the first inverse stage
 // combines.  That stage, the pointwise factor and the first inverse stage
 // therefore run in registers as one pass.  kf(pos, f) is the real factor at
 // digit-reversed position pos of transform f.
-template <int R, typename T, class KF>
-FX_HD void mid_bfly(cpx<T>* s, int count, int es, int fs, int b, KF kf) {
-  const int f = b % count;
-  const int blk = b / count;
-  const int base = f * fs + blk * R * es;
-  cpx<T> x[R];
+template <int R, bool NT, typename T, class KF>
+FX_HD void mid_loop(Span<T> in, Span<T> out, const AxisStage& st, const Lines& ln, KF kf, int tid, int nthr) {
+  const int total = ln.count * st.nb;
+  for (int b = tid; b < total; b += nthr) {
+    const int blk = fdiv(b, ln.dcount);
+    const int f = b - blk * ln.count;
+    if (f >= ln.lim) continue;
+    cpx<T> x[R];
+    const cpx<T>* pi = in.p + (f * in.fs + blk * R * in.es);
 #pragma unroll
-  for (int m = 0; m < R; ++m) x[m] = s[base + m * es];
-  Dft<R, -1, T>::run(x);
+    for (int m = 0; m < R; ++m) x[m] = g_load2<NT>(pi + m * in.es);
+    Dft<R, -1, T>::run(x);
 #pragma unroll
-  for (int k = 0; k < R; ++k) x[k] = cscale(x[k], kf(blk * R + k, f));
-  Dft<R, 1, T>::run(x);
+    for (int k = 0; k < R; ++k) x[k] = cscale(x[k], kf(blk * R + k, f));
+    Dft<R, 1, T>::run(x);
+    cpx<T>* po = out.p + (f * out.fs + blk * R * out.es);
 #pragma unroll
-  for (int m = 0; m < R; ++m) s[base + m * es] = x[m];
+    for (int m = 0; m < R; ++m) g_store<NT>(po + m * out.es, x[m]);
+  }
 }
 
-template <int R, typename T, class KF>
-FX_HD void mid_loop(cpx<T>* s, int n, int count, int es, int fs, KF kf, int tid, int nthr) {
-  const int total = count * (n / R);
-  for (int b = tid; b < total; b += nthr) mid_bfly<R, T>(s, count, es, fs, b, kf);
-}
-
-template <typename T, class KF>
-FX_HD void mid_dispatch(int R, cpx<T>* s, int n, int count, int es, int fs, KF kf, int tid, int nthr) {
-  switch (R) {
-    case 2: mid_loop<2, T>(s, n, count, es, fs, kf, tid, nthr); break;
-    case 3: mid_loop<3, T>(s, n, count, es, fs, kf, tid, nthr); break;
-    case 4: mid_loop<4, T>(s, n, count, es, fs, kf, tid, nthr); break;
-    case 6: mid_loop<6, T>(s, n, count, es, fs, kf, tid, nthr); break;
-    case 8: mid_loop<8, T>(s, n, count, es, fs, kf, tid, nthr); break;
-    case 9: mid_loop<9, T>(s, n, count, es, fs, kf, tid, nthr); break;
-    case 12: mid_loop<12, T>(s, n, count, es, fs, kf, tid, nthr); break;
+template <bool NT, typename T, class KF>
+FX_HD void run_mid(Span<T> in, Span<T> out, const AxisStage& st, const Lines& ln, KF kf, int tid, int nthr) {
+  switch (st.R) {
+    case 2: mid_loop<2, NT, T>(in, out, st, ln, kf, tid, nthr); break;
+    case 3: mid_loop<3, NT, T>(in, out, st, ln, kf, tid, nthr); break;
+    case 4: mid_loop<4, NT, T>(in, out, st, ln, kf, tid, nthr); break;
+    case 6: mid_loop<6, NT, T>(in, out, st, ln, kf, tid, nthr); break;
+    case 8: mid_loop<8, NT, T>(in, out, st, ln, kf, tid, nthr); break;
+    case 9: mid_loop<9, NT, T>(in, out, st, ln, kf, tid, nthr); break;
+    case 12: mid_loop<12, NT, T>(in, out, st, ln, kf, tid, nthr); break;
     default: break;
-  }
-}
-
-template <typename T, class KF, class Sync>
-FX_HD void lds_conv(cpx<T>* s, const AxisArg& a, int count, int es, int fs, const cpx<T>* tw, KF kf, int tid,
-                    int nthr, Sync sync) {
-  int L = a.n;
-  for (int st = 0; st + 1 < a.nst; ++st) {
-    stage_dispatch<true, T>(a.R[st], s, a.n, L, count, es, fs, tw, tid, nthr);
-    sync();
-    L /= a.R[st];
-  }
-  mid_dispatch<T>(a.R[a.nst - 1], s, a.n, count, es, fs, kf, tid, nthr);
-  sync();
-  for (int st = a.nst - 2; st >= 0; --st) {
-    int Ls = a.n;
-    for (int u = 0; u < st; ++u) Ls /= a.R[u];
-    stage_dispatch<false, T>(a.R[st], s, a.n, Ls, count, es, fs, tw, tid, nthr);
-    sync();
   }
 }
 

@@ -69,38 +69,6 @@ FX_HD void ct_stage(cpx<T>* s, const cpx<T>* tw, int tid) {
   }
 }
 
-// Global accesses with a non-temporal hint: data read or written once (the
-// pair volume) need not displace data that is reused from the caches (the
-// orbital and target planes the workgroups of an XCD share).  At 96^3 the
-// hint took the three passes from 10.5 to 9.5 ms per launch of 1170 pairs.
-template <typename T>
-struct Vec2;
-template <>
-struct Vec2<float> {
-  typedef float type __attribute__((ext_vector_type(2)));
-};
-template <>
-struct Vec2<double> {
-  typedef double type __attribute__((ext_vector_type(2)));
-};
-template <bool NTS, typename T>
-FX_HD cpx<T> g_load(const cpx<T>* p) {
-  if (!NTS) return *p;
-  const typename Vec2<T>::type v = __builtin_nontemporal_load(reinterpret_cast<const typename Vec2<T>::type*>(p));
-  return cpx<T>{v.x, v.y};
-}
-template <bool NTS, typename T>
-FX_HD void g_store(cpx<T>* p, cpx<T> a) {
-  if (!NTS) {
-    *p = a;
-    return;
-  }
-  typename Vec2<T>::type v;
-  v.x = a.x;
-  v.y = a.y;
-  __builtin_nontemporal_store(v, reinterpret_cast<typename Vec2<T>::type*>(p));
-}
-
 // A stage split into its three parts, so that a kernel can issue a stage's
 // loads early (software pipelining): butterfly it of thread tid holds
 // elements x[it][0..R) at positions pos0 + m*SPAN of transform f.  In global
@@ -288,7 +256,8 @@ __device__ inline void ct_fft(cpx<T>* s, const cpx<T>* tw, int tid) {
 
 // Convolution along one axis: first forward stage, then the last forward
 // stage + pointwise factor + first inverse stage in registers, then the last
-// inverse stage.  kf(pos, f) as in lds_conv.
+// inverse stage.  kf(pos, f) is the real factor at
+// digit-reversed position pos of transform f.
 template <typename T, int N, int COUNT, int ES, int FS, int NTHR, class KF>
 __device__ inline void ct_conv(cpx<T>* s, const cpx<T>* tw, KF kf, int tid) {
   constexpr int R0 = Plan2<N>::R0, R1 = Plan2<N>::R1;

@@ -1,0 +1,54 @@
+// How the workgroups of a persistent plane kernel share its items, and which
+// XCD takes which.  Integer logic only, for host and device (FX_HD must be
+// defined before inclusion), so that it can be checked on the CPU.
+#pragma once
+#include <cstdint>
+
+namespace fx {
+
+// Work of a persistent plane kernel: `units` (pairs, or targets) x nz planes.
+// Workgroups are dispatched round-robin over the XCDs, so with a grid that is
+// a multiple of the XCD count workgroup b runs on XCD b % kXcds.  Each XCD
+// takes either a contiguous chunk of the units (preferred with zsplit 0) or a
+// contiguous range of the planes of every unit (zsplit 1), and walks its share
+// z-major: the workgroups of one XCD work on the same z at the same time and
+// find that plane's input data (orbital and target planes in pass A, orbital
+// planes in pass C) in their shared L2 instead of reading it again from HBM.
+// With the z split no two XCDs read the same input plane.
+// A split whose largest share exceeds the mean by more than 5% is not taken:
+// the other one is, or else all workgroups walk all items z-major.  (One target
+// of 427 terms at 72 x 72 x 24 ran on a single XCD, 21.7 ms; the halved 48^3
+// apply, 43 targets per launch, has shares of 5 and 6.)
+constexpr int kXcds = 8;
+
+struct ItemMap {
+  int u_lo, u_n, z_lo, first, step, total;
+  FX_HD void at(int li, int* unit, int* z) const {
+    const int zz = li / u_n;
+    *z = z_lo + zz;
+    *unit = u_lo + (li - zz * u_n);
+  }
+};
+
+// The items of workgroup b of G.
+FX_HD ItemMap item_map(int nz, int units, int zsplit, int G, int b) {
+  ItemMap m{0, units, 0, b, G, units * nz};
+  if (G < kXcds || G % kXcds != 0) return m;
+  const auto even = [](int n) { return (n + kXcds - 1) / kXcds * kXcds * 20 <= 21 * n; };
+  const bool by_z = even(nz) && (zsplit || !even(units));
+  if (!by_z && !even(units)) return m;
+  const int x = b % kXcds;
+  m.first = b / kXcds;
+  m.step = G / kXcds;
+  if (by_z) {
+    m.z_lo = nz * x / kXcds;
+    m.total = units * (nz * (x + 1) / kXcds - m.z_lo);
+  } else {
+    m.u_lo = (int)((int64_t)units * x / kXcds);
+    m.u_n = (int)((int64_t)units * (x + 1) / kXcds) - m.u_lo;
+    m.total = m.u_n * nz;
+  }
+  return m;
+}
+
+}  // namespace fx

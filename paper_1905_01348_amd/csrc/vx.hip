@@ -13,230 +13,6 @@
 
 namespace fx {
 
-// ---------------------------------------------------------------------------
-// kernels
-//
-// The plane passes are persistent: each workgroup walks items (pair, z) or
-// (target, z) with stride gridDim.x, and issues the global loads of the next
-// plane into registers (EPT elements per thread) before running the FFT of
-// the current one, so the loads are in flight while the LDS stages run.
-// ---------------------------------------------------------------------------
-constexpr int kPlaneThreads = 512;
-// most threads of a generic z-pass workgroup (its launch bound)
-constexpr int kPencilThreads = 256;
-
-template <typename T, int EPT>
-__global__ void __launch_bounds__(kPlaneThreads) k_pass_a(const cpx<T>* __restrict__ psi, int64_t ld_psi,
-                                                 const cpx<T>* __restrict__ phi, int64_t ld_phi,
-                                                 cpx<T>* __restrict__ work, int j0, int nj, int k0, int nitems,
-                                                 PassGeom g, const cpx<T>* __restrict__ twx_g,
-                                                 const cpx<T>* __restrict__ twy_g) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  cpx<T>* s = reinterpret_cast<cpx<T>*>(smem_raw);
-  cpx<T>* twx = s + plane_lds_elems(g);
-  cpx<T>* twy = twx + g.nx;
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  for (int i = tid; i < g.nx; i += nthr) twx[i] = twx_g[i];
-  for (int i = tid; i < g.ny; i += nthr) twy[i] = twy_g[i];
-  const int nxy = g.nx * g.ny;
-  const size_t nr = (size_t)nxy * g.nz;
-  cpx<T> va[EPT], vb[EPT];
-  auto fetch = [&](int it) __attribute__((always_inline)) {
-    if (it >= nitems) return;
-    const int z = it % g.nz, p = it / g.nz;
-    const cpx<T>* a = psi + (int64_t)(j0 + p % nj) * ld_psi + (size_t)z * nxy;
-    const cpx<T>* b = phi + (int64_t)(k0 + p / nj) * ld_phi + (size_t)z * nxy;
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-      const int e = tid + i * nthr;
-      if (e < nxy) {
-        va[i] = a[e];
-        vb[i] = b[e];
-      }
-    }
-  };
-  // FP32: the next plane loads while this one transforms; FP64 planes do
-  // not leave room in registers for that, so they load just before use
-  constexpr bool kPipe = sizeof(T) == 4;
-  int item = blockIdx.x;
-  if (kPipe) fetch(item);
-  for (; item < nitems; item += gridDim.x) {
-    if (!kPipe) fetch(item);
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-      const int e = tid + i * nthr;
-      if (e < nxy) {
-        const int y = e / g.nx, x = e - y * g.nx;
-        s[y * g.sx + x] = cconjmul(va[i], vb[i]);
-      }
-    }
-    __syncthreads();
-    if (kPipe) fetch(item + gridDim.x);
-    lds_fft<true, T>(s, g.ax, g.ny, 1, g.sx, twx, tid, nthr, DeviceSync{});
-    lds_fft<true, T>(s, g.ay, g.nx, g.sx, 1, twy, tid, nthr, DeviceSync{});
-    const int z = item % g.nz, p = item / g.nz;
-    cpx<T>* o = work + p * nr + (size_t)z * nxy;
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-      const int e = tid + i * nthr;
-      if (e < nxy) {
-        const int y = e / g.nx, x = e - y * g.nx;
-        o[e] = s[y * g.sx + x];
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// Pass B: one (pair, y, x-tile) per workgroup; many small workgroups per CU.
-template <typename T, int EPT>
-__global__ void __launch_bounds__(kPencilThreads) k_pass_b(cpx<T>* __restrict__ work, int xt, int ntx, PassGeom g,
-                                                const cpx<T>* __restrict__ twz_g, const T* __restrict__ kfold,
-                                                const int* __restrict__ foldx_g, const int* __restrict__ foldy_g,
-                                                const int* __restrict__ foldz_g) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int n = g.nz * xt;
-  cpx<T>* s = reinterpret_cast<cpx<T>*>(smem_raw);
-  cpx<T>* twz = s + n;
-  T* kl = reinterpret_cast<T*>(twz + g.nz);
-  int* fxl = reinterpret_cast<int*>(kl + g.hz * g.hx);
-  int* fzl = fxl + g.nx;
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  const int tx = blockIdx.x % ntx;
-  const int rest = blockIdx.x / ntx;
-  const int y = rest % g.ny;
-  const int p = rest / g.ny;
-  const int x0 = tx * xt;
-  cpx<T>* vol = work + (size_t)p * g.nx * g.ny * g.nz;
-  cpx<T> v[EPT];
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) {
-    const int e = tid + i * nthr;
-    const int z = e / xt, x = x0 + (e - z * xt);
-    v[i] = cpx<T>{0, 0};
-    if (e < n && x < g.nx) v[i] = vol[((size_t)z * g.ny + y) * g.nx + x];
-  }
-  // tables while the loads are in flight
-  const int fy = foldy_g[y];
-  for (int i = tid; i < g.nz; i += nthr) {
-    twz[i] = twz_g[i];
-    fzl[i] = foldz_g[i];
-  }
-  for (int i = tid; i < g.nx; i += nthr) fxl[i] = foldx_g[i];
-  for (int i = tid; i < g.hz * g.hx; i += nthr) {
-    const int fz = i / g.hx, fx = i - fz * g.hx;
-    kl[i] = kfold[((size_t)fz * g.hy + fy) * g.hx + fx];
-  }
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) {
-    const int e = tid + i * nthr;
-    if (e < n) s[e] = v[i];
-  }
-  __syncthreads();
-  const KSlice<T> kf{kl, fxl, fzl, x0, g.nx, g.hx};
-  lds_conv<T>(s, g.az, xt, xt, 1, twz, kf, tid, nthr, DeviceSync{});
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) {
-    const int e = tid + i * nthr;
-    const int z = e / xt, x = x0 + (e - z * xt);
-    if (e < n && x < g.nx) vol[((size_t)z * g.ny + y) * g.nx + x] = s[e];
-  }
-}
-
-// Pass C.  acc (ld_acc) holds the running sum over j of the targets in the
-// accumulation precision A; when `last` is set the final sum goes to `out`
-// in its own dtype instead (out may be the same memory as acc).  While the
-// FFT of orbital j runs, psi_j and the work plane of orbital j+1 are loading.
-template <typename T, typename A, int EPT, bool PIPE>
-__global__ void __launch_bounds__(kPlaneThreads) k_pass_c(const cpx<T>* __restrict__ psi, int64_t ld_psi,
-                                                 const cpx<T>* __restrict__ work, int j0, int nj, int k0, int nitems,
-                                                 cpx<A>* acc, int64_t ld_acc, int first, void* out, int64_t ld_out,
-                                                 int out_c64, int last, PassGeom g,
-                                                 const cpx<T>* __restrict__ twx_g, const cpx<T>* __restrict__ twy_g) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  cpx<T>* s = reinterpret_cast<cpx<T>*>(smem_raw);
-  cpx<T>* twx = s + plane_lds_elems(g);
-  cpx<T>* twy = twx + g.nx;
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  for (int i = tid; i < g.nx; i += nthr) twx[i] = twx_g[i];
-  for (int i = tid; i < g.ny; i += nthr) twy[i] = twy_g[i];
-  const int nxy = g.nx * g.ny;
-  const size_t nr = (size_t)nxy * g.nz;
-  for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
-    const int z = item % g.nz;
-    const int kk = item / g.nz;
-    const int k = k0 + kk;
-    cpx<A> a[EPT];
-    cpx<T> vt[EPT], vp[EPT];
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-      const int e = tid + i * nthr;
-      a[i] = cpx<A>{0, 0};
-      if (!first && e < nxy) a[i] = acc[k * ld_acc + (size_t)z * nxy + e];
-    }
-    constexpr bool kPipe = PIPE;  // prefetch the next work plane during the FFT
-    auto tload = [&](int jj) __attribute__((always_inline)) {
-      const cpx<T>* tp = work + ((size_t)kk * nj + jj) * nr + (size_t)z * nxy;
-#pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        const int e = tid + i * nthr;
-        if (e < nxy) vt[i] = tp[e];
-      }
-    };
-    if (kPipe) tload(0);
-    for (int jj = 0; jj < nj; ++jj) {
-      if (!kPipe) tload(jj);
-#pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        const int e = tid + i * nthr;
-        if (e < nxy) {
-          const int y = e / g.nx, x = e - y * g.nx;
-          s[y * g.sx + x] = vt[i];
-        }
-      }
-      __syncthreads();
-      const cpx<T>* pj = psi + (int64_t)(j0 + jj) * ld_psi + (size_t)z * nxy;
-#pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        const int e = tid + i * nthr;
-        if (e < nxy) vp[i] = pj[e];
-      }
-      if (kPipe && jj + 1 < nj) tload(jj + 1);
-      lds_fft<false, T>(s, g.ay, g.nx, g.sx, 1, twy, tid, nthr, DeviceSync{});
-      lds_fft<false, T>(s, g.ax, g.ny, 1, g.sx, twx, tid, nthr, DeviceSync{});
-#pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        const int e = tid + i * nthr;
-        if (e < nxy) {
-          const int y = e / g.nx, x = e - y * g.nx;
-          const cpx<T> v = s[y * g.sx + x];
-          // FP32 transforms: four FMAs per term; FP64: product then sum (the
-          // FMA chain costs the FP64 kernels registers they do not have)
-          if constexpr (sizeof(T) == 4)
-            a[i] = cfma(a[i], cpx<A>{(A)vp[i].x, (A)vp[i].y}, cpx<A>{(A)v.x, (A)v.y});
-          else
-            a[i] = cadd(a[i], cmul(cpx<A>{(A)vp[i].x, (A)vp[i].y}, cpx<A>{(A)v.x, (A)v.y}));
-        }
-      }
-      __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-      const int e = tid + i * nthr;
-      if (e >= nxy) continue;
-      const size_t off = (size_t)z * nxy + e;
-      if (last) {
-        if (out_c64)
-          reinterpret_cast<cpx<float>*>(out)[k * ld_out + off] = cpx<float>{(float)a[i].x, (float)a[i].y};
-        else
-          reinterpret_cast<cpx<double>*>(out)[k * ld_out + off] = cpx<double>{(double)a[i].x, (double)a[i].y};
-      } else {
-        acc[k * ld_acc + off] = a[i];
-      }
-    }
-  }
-}
-
 template <typename TI, typename TO>
 __global__ void k_convert(const cpx<TI>* __restrict__ in, int64_t ld_in, cpx<TO>* __restrict__ out, int64_t ld_out,
                           int64_t nr, int ncols) {
@@ -282,10 +58,14 @@ __global__ void k_half_sum(const double* __restrict__ partial, int n, double* __
 // host side
 // ---------------------------------------------------------------------------
 static AxisArg to_arg(const AxisPlan& p) {
-  AxisArg a;
+  AxisArg a{};
   a.n = p.n;
   a.nst = p.nst;
-  for (int i = 0; i < 4; ++i) a.R[i] = p.R[i];
+  for (int i = 0, L = p.n; i < p.nst; ++i) {
+    const int R = p.R[i];
+    a.st[i] = AxisStage{R, L, L / R, p.n / L, p.n / R, fast_div(L / R)};
+    L /= R;
+  }
   return a;
 }
 
@@ -307,24 +87,10 @@ PassGeom make_geom(const fx_cell* cell, const PlanSet* plans = nullptr) {
   g.hx = g.nx / 2 + 1;
   g.hy = g.ny / 2 + 1;
   g.hz = g.nz / 2 + 1;
+  g.dnx = fast_div(g.nx);
+  g.dny = fast_div(g.ny);
+  g.dhx = fast_div(g.hx);
   return g;
-}
-
-static int round64(int v) { return (v + 63) / 64 * 64; }
-
-template <typename K>
-static fx_status allow_lds(K kernel, size_t bytes) {
-  return allow_dynamic_lds(reinterpret_cast<const void*>(kernel), bytes);
-}
-
-// Workgroups of a persistent kernel: resident workgroups per CU x CUs.
-template <typename K>
-static fx_status persistent_grid(fx_ctx* ctx, K kernel, int nthr, size_t lds, int items, int* grid) {
-  int per_cu = 0;
-  FX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel), nthr, lds));
-  if (per_cu < 1) per_cu = 1;
-  *grid = std::max(1, std::min(items, per_cu * std::max(ctx->n_cu, 1)));
-  return FX_OK;
 }
 
 static size_t work_cap_bytes(fx_ctx* ctx) {
@@ -335,33 +101,6 @@ static size_t work_cap_bytes(fx_ctx* ctx) {
   if (cap > ctx->budget / 4) cap = ctx->budget / 4;
   return cap;
 }
-
-// Elements per thread (a compile-time register count) and threads for
-// `elems` elements and at most max_thr threads.
-static const int kEpts[] = {1, 2, 3, 4, 6, 9, 18};
-static bool pick_ept(int elems, int max_thr, int* ept, int* nthr) {
-  for (int e : kEpts) {
-    const int t = round64((elems + e - 1) / e);
-    if (t <= max_thr) {
-      *ept = e;
-      *nthr = t;
-      return true;
-    }
-  }
-  return false;
-}
-
-#define FX_EPT_SWITCH(EPT_VAR, ...) \
-  switch (EPT_VAR) {                 \
-    case 1: { constexpr int E = 1; __VA_ARGS__; } break;   \
-    case 2: { constexpr int E = 2; __VA_ARGS__; } break;   \
-    case 3: { constexpr int E = 3; __VA_ARGS__; } break;   \
-    case 4: { constexpr int E = 4; __VA_ARGS__; } break;   \
-    case 6: { constexpr int E = 6; __VA_ARGS__; } break;   \
-    case 9: { constexpr int E = 9; __VA_ARGS__; } break;   \
-    case 18: { constexpr int E = 18; __VA_ARGS__; } break; \
-    default: FX_FAIL(FX_ERR_UNSUPPORTED, "no kernel for %d elements per thread", EPT_VAR); \
-  }
 
 // z-pass form of the specialised kernels: the persistent kernel with whole x
 // rows is the automatic choice at 96^3, where it measured faster (3.12 vs
@@ -396,11 +135,36 @@ static int ct_c_variant(const VxArgs& a) {
 // the pass has few items (targets x planes); S times as many balance the
 // CUs.  The grouping depends on the orbital index only, so a column's result
 // is the same whatever the batch size and whichever targets share a launch.
-// S = 1 (automatic) keeps one running sum per target; the allocation-free
-// form always does.
-static int ct_jsplit(const VxArgs& a) {
+// Automatic: as many groups as give the eight targets of a request the
+// workgroups that are resident at once (256 CUs of 12 waves; a plane has about
+// ny nx / R butterflies in its last stage, R the first x radix), with at least
+// four terms each.  The count of targets must not enter, since served requests
+// are merged; the phi == psi form keeps one running sum (its partial sums then
+// need no memory beyond `out`), as does the allocation-free form.
+// 27 orbitals x 11 targets at 32 x 36 x 24: one sum leaves 264 items of 27
+// terms one after the other, 182 us, four groups 71 and 7 to add them; at 64^3
+// two groups gain nothing and their partial sums cost the other passes 130 of
+// 2440 us.
+static int ct_jsplit(const VxArgs& a, const PassGeom& g, bool square) {
   if (a.no_alloc || a.add) return 1;
-  return a.c_split == 2 || a.c_split == 4 || a.c_split == 8 ? a.c_split : 1;
+  if (a.c_split == 1 || a.c_split == 2 || a.c_split == 4 || a.c_split == 8) return a.c_split;
+  if (square) return 1;
+  const int waves = (g.ny * g.ax.st[0].nb + 63) / 64;
+  const int64_t most = std::min<int64_t>(a.n_psi / 4, 256 * std::max(1, 12 / waves) / (8 * g.nz));
+  int s = 1;
+  while (s < 8 && 2 * s <= most) s *= 2;
+  return s;
+}
+
+// Whether the phi == psi form is halved off the workload edges (on them it
+// always is).  FP32 transforms with FP64 sums keep every ordered pair's own
+// solve: the solve of (k, j) is the conjugate of that of (j, k) only to FP32
+// rounding, which the FP64 sums would show.  And the halved passes run one
+// after the other over the same planes, so there must be planes enough for the
+// resident workgroups (see ct_jsplit) twice over.
+static bool gen_halved(const VxArgs& a, const PassGeom& g) {
+  const int waves = (g.ny * g.ax.st[0].nb + 63) / 64;
+  return a.prec != FX_PREC_FP32_ACC64 && (int64_t)a.n_psi * g.nz >= 2 * 256 * std::max(1, 12 / waves);
 }
 
 // out[t] = sum over the groups g = 0, 1, ... of acc[g][t] (targets t0 ..
@@ -441,6 +205,26 @@ static int ct_zsplit() {
   return e ? atoi(e) : 5;
 }
 
+// The three passes of a batch, by the kernels chosen for the grid.
+template <typename T, typename A>
+struct PairPasses {
+  fx_ctx* ctx;
+  hipStream_t st;
+  bool ct;
+  PassGeom g;
+  const GridTables* tb;
+  int xtile, nthr_b;
+  fx_status a(const CtBatch<T>& b) const {
+    return ct ? ct_pass_a<T>(ctx, st, g.nx, b) : gen_pass_a<T>(ctx, st, g, tb, b);
+  }
+  fx_status b(const CtBatch<T>& b) const {
+    return ct ? ct_pass_b<T>(ctx, st, g.nx, b) : gen_pass_b<T>(ctx, st, g, tb, b, xtile, nthr_b);
+  }
+  fx_status c(const CtBatch<T>& b, const CtAcc<A>& c, int role) const {
+    return ct ? ct_pass_c<T, A>(ctx, st, g.nx, b, c, role) : gen_pass_c<T, A>(ctx, st, g, tb, b, c, role);
+  }
+};
+
 // Halved apply for phi == psi (all N targets): each unordered pair {j, k} is
 // solved once, as (min, max), since v_kj = conj(v_jk) for a real, even kernel.
 // Orbitals are cut into blocks of B; block pairs (J <= K) run in ascending
@@ -450,10 +234,10 @@ static int ct_zsplit() {
 // from the ordered pair (min(j,k), max(j,k)), so the result does not depend
 // on B.  Diagonal block pairs hold only the B(B+1)/2 pairs j <= k.
 template <typename T, typename A>
-static fx_status run_halved(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const GridTables* tb, const cpx<T>* psi,
-                            int64_t ld_psi, int64_t pairs_cap, hipStream_t st, VxStats* stats) {
-  const int n = a.cell->n[0];
-  const int64_t nr = (int64_t)n * n * n;
+static fx_status run_halved(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const PairPasses<T, A>& pass,
+                            const GridTables* tb, const cpx<T>* psi, int64_t ld_psi, int64_t pairs_cap, hipStream_t st,
+                            VxStats* stats) {
+  const int64_t nr = (int64_t)a.cell->n[0] * a.cell->n[1] * a.cell->n[2];
   const size_t pair_bytes = (size_t)nr * sizeof(cpx<T>);
   const int N = a.n_psi;
   int B = (int)std::min<int64_t>(N, std::max<int64_t>(1, (int64_t)std::sqrt((double)pairs_cap)));
@@ -464,7 +248,7 @@ static fx_status run_halved(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const G
   FX_TRY(ws_get(ctx, ws, "vx_work", (size_t)B * B * pair_bytes, &work));
   const bool out_c64 = a.out_dtype == FX_C64;
   const bool out_is_A = (sizeof(A) == 8) == !out_c64;
-  const int jsplit = ct_jsplit(a);
+  const int jsplit = ct_jsplit(a, pass.g, true);
   // partial sums live between the two roles of every block pair
   cpx<A>* acc = nullptr;
   int64_t ld_acc = 0, gstride = 0;
@@ -494,28 +278,28 @@ static fx_status run_halved(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const G
       const double vol = (double)npairs * nr * sz;
       int slot;
       FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_FWD, 2.0 * vol, &slot));
-      FX_TRY(ct_pass_a<T>(ctx, st, n, cb));
+      FX_TRY(pass.a(cb));
       FX_TRY(prof_end(ctx, st, slot));
       FX_TRY(prof_begin(ctx, st, FX_K_VX_PENCIL_Z, 2.0 * vol, &slot));
-      FX_TRY(ct_pass_b<T>(ctx, st, n, cb));
+      FX_TRY(pass.b(cb));
       FX_TRY(prof_end(ctx, st, slot));
       // role 0: targets of block K; the first contribution to them is J = 0
       {
         const int first = J == 0;
-        CtAcc<A> ca{acc, ld_acc, first, a.out, a.ld_out, out_c64 ? 1 : 0, 0, -1, gstride};
+        CtAcc<A> ca{acc, ld_acc, first, a.out, a.ld_out, out_c64 ? 1 : 0, 0, gstride};
         const double accb = (double)kb * nr * ((first ? 0.0 : asz) + asz) * jsplit;
         FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_INV, 2.0 * vol + accb, &slot));
-        FX_TRY((ct_pass_c<T, A>(ctx, st, n, cb, ca, 0)));
+        FX_TRY(pass.c(cb, ca, 0));
         FX_TRY(prof_end(ctx, st, slot));
       }
       // role 1: targets of block J; their last contribution is K = nblk - 1
       {
         const int last = K == nblk - 1 && jsplit == 1;
-        CtAcc<A> ca{acc, ld_acc, 0, a.out, a.ld_out, out_c64 ? 1 : 0, last, -1, gstride};
+        CtAcc<A> ca{acc, ld_acc, 0, a.out, a.ld_out, out_c64 ? 1 : 0, last, gstride};
         const double planes = tri ? (double)(npairs - jb) : (double)npairs;
         const double accb = (double)jb * nr * (asz + (last ? osz : asz)) * jsplit;
         FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_INV, 2.0 * planes * nr * sz + accb, &slot));
-        FX_TRY((ct_pass_c<T, A>(ctx, st, n, cb, ca, 1)));
+        FX_TRY(pass.c(cb, ca, 1));
         FX_TRY(prof_end(ctx, st, slot));
       }
       launches += 4;
@@ -544,7 +328,6 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
                              VxStats* stats) {
   const PassGeom g = make_geom(a.cell, a.plans_set ? &a.plans : nullptr);
   const int64_t nr = (int64_t)g.nx * g.ny * g.nz;
-  const int nxy = g.nx * g.ny;
   const size_t pair_bytes = (size_t)nr * sizeof(cpx<T>);
   size_t cap = a.work_cap ? std::min(a.work_cap, ctx->budget / 4) : work_cap_bytes(ctx);
   const int64_t pairs_cap = (int64_t)std::max<size_t>(1, cap / pair_bytes);
@@ -561,8 +344,10 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
             g.nz);
   if (a.segs.n > 0 && (!use_ct || psi == phi))
     FX_FAIL(FX_ERR_UNSUPPORTED, "multi-trajectory launches need the specialised kernels and phi != psi");
-  if (use_ct && a.halve != 0 && psi == phi && ld_psi == ld_phi && a.n_psi == a.n_phi)
-    return run_halved<T, A>(ctx, ws, a, tb, psi, ld_psi, pairs_cap, st, stats);
+  const PairPasses<T, A> pass{ctx, st, use_ct, g, tb, a.xtile, a.nthr_b};
+  const bool square = psi == phi && ld_psi == ld_phi && a.n_psi == a.n_phi;
+  if (square && a.halve != 0 && (use_ct || a.halve > 0 || gen_halved(a, g)))
+    return run_halved<T, A>(ctx, ws, a, pass, tb, psi, ld_psi, pairs_cap, st, stats);
   // Batch shape: up to 16 orbitals per batch first (the plane-inverse pass
   // reads and writes its partial sums once per batch), then as many targets
   // as fit, balanced over the target blocks, then any leftover capacity
@@ -578,16 +363,27 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
   const bool out_c64 = a.out_dtype == FX_C64;
   const bool out_is_A = (sizeof(A) == 8) == !out_c64;
   const bool multi_j = nj < a.n_psi;
-  const int jsplit = use_ct ? ct_jsplit(a) : 1;
   cpx<A>* acc = nullptr;
   int64_t ld_acc = 0, gstride = 0;
+  int jsplit = ct_jsplit(a, g, false);
   if (jsplit > 1) {
-    // the groups' partial sums, added into out after the last batch
+    // the groups' partial sums of a block of targets, added into out after its
+    // last batch; a budget that cannot hold them gets one sum (where the groups
+    // were not asked for)
     void* p = nullptr;
-    FX_TRY(ws_get(ctx, ws, "vx_acc", (size_t)jsplit * a.n_phi * nr * sizeof(cpx<A>), &p));
+    const fx_status s = ws_get(ctx, ws, "vx_acc", (size_t)jsplit * nk * nr * sizeof(cpx<A>), &p);
+    if (s == FX_ERR_OOM && !a.c_split) {
+      clear_error();
+      jsplit = 1;
+    } else if (s != FX_OK) {
+      return s;
+    }
     acc = reinterpret_cast<cpx<A>*>(p);
     ld_acc = nr;
-    gstride = (int64_t)a.n_phi * nr;
+    gstride = (int64_t)nk * nr;
+  }
+  if (jsplit > 1) {
+    // nothing to carry in out
   } else if (a.add) {
     // the one batch of each target starts from the caller's columns
     if (multi_j || sizeof(A) != 8) FX_FAIL(FX_ERR_INVALID, "a start value needs one orbital and FP64 sums");
@@ -605,23 +401,7 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
     }
   }
   const cpx<T>* twx = reinterpret_cast<const cpx<T>*>(tb->tw[0]);
-  const cpx<T>* twy = reinterpret_cast<const cpx<T>*>(tb->tw[1]);
-  const cpx<T>* twz = reinterpret_cast<const cpx<T>*>(tb->tw[2]);
   const T* kf = reinterpret_cast<const T*>(tb->kfold);
-
-  // launch shapes
-  int ept_p = 0, nthr_p = 0;
-  if (!pick_ept(nxy, kPlaneThreads, &ept_p, &nthr_p)) FX_FAIL(FX_ERR_UNSUPPORTED, "plane of %d points is too large", nxy);
-  const bool pipe_c = a.pipe >= 0 ? a.pipe != 0 : ept_p < 18;
-  int xt = g.nx < 32 ? g.nx : 32;
-  if (a.xtile > 0) xt = std::min(g.nx, a.xtile);
-  const int ntx = (g.nx + xt - 1) / xt;
-  int ept_b = 0, nthr_b = 0;
-  if (!pick_ept(g.nz * xt, a.nthr_b > 0 ? std::min(a.nthr_b, kPencilThreads) : kPencilThreads, &ept_b, &nthr_b))
-    FX_FAIL(FX_ERR_UNSUPPORTED, "pencil tile of %d points is too large", g.nz * xt);
-  const size_t lds_plane = ((size_t)plane_lds_elems(g) + g.nx + g.ny) * sizeof(cpx<T>);
-  const size_t lds_b = ((size_t)g.nz * xt + g.nz) * sizeof(cpx<T>) + (size_t)g.hz * g.hx * sizeof(T) +
-                       (size_t)(g.nx + g.nz) * sizeof(int);
 
   int64_t launches = 0;
   for (int k0 = 0; k0 < a.n_phi; k0 += nk) {
@@ -639,66 +419,27 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
                           ((first ? 0.0 : (double)sizeof(cpx<A>)) +
                            (last ? (out_c64 ? 8.0 : 16.0) : (double)sizeof(cpx<A>)));
       int slot;
-      if (use_ct) {
-        CtBatch<T> cb{psi, ld_psi, phi, ld_phi, reinterpret_cast<cpx<T>*>(work), j0, jb, k0, kb, npairs, twx, kf,
-                      tb->fold[0], 0, a.a_pipe > 0 ? 1 : 0, ct_b_variant(a), ct_c_variant(a), (a.a_var >= 1 && a.a_var <= 3) ? a.a_var : 0, a.nt_hint != 0 ? 1 : 0, ct_zsplit(), a.segs, jsplit};
-        CtAcc<A> ca{acc, ld_acc, first, a.out, a.ld_out, out_c64 ? 1 : 0, jsplit > 1 ? 0 : last, a.pipe, gstride};
-        FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_FWD, 2.0 * vol, &slot));
-        FX_TRY(ct_pass_a<T>(ctx, st, g.nx, cb));
-        FX_TRY(prof_end(ctx, st, slot));
-        FX_TRY(prof_begin(ctx, st, FX_K_VX_PENCIL_Z, 2.0 * vol, &slot));
-        FX_TRY(ct_pass_b<T>(ctx, st, g.nx, cb));
-        FX_TRY(prof_end(ctx, st, slot));
-        FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_INV, 2.0 * vol + accb, &slot));
-        FX_TRY((ct_pass_c<T, A>(ctx, st, g.nx, cb, ca, 0)));
-        FX_TRY(prof_end(ctx, st, slot));
-        launches += 3;
-        if (jsplit > 1 && last) {
-          const double osz = out_c64 ? 8.0 : 16.0;
-          FX_TRY(prof_begin(ctx, st, FX_K_REDUCE, (double)kb * nr * (jsplit * sizeof(cpx<A>) + osz), &slot));
-          FX_TRY(combine_groups<A>(ctx, st, acc, gstride, ld_acc, jsplit, k0, kb, nr, a.out, a.ld_out,
-                                   out_c64 ? 1 : 0));
-          FX_TRY(prof_end(ctx, st, slot));
-          ++launches;
-        }
-        continue;
-      }
+      CtBatch<T> cb{psi, ld_psi, phi, ld_phi, reinterpret_cast<cpx<T>*>(work), j0, jb, k0, kb, npairs, twx, kf,
+                    tb->fold[0], 0, a.a_pipe > 0 ? 1 : 0, ct_b_variant(a), ct_c_variant(a), (a.a_var >= 1 && a.a_var <= 3) ? a.a_var : 0, a.nt_hint != 0 ? 1 : 0, ct_zsplit(), a.segs, jsplit};
+      CtAcc<A> ca{jsplit > 1 ? acc - (int64_t)k0 * ld_acc : acc, ld_acc, first, a.out, a.ld_out, out_c64 ? 1 : 0,
+                  jsplit > 1 ? 0 : last, gstride};
       FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_FWD, 2.0 * vol, &slot));
-      FX_EPT_SWITCH(ept_p, {
-        auto kern = k_pass_a<T, E>;
-        FX_TRY(allow_lds(kern, lds_plane));
-        int grid = 0;
-        FX_TRY(persistent_grid(ctx, kern, nthr_p, lds_plane, npairs * g.nz, &grid));
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(nthr_p), lds_plane, st, psi, ld_psi, phi, ld_phi,
-                           reinterpret_cast<cpx<T>*>(work), j0, jb, k0, npairs * g.nz, g, twx, twy);
-      });
-      FX_LAUNCH_CHECK();
+      FX_TRY(pass.a(cb));
       FX_TRY(prof_end(ctx, st, slot));
       FX_TRY(prof_begin(ctx, st, FX_K_VX_PENCIL_Z, 2.0 * vol, &slot));
-      FX_EPT_SWITCH(ept_b, {
-        auto kern = k_pass_b<T, E>;
-        FX_TRY(allow_lds(kern, lds_b));
-        hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)npairs * g.ny * ntx)), dim3(nthr_b), lds_b, st,
-                           reinterpret_cast<cpx<T>*>(work), xt, ntx, g, twz, kf, tb->fold[0], tb->fold[1],
-                           tb->fold[2]);
-      });
-      FX_LAUNCH_CHECK();
+      FX_TRY(pass.b(cb));
       FX_TRY(prof_end(ctx, st, slot));
       FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_INV, 2.0 * vol + accb, &slot));
-      FX_EPT_SWITCH(ept_p, {
-        // prefetching the next work plane needs registers the FP64 form and
-        // the largest planes do not have
-        auto kern = pipe_c ? k_pass_c<T, A, E, sizeof(T) == 4> : k_pass_c<T, A, E, false>;
-        FX_TRY(allow_lds(kern, lds_plane));
-        int grid = 0;
-        FX_TRY(persistent_grid(ctx, kern, nthr_p, lds_plane, kb * g.nz, &grid));
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(nthr_p), lds_plane, st, psi, ld_psi,
-                           reinterpret_cast<const cpx<T>*>(work), j0, jb, k0, kb * g.nz, acc, ld_acc, first, a.out,
-                           a.ld_out, out_c64 ? 1 : 0, last, g, twx, twy);
-      });
-      FX_LAUNCH_CHECK();
+      FX_TRY(pass.c(cb, ca, 0));
       FX_TRY(prof_end(ctx, st, slot));
       launches += 3;
+      if (jsplit > 1 && last) {
+        const double osz = out_c64 ? 8.0 : 16.0;
+        FX_TRY(prof_begin(ctx, st, FX_K_REDUCE, (double)kb * nr * (jsplit * sizeof(cpx<A>) + osz), &slot));
+        FX_TRY(combine_groups<A>(ctx, st, ca.acc, gstride, ld_acc, jsplit, k0, kb, nr, a.out, a.ld_out, out_c64 ? 1 : 0));
+        FX_TRY(prof_end(ctx, st, slot));
+        ++launches;
+      }
     }
   }
   if (stats) {
@@ -782,7 +523,6 @@ void resolve_vx_config(fx_ctx* ctx, VxArgs* a) {
   // environment overrides, for experiments and comparisons
   if (const char* e = getenv("FX_VX_NJ")) a->force_nj = atoi(e);
   if (const char* e = getenv("FX_VX_XT")) a->xtile = atoi(e);
-  if (const char* e = getenv("FX_VX_PIPE")) a->pipe = atoi(e);
   if (const char* e = getenv("FX_VX_NTHR_B")) a->nthr_b = atoi(e);
   if (const char* e = getenv("FX_VX_HALVE")) a->halve = atoi(e);
   if (const char* e = getenv("FX_VX_A_PIPE")) a->a_pipe = atoi(e);
@@ -943,13 +683,16 @@ static void host_pair(const fx_cell* cell, const HostTables& h, const double* ps
     const int fy = h.fold[1][y];
     for (int fz = 0; fz < g.hz; ++fz)
       for (int fx = 0; fx < g.hx; ++fx) kl[fz * g.hx + fx] = (T)h.kfold[((size_t)fz * g.hy + fy) * g.hx + fx];
+    const Lines tile{xt, xt, fast_div(xt)};
     for (int x0 = 0; x0 < g.nx; x0 += xt) {
-      const KSlice<T> kf{kl.data(), h.fold[0].data(), h.fold[2].data(), x0, g.nx, g.hx};
-      pass_b_body<T>(vol.data(), y, x0, xt, s.data(), tw[2].data(), kf, g, 0, 1, HostSync{});
+      const KSlice<T> kf{kl.data(), h.fold[0].data(), h.fold[2].data(), x0, g.hx};
+      pass_b_body<T>(vol.data(), y, x0, tile, s.data(), tw[2].data(), tw[2].data(), kf, g, 0, 1, HostSync{});
     }
   }
   for (int z = 0; z < g.nz; ++z) {
-    pass_c_fft<T>(vol.data() + z * nxy, s.data(), tw[0].data(), tw[1].data(), g, 0, 1, HostSync{});
+    pass_c_fft<T>(vol.data() + z * nxy, s.data(), tw[0].data(), tw[1].data(), g, 0, 1, HostSync{}, [] {});
+    const Span<T> rows = lds_rows(s.data(), g);
+    run_stage<false, false, false, T>(rows, rows, g.ax.st[0], plane_rows(g), tw[0].data(), 0, 1);
     for (size_t e = 0; e < nxy; ++e) {
       const int y = (int)(e / g.nx), x = (int)(e - (size_t)y * g.nx);
       v[2 * (z * nxy + e)] = (double)s[(size_t)y * g.sx + x].x;

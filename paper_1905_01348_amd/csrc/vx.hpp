@@ -53,7 +53,6 @@ struct VxArgs {
   int force_nj = 0;     // orbitals per batch
   int nthr_b = 0;  // generic z pass: threads per workgroup
   int xtile = 0;   // generic z pass: x columns per workgroup
-  int pipe = -1;   // generic plane-inverse pass prefetches the next plane: 1 yes, 0 no, -1 automatic
   int halve = -1;  // phi == psi: solve each unordered pair once (1 yes, 0 no, -1 automatic)
   int kernels = 0;  // 1 specialised (cubic workload edges only), 2 generic, 0 automatic
   int a_pipe = -1;  // specialised plane-forward pass: 1 register prefetch, 0 two workgroups per CU
@@ -95,8 +94,9 @@ struct VxStats {
   int64_t solves = 0;  // pair Poisson solves run (N*N_t, or N(N+1)/2 when halved)
 };
 
-// One batch of the pair passes for the compile-time-specialised kernels
-// (cubic grids of edge 24, 48, 72 or 96; vx_ct.hip).
+// One batch of the pair passes: for the compile-time-specialised kernels
+// (cubic grids of edge 24, 48, 72 or 96; vx_ct.hip) and for those of any grid
+// (vx_gen.hip, which take tables and geometry beside it).
 template <typename T>
 struct CtBatch {
   const cpx<T>* psi;
@@ -131,7 +131,7 @@ struct CtAcc {
   int first;
   void* out;
   int64_t ld_out;
-  int out_c64, last, pipe;
+  int out_c64, last;
   int64_t gstride = 0;
 };
 bool ct_supported(const fx_cell* cell);
@@ -142,6 +142,17 @@ fx_status ct_pass_b(fx_ctx* ctx, hipStream_t st, int n, const CtBatch<T>& b);
 // role 0: targets are the batch's k; role 1: targets are its j (halved apply)
 template <typename T, typename A>
 fx_status ct_pass_c(fx_ctx* ctx, hipStream_t st, int n, const CtBatch<T>& b, const CtAcc<A>& c, int role);
+
+// The passes on any grid.  xtile / threads of the z pass: 0 automatic.
+struct PassGeom;
+template <typename T>
+fx_status gen_pass_a(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb, const CtBatch<T>& b);
+template <typename T>
+fx_status gen_pass_b(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb, const CtBatch<T>& b,
+                     int xtile, int most_threads);
+template <typename T, typename A>
+fx_status gen_pass_c(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb, const CtBatch<T>& b,
+                     const CtAcc<A>& c, int role);
 
 fx_status check_vx_args(const VxArgs& a);
 // Copy ncols columns of nr complex values between dtypes (strided).

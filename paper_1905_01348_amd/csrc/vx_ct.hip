@@ -5,6 +5,7 @@
 #include <cstdlib>
 
 #include "fft_ct.hpp"
+#include "item_map.hpp"
 #include "pair_order.hpp"
 #include "vx.hpp"
 #include "vx_passes.hpp"
@@ -15,52 +16,6 @@ template <int A, int B>
 struct CeilDiv {
   static constexpr int value = (A + B - 1) / B;
 };
-
-// Work of a persistent plane kernel: `units` (pairs, or targets) x N planes.
-// Workgroups are dispatched round-robin over the XCDs, so with a grid that is
-// a multiple of the XCD count workgroup b runs on XCD b % kXcds.  Each XCD
-// takes either a contiguous chunk of the units (zsplit 0) or a contiguous
-// range of N / kXcds planes of every unit (zsplit 1), and walks its share
-// z-major: the workgroups of one XCD work on the same z at the same time and
-// find that plane's input data (orbital and target planes in pass A, orbital
-// planes in pass C) in their shared L2 instead of reading it again from HBM.
-// With the z split no two XCDs read the same input plane.
-constexpr int kXcds = 8;
-
-struct ItemMap {
-  int u_lo, u_n, z_lo, first, step, total;
-  FX_HD void at(int li, int* unit, int* z) const {
-    const int zz = li / u_n;
-    *z = z_lo + zz;
-    *unit = u_lo + (li - zz * u_n);
-  }
-};
-
-template <int N>
-__device__ inline ItemMap item_map(int units, int zsplit) {
-  ItemMap m;
-  const int G = gridDim.x, b = blockIdx.x;
-  m.u_lo = 0;
-  m.u_n = units;
-  m.z_lo = 0;
-  m.first = b;
-  m.step = G;
-  m.total = units * N;
-  if (G >= kXcds && G % kXcds == 0) {
-    const int x = b % kXcds;
-    m.first = b / kXcds;
-    m.step = G / kXcds;
-    if (zsplit && N % kXcds == 0) {
-      m.z_lo = x * (N / kXcds);
-      m.total = units * (N / kXcds);
-    } else {
-      m.u_lo = (int)((int64_t)units * x / kXcds);
-      m.u_n = (int)((int64_t)units * (x + 1) / kXcds) - m.u_lo;
-      m.total = m.u_n * N;
-    }
-  }
-  return m;
-}
 
 // ---- pass A: pair product, forward FFT x and y (persistent, pipelined) ------
 // PIPE: the next plane's loads are issued into registers before the current
@@ -91,7 +46,7 @@ __global__ void __launch_bounds__(NT, (PassAWaves<T, PIPE, NT>::value)) k_pass_a
   const int tid = threadIdx.x;
   for (int i = tid; i < N; i += NT) tw[i] = twg[i];
   cpx<T> va[EPT], vb[EPT];
-  const ItemMap im = item_map<N>(nitems / N, zsplit & 1);
+  const ItemMap im = item_map(N, nitems / N, zsplit & 1, gridDim.x, blockIdx.x);
   const bool kBlocked = (zsplit >> 2) & 1;
   // VEC with whole pairs of values per thread: each thread takes two
   // consecutive plane values per load (16-byte loads, half the load
@@ -409,7 +364,7 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
   for (int i = tid; i < N; i += NT) tw[i] = twg[i];
   __syncthreads();
   // units: (target tt, sum group g) as tt * jsplit + g
-  const ItemMap im = item_map<N>(nitems / N, zsplit);
+  const ItemMap im = item_map(N, nitems / N, zsplit, gridDim.x, blockIdx.x);
   // terms l = lo, lo + jsplit, ... < hi of target tt in group g: the terms
   // whose orbital m0 + l is g modulo jsplit, in ascending order
   auto range = [&](int tt_, int g_, int* lo_, int* hi_) __attribute__((always_inline)) {

@@ -1,0 +1,357 @@
+// V_X pair passes for any supported grid: the bodies of vx_passes.hpp with
+// run-time plans, persistent like the compile-time-specialised kernels of the
+// cubic workload edges (vx_ct.hip) and with the same batch interface (packed
+// diagonal batches, conjugated second role, sum groups, several trajectories).
+//
+// What bounds them is instruction issue and the latency across the stage
+// barriers, not HBM, so: every index is a high multiply by a constant of the
+// grid (FastDiv) instead of a division, the stage next to a global read or
+// write moves the data itself (no LDS round trip, one barrier fewer), the last
+// inverse x stage accumulates from its registers, and thread counts are taken
+// so that the butterflies of the stages fill them.
+#include <algorithm>
+
+#include "fft.hpp"
+#include "item_map.hpp"
+#include "pair_order.hpp"
+#include "vx.hpp"
+#include "vx_passes.hpp"
+
+namespace fx {
+
+constexpr int kGenAThreads = 512;
+// most threads of a generic z-pass workgroup (its launch bound)
+constexpr int kPencilThreads = 512;
+
+// ---- pass A ------------------------------------------------------------------
+template <typename T>
+__global__ void __launch_bounds__(kGenAThreads, 4) k_gen_a(const cpx<T>* __restrict__ psi, int64_t ld_psi,
+                                                          const cpx<T>* __restrict__ phi, int64_t ld_phi,
+                                                          cpx<T>* __restrict__ work, int j0, int nj, int k0, int tri,
+                                                          int npairs, PassGeom g, const cpx<T>* __restrict__ twx_g,
+                                                          const cpx<T>* __restrict__ twy_g, int zsplit, TrajSegs segs) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cpx<T>* s = reinterpret_cast<cpx<T>*>(smem_raw);
+  cpx<T>* twx = s + plane_lds_elems(g);
+  cpx<T>* twy = twx + g.nx;
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  for (int i = tid; i < g.nx; i += nthr) twx[i] = twx_g[i];
+  for (int i = tid; i < g.ny; i += nthr) twy[i] = twy_g[i];
+  const int nxy = g.nx * g.ny;
+  const size_t nr = (size_t)nxy * g.nz;
+  const ItemMap im = item_map(g.nz, npairs, zsplit & 1, gridDim.x, blockIdx.x);
+  for (int li = im.first; li < im.total; li += im.step) {
+    int p, z;
+    im.at(li, &p, &z);
+    p = unit_plane(p, npairs, nj, tri, (zsplit >> 2) & 1);
+    int jj, kk;
+    pair_of(p, nj, tri, &jj, &kk);
+    const cpx<T>* a = seg_psi<T>(segs, psi, k0 + kk) + (int64_t)(j0 + jj) * ld_psi + (size_t)z * nxy;
+    const cpx<T>* b = phi + (int64_t)(k0 + kk) * ld_phi + (size_t)z * nxy;
+    pass_a_body<T>(a, b, work + p * nr + (size_t)z * nxy, s, twx, twy, g, tid, nthr, DeviceSync{});
+    __syncthreads();
+  }
+}
+
+// ---- pass B: one (pair, y, x-tile) per workgroup -------------------------------
+template <typename T>
+__global__ void __launch_bounds__(kPencilThreads) k_gen_b(cpx<T>* __restrict__ work, Lines tile, int ntx, PassGeom g,
+                                                          const cpx<T>* __restrict__ twz_g,
+                                                          const T* __restrict__ kfold, const int* __restrict__ foldx_g,
+                                                          const int* __restrict__ foldy_g,
+                                                          const int* __restrict__ foldz_g) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cpx<T>* s = reinterpret_cast<cpx<T>*>(smem_raw);
+  cpx<T>* twz = s + g.nz * tile.count;
+  T* kl = reinterpret_cast<T*>(twz + g.nz);
+  int* fxl = reinterpret_cast<int*>(kl + g.hz * g.hx);
+  int* fzl = fxl + g.nx;
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  const int tx = blockIdx.x % ntx;
+  const int rest = blockIdx.x / ntx;
+  const int y = rest % g.ny;
+  const int p = rest / g.ny;
+  const int fy = foldy_g[y];
+  for (int i = tid; i < g.nz; i += nthr) {
+    twz[i] = twz_g[i];
+    fzl[i] = foldz_g[i];
+  }
+  for (int i = tid; i < g.nx; i += nthr) fxl[i] = foldx_g[i];
+  for (int i = tid; i < g.hz * g.hx; i += nthr) {
+    const int fz = fdiv(i, g.dhx);
+    kl[i] = kfold[((size_t)fz * g.hy + fy) * g.hx + (i - fz * g.hx)];
+  }
+  const int x0 = tx * tile.count;
+  const KSlice<T> kf{kl, fxl, fzl, x0, g.hx};
+  pass_b_body<T>(work + (size_t)p * g.nx * g.ny * g.nz, y, x0, tile, s, twz_g, twz, kf, g, tid, nthr, DeviceSync{});
+}
+
+// ---- pass C ------------------------------------------------------------------
+// One item = (target tt of the batch, sum group gr, plane z).  Role 0: targets
+// t0 + kk, terms psi_{m0+jj} v_{jk}; role 1 (conj): targets t0 + jj, terms
+// psi_{m0+kk} conj(v_{jk}); on a diagonal batch role 0 takes jj <= kk, role 1
+// kk > jj (see k_pass_c_ct).  R: radix of the last inverse x stage, IT its
+// butterflies per thread; their R IT sums per thread stay in registers over
+// the batch's terms.  Two LDS planes, alternating by term, where dbl is set
+// (they then take at most 40 KB): a term's first stage need not wait for the
+// previous term's last reads.
+constexpr int kGenCThreads = 768;  // launch bound: 170 registers a thread
+
+template <typename T, typename A, int R, int IT, int RMAX>
+__global__ void __launch_bounds__(kGenCThreads, (sizeof(T) == 4 && R * IT <= 8 ? 4 : 3))
+    k_gen_c(const cpx<T>* __restrict__ mult, int64_t ld_mult, const cpx<T>* __restrict__ work, int nj, int nk, int tri,
+            int conj, int m0, int t0, int units, cpx<A>* acc, int64_t ld_acc, int first, void* out, int64_t ld_out,
+            int out_c64, int last, PassGeom g, const cpx<T>* __restrict__ twx_g, const cpx<T>* __restrict__ twy_g,
+            int zsplit, TrajSegs segs, int jsplit, int64_t gstride, int dbl) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cpx<T>* s = reinterpret_cast<cpx<T>*>(smem_raw);
+  const int plane = plane_lds_elems(g);
+  cpx<T>* twx = s + (dbl ? 2 : 1) * plane;
+  cpx<T>* twy = twx + g.nx;
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  for (int i = tid; i < g.nx; i += nthr) twx[i] = twx_g[i];
+  for (int i = tid; i < g.ny; i += nthr) twy[i] = twy_g[i];
+  __syncthreads();
+  const int nxy = g.nx * g.ny;
+  const size_t nr = (size_t)nxy * g.nz;
+  const int total = g.ny * g.ax.st[0].nb, span = g.ax.st[0].span;
+  // the orbital values once the transform's registers are free: FP32 with sums
+  // of up to 8 values then keeps four waves per SIMD (64^3: 1200 -> 850 us)
+  constexpr bool kLate = sizeof(T) == 8 || R * IT > 4;
+  const A sgn = conj ? (A)-1 : (A)1;
+  int pos[IT];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) pos[it] = row_last_pos(g, tid + it * nthr);
+  const auto owns = [&](int it) __attribute__((always_inline)) { return tid + it * nthr < total; };
+  const ItemMap im = item_map(g.nz, units, zsplit, gridDim.x, blockIdx.x);
+  int par = 0;
+  for (int li = im.first; li < im.total; li += im.step) {
+    int u, z;
+    im.at(li, &u, &z);
+    const int tt = u / jsplit, gr = u - tt * jsplit;
+    const int t = t0 + tt;
+    cpx<A>* accg = acc + gr * gstride + t * ld_acc + (size_t)z * nxy;
+    cpx<A> a[IT][R];
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+      for (int m = 0; m < R; ++m) {
+        a[it][m] = cpx<A>{0, 0};
+        if (!first && owns(it)) a[it][m] = accg[pos[it] + m * span];
+      }
+    // terms lo, lo + jsplit, ... < hi: those whose orbital m0 + l is gr mod jsplit
+    int lo = conj ? (tri ? tt + 1 : 0) : 0;
+    const int hi = conj ? nk : (tri ? tt + 1 : nj);
+    const int r = (m0 + lo) % jsplit;
+    lo += gr >= r ? gr - r : gr - r + jsplit;
+    for (int l = lo; l < hi; l += jsplit) {
+      const cpx<T>* pm = seg_psi<T>(segs, mult, t) + (int64_t)(m0 + l) * ld_mult + (size_t)z * nxy;
+      const int pl = conj ? plane_of(tt, l, nj, tri) : plane_of(l, tt, nj, tri);
+      cpx<T>* sl = s + (dbl && par ? plane : 0);
+      cpx<T> vp[IT][R];
+      const auto orbital = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int it = 0; it < IT; ++it)
+#pragma unroll
+          for (int m = 0; m < R; ++m)
+            if (owns(it)) vp[it][m] = pm[pos[it] + m * span];
+      };
+      pass_c_fft<T, RMAX>(work + (size_t)pl * nr + (size_t)z * nxy, sl, twx, twy, g, tid, nthr, DeviceSync{},
+                    [&]() __attribute__((always_inline)) {
+                      if (!kLate) orbital();
+                    });
+      cpx<T> x[IT][R];
+#pragma unroll
+      for (int it = 0; it < IT; ++it)
+        if (owns(it)) row_last_stage<R, T>(sl, twx, g, tid + it * nthr, x[it]);
+      if (kLate) orbital();
+#pragma unroll
+      for (int it = 0; it < IT; ++it)
+#pragma unroll
+        for (int m = 0; m < R; ++m)
+          if (owns(it))
+            a[it][m] = cfma(a[it][m], cpx<A>{(A)vp[it][m].x, (A)vp[it][m].y},
+                            cpx<A>{(A)x[it][m].x, sgn * (A)x[it][m].y});
+      if (dbl)
+        par ^= 1;
+      else
+        __syncthreads();
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+      for (int m = 0; m < R; ++m) {
+        if (!owns(it)) continue;
+        const int e = pos[it] + m * span;
+        if (!last) {
+          accg[e] = a[it][m];
+        } else {
+          const size_t off = t * ld_out + (size_t)z * nxy + e;
+          if (out_c64)
+            reinterpret_cast<cpx<float>*>(out)[off] = cpx<float>{(float)a[it][m].x, (float)a[it][m].y};
+          else
+            reinterpret_cast<cpx<double>*>(out)[off] = cpx<double>{(double)a[it][m].x, (double)a[it][m].y};
+        }
+      }
+  }
+}
+
+// ---- host side ------------------------------------------------------------------
+static int round64(int v) { return (v + 63) / 64 * 64; }
+
+// Persistent grid: resident workgroups, a multiple of the XCD count.
+template <typename K>
+static fx_status gen_grid(fx_ctx* ctx, K kernel, int nthr, size_t lds, int64_t items, int* grid) {
+  FX_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds));
+  int per_cu = 0;
+  FX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel), nthr, lds));
+  int g = (int)std::max<int64_t>(1, std::min<int64_t>(items, (int64_t)std::max(per_cu, 1) * std::max(ctx->n_cu, 1)));
+  if (g >= kXcds) g -= g % kXcds;
+  *grid = g;
+  return FX_OK;
+}
+
+// Threads of a plane-forward workgroup.  A stage of `total` butterflies of
+// radix R takes ceil(total / t) rounds of about R + 4 LDS accesses and 4 more
+// for its barrier; the workgroups that LDS and registers (at most `waves` per
+// CU) let a CU hold overlap each other up to 20 waves, past which the CU's
+// issue rate is shared.  On ten planes from 9 x 8 to 96 x 96 in both precisions
+// the count with the smallest time per plane so estimated measured within 5%
+// of the best of 64, 128, ... 512, which itself is 1.2 to 5 times faster than
+// the worst.
+static int plane_threads(const PassGeom& g, size_t lds, int waves) {
+  int best = 64;
+  double best_cost = 0.0;
+  for (int t = 64; t <= kGenAThreads; t += 64) {
+    double c = (g.nx * g.ny + t - 1) / t + 4.0;
+    const auto add = [&](const AxisArg& a, int lines) {
+      for (int st = 0; st < a.nst; ++st) c += ((lines * a.st[st].nb + t - 1) / t) * (a.st[st].R + 4.0) + 4.0;
+    };
+    add(g.ax, g.ny);
+    add(g.ay, g.nx);
+    const int wg = std::max(1, std::min({(int)((160 << 10) / lds), waves * 64 / t, 32}));
+    c *= std::max(1.0, wg * t / 64 / 20.0) / wg;
+    if (t == 64 || c < best_cost) {
+      best = t;
+      best_cost = c;
+    }
+  }
+  return best;
+}
+
+template <typename T>
+fx_status gen_pass_a(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb, const CtBatch<T>& b) {
+  const size_t lds = ((size_t)plane_lds_elems(g) + g.nx + g.ny) * sizeof(cpx<T>);
+  const int nthr = plane_threads(g, lds, sizeof(T) == 4 ? 28 : 16);
+  const auto kern = k_gen_a<T>;
+  int grid = 0;
+  FX_TRY(gen_grid(ctx, kern, nthr, lds, (int64_t)b.npairs * g.nz, &grid));
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(nthr), lds, st, b.psi, b.ld_psi, b.phi, b.ld_phi, b.work, b.j0, b.nj, b.k0,
+                     b.tri, b.npairs, g, (const cpx<T>*)tb->tw[0], (const cpx<T>*)tb->tw[1], b.zsplit & 5, b.segs);
+  FX_LAUNCH_CHECK();
+  return FX_OK;
+}
+
+template <typename T>
+fx_status gen_pass_b(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb, const CtBatch<T>& b,
+                     int xtile, int most_threads) {
+  // Columns of a tile: whole x rows (the longest runs in memory) where the
+  // tile stays within 56 KB of LDS, so that two workgroups share a CU; else the
+  // largest divisor of the edge within 50 KB (a ragged last tile wastes its
+  // share of the threads).  48 x 64 x 72 FP64: 32 columns 1566 us, whole rows
+  // 1327; 81 x 54 x 64 FP32: 32 1770, 81 1159; 96 x 96 x 64 FP64: whole rows
+  // (96 KB) 2127, 48 1909, 32 1807.
+  int xt = g.nx;
+  if (xtile > 0) {
+    xt = std::min(g.nx, xtile);
+  } else if ((size_t)g.nz * g.nx * sizeof(cpx<T>) > 56 * 1024) {
+    do {
+      do --xt;
+      while (g.nx % xt != 0);
+    } while (xt > 1 && (size_t)g.nz * xt * sizeof(cpx<T>) > 50 * 1024);
+  }
+  const int ntx = (g.nx + xt - 1) / xt;
+  int widest = 0;
+  for (int i = 0; i < g.az.nst; ++i) widest = std::max(widest, xt * g.az.st[i].nb);
+  const int cap = most_threads > 0 ? std::min(most_threads, kPencilThreads) : kPencilThreads;
+  const int nthr = std::min(cap, round64(widest));
+  const size_t lds = ((size_t)g.nz * xt + g.nz) * sizeof(cpx<T>) + (size_t)g.hz * g.hx * sizeof(T) +
+                     (size_t)(g.nx + g.nz) * sizeof(int);
+  const auto kern = k_gen_b<T>;
+  FX_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
+  const Lines tile{xt, xt, fast_div(xt)};
+  hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)b.npairs * g.ny * ntx)), dim3(nthr), lds, st, b.work, tile, ntx, g,
+                     (const cpx<T>*)tb->tw[2], (const T*)tb->kfold, tb->fold[0], tb->fold[1], tb->fold[2]);
+  FX_LAUNCH_CHECK();
+  return FX_OK;
+}
+
+template <typename T, typename A, int R, int IT, int RMAX>
+static fx_status gen_c_launch(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb, const CtBatch<T>& b,
+                              const CtAcc<A>& c, int role) {
+  const size_t plane = (size_t)plane_lds_elems(g) * sizeof(cpx<T>), tw = (size_t)(g.nx + g.ny) * sizeof(cpx<T>);
+  const int dbl = 2 * plane <= 40 * 1024;
+  const size_t lds = (dbl ? 2 : 1) * plane + tw;
+  const int total = g.ny * g.ax.st[0].nb;
+  const int nthr = round64((total + IT - 1) / IT);
+  const int units = (role ? b.nj : b.nk) * b.jsplit;
+  const auto kern = k_gen_c<T, A, R, IT, RMAX>;
+  int grid = 0;
+  FX_TRY(gen_grid(ctx, kern, nthr, lds, (int64_t)units * g.nz, &grid));
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(nthr), lds, st, role ? b.phi : b.psi, role ? b.ld_phi : b.ld_psi,
+                     (const cpx<T>*)b.work, b.nj, b.nk, b.tri, role, role ? b.k0 : b.j0, role ? b.j0 : b.k0, units,
+                     c.acc, c.ld_acc, c.first, c.out, c.ld_out, c.out_c64, c.last, g, (const cpx<T>*)tb->tw[0],
+                     (const cpx<T>*)tb->tw[1], (b.zsplit >> 1) & 1, role ? TrajSegs{} : b.segs, b.jsplit, c.gstride,
+                     dbl);
+  FX_LAUNCH_CHECK();
+  return FX_OK;
+}
+
+// IT > 1 only where the first x radix of a tuned schedule leaves more
+// butterflies than one per thread of the launch bound.
+template <typename T, typename A, int R, int ITM>
+static fx_status gen_c_radix(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb, const CtBatch<T>& b,
+                             const CtAcc<A>& c, int role) {
+  // radices of the stages that run through LDS; up to 8, the kernel without
+  // the wider ones (in FP64 those cost it 100 to 300 bytes of spills)
+  int widest = 2;
+  for (int i = 1; i < g.ax.nst; ++i) widest = std::max(widest, g.ax.st[i].R);
+  for (int i = 0; i < g.ay.nst; ++i) widest = std::max(widest, g.ay.st[i].R);
+  if (g.ny * g.ax.st[0].nb <= kGenCThreads)
+    return widest <= 8 ? gen_c_launch<T, A, R, 1, 8>(ctx, st, g, tb, b, c, role)
+                       : gen_c_launch<T, A, R, 1, 12>(ctx, st, g, tb, b, c, role);
+  if constexpr (ITM > 1) return gen_c_launch<T, A, R, ITM, 12>(ctx, st, g, tb, b, c, role);
+  FX_FAIL(FX_ERR_UNSUPPORTED, "no plane-inverse kernel for %d butterflies of radix %d", g.ny * g.ax.st[0].nb, R);
+}
+
+template <typename T, typename A>
+fx_status gen_pass_c(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb, const CtBatch<T>& b,
+                     const CtAcc<A>& c, int role) {
+  switch (g.ax.st[0].R) {
+    // most butterflies of a stage: 96 rows x 96 / R (radix 9: x 9), so
+    // ITM = ceil(9216 / (768 R))
+    case 2: return gen_c_radix<T, A, 2, 6>(ctx, st, g, tb, b, c, role);
+    case 3: return gen_c_radix<T, A, 3, 4>(ctx, st, g, tb, b, c, role);
+    case 4: return gen_c_radix<T, A, 4, 3>(ctx, st, g, tb, b, c, role);
+    case 6: return gen_c_radix<T, A, 6, 2>(ctx, st, g, tb, b, c, role);
+    case 8: return gen_c_radix<T, A, 8, 2>(ctx, st, g, tb, b, c, role);
+    case 9: return gen_c_radix<T, A, 9, 2>(ctx, st, g, tb, b, c, role);
+    case 12: return gen_c_radix<T, A, 12, 1>(ctx, st, g, tb, b, c, role);
+    default: FX_FAIL(FX_ERR_UNSUPPORTED, "no plane-inverse kernel for radix %d", g.ax.st[0].R);
+  }
+}
+
+template fx_status gen_pass_a<float>(fx_ctx*, hipStream_t, const PassGeom&, const GridTables*, const CtBatch<float>&);
+template fx_status gen_pass_a<double>(fx_ctx*, hipStream_t, const PassGeom&, const GridTables*, const CtBatch<double>&);
+template fx_status gen_pass_b<float>(fx_ctx*, hipStream_t, const PassGeom&, const GridTables*, const CtBatch<float>&,
+                                     int, int);
+template fx_status gen_pass_b<double>(fx_ctx*, hipStream_t, const PassGeom&, const GridTables*, const CtBatch<double>&,
+                                      int, int);
+template fx_status gen_pass_c<float, double>(fx_ctx*, hipStream_t, const PassGeom&, const GridTables*,
+                                             const CtBatch<float>&, const CtAcc<double>&, int);
+template fx_status gen_pass_c<float, float>(fx_ctx*, hipStream_t, const PassGeom&, const GridTables*,
+                                            const CtBatch<float>&, const CtAcc<float>&, int);
+template fx_status gen_pass_c<double, double>(fx_ctx*, hipStream_t, const PassGeom&, const GridTables*,
+                                              const CtBatch<double>&, const CtAcc<double>&, int);
+
+}  // namespace fx
