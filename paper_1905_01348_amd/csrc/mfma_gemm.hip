@@ -90,22 +90,33 @@ __device__ inline double scale_of(const unsigned* maxbits, int i) {
 
 // Largest |x| of each column (per_col) or of all columns, as FP32 bits
 // (monotone for non-negative floats, so an integer max merges blocks);
-// `out` must hold zeros first.  x: real view, column c at x + c * ld.
+// `out` must hold zeros first.  x: complex columns of nr values, column c at
+// x + c * ld.  Read-bound: four complex loads in flight per thread, and blocks
+// of at most 2048 values (with 32768, the 8 columns of a request at 48^3 ran in
+// 32 workgroups, 55 us).
 template <typename T>
-__global__ void k_absmax(const T* __restrict__ x, int64_t ld, int64_t len, int per_col, unsigned* __restrict__ out) {
-  __shared__ float red[256];
+__global__ void __launch_bounds__(256) k_absmax(const cpx<T>* __restrict__ x, int64_t ld, int64_t nr, int per_col,
+                                                unsigned* __restrict__ out) {
+  __shared__ float red[4];
   const int c = blockIdx.y;
-  const T* col = x + (int64_t)c * ld;
+  const cpx<T>* col = x + (int64_t)c * ld;
   float m = 0.f;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < len; i += (int64_t)gridDim.x * blockDim.x)
-    m = fmaxf(m, (float)fabs((double)col[i]));
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
-    __syncthreads();
+  const int64_t step = (int64_t)gridDim.x * 256;
+  for (int64_t i0 = blockIdx.x * (int64_t)256 + threadIdx.x; i0 < nr; i0 += 4 * step) {
+    cpx<T> v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = col[i0 + u * step < nr ? i0 + u * step : i0];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf((float)fabs((double)v[u].x), (float)fabs((double)v[u].y)));
   }
-  if (threadIdx.x == 0) atomicMax(out + (per_col ? c : 0), __float_as_uint(red[0]));
+  for (int w = 32; w > 0; w >>= 1) m = fmaxf(m, __shfl_xor(m, w));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    atomicMax(out + (per_col ? c : 0), __float_as_uint(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))));
+}
+static unsigned absmax_blocks(int64_t nr, int cols) {
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>((nr + 2047) / 2048, std::max(1, 8192 / cols)));
 }
 
 __global__ void k_zero_u32(unsigned* __restrict__ p, int n) {
@@ -592,6 +603,179 @@ __global__ void __launch_bounds__(256, 2) k_tn_mfma_dl(int M, int N, int K, int 
                             alpha, colalpha);
 }
 
+// ---------------------------------------------------------------------------
+// The TN GEMM for few right-hand sides (N <= 64 real columns): one wave per 32
+// rows of A, no LDS and no barrier.  Such a product is bound by reading A (xi
+// in p and r form: 113 MB at 48^3, 128 factors); in 128 x 128 tiles seven
+// eighths of the matrix work is padding and 128 workgroups with two barriers
+// per step leave half the chip idle (70 us for 8 right-hand sides, 1.6 TB/s).
+// Each lane reads its operands straight from memory: the four (two for r and
+// p each) 16-byte pieces of a step of row l % 32 that lane l multiplies, so a
+// wave uses whole 128-byte lines over a step, A three steps ahead, B (a few
+// rows, from L2) one.  CT: 32-wide column tiles (1 or 2).
+// The k terms of an element run in the order of k_tn_mfma over the same split
+// chunks, so a right-hand side's bits do not depend on which kernel ran.
+// MODE 0 as k_tn_mfma.  MODE 1 gives the matrix instruction B as its rows: lane
+// l then holds y(r = l % 32) of several targets, and stores run along r.
+// ---------------------------------------------------------------------------
+template <typename S>
+__device__ inline floatx16 mfma_vec(uint4 a, uint4 b, floatx16 c) {
+  if constexpr (std::is_same<S, float>::value) {
+    const float4 x = __builtin_bit_cast(float4, a), y = __builtin_bit_cast(float4, b);
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, c, 0, 0, 0);
+  } else if constexpr (std::is_same<S, _Float16>::value) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a), __builtin_bit_cast(halfx8, b), c, 0,
+                                                  0, 0);
+  } else {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                   0, 0);
+  }
+}
+
+template <typename S, bool REFINE, bool BDOUBLE, int MODE, int CT>
+__global__ void __launch_bounds__(64, 2) k_tn_skinny(int M, int N, int kchunk, int K, const S* __restrict__ Ap,
+                                                     const S* __restrict__ Ar, int64_t lda, const S* __restrict__ Bp,
+                                                     const S* __restrict__ Br, int64_t ldb,
+                                                     double* __restrict__ partial, void* __restrict__ out, int64_t ldo,
+                                                     int out_c64, const double* __restrict__ colalpha, int tiles_m) {
+  constexpr int BK = Prec<S>::BK;  // 128 bytes of a row
+  constexpr int DA = CT == 1 ? 4 : 2;  // A buffers: steps in flight plus one
+  const int lane = threadIdx.x, l32 = lane & 31, half = lane >> 5;
+  const int tm = blockIdx.x % tiles_m, split = blockIdx.x / tiles_m;
+  const int m0 = tm * 32;
+  const int kbeg = split * kchunk, kend = min(K, kbeg + kchunk);
+  // piece v of a step: bytes [off(v), off(v) + 16) of the row's 128 (k_tn_mfma's
+  // lane layout: 2-byte types k = 16 v + 8 half, FP32 k = 16 half + 4 v)
+  const auto off = [half](int v) { return sizeof(S) == 4 ? 16 * half + 4 * v : 16 * v + 8 * half; };
+  const int64_t arow = (int64_t)min(m0 + l32, M - 1) * lda;
+  const S* ap = Ap + arow;
+  const S* ar = Ar + arow;
+  const S *bp[CT], *br[CT];
+  bool odd[CT];
+#pragma unroll
+  for (int t = 0; t < CT; ++t) {
+    const int n = min(32 * t + l32, N - 1);
+    const int64_t row = (int64_t)(BDOUBLE ? n >> 1 : n) * ldb;
+    odd[t] = BDOUBLE && (n & 1);
+    bp[t] = Bp + row;
+    br[t] = Br + row;
+  }
+  uint4 fa[DA][REFINE ? 8 : 4], fb[2][CT][REFINE ? 8 : 4];
+  const auto load_a = [&](int k0, uint4 (&f)[REFINE ? 8 : 4]) __attribute__((always_inline)) {
+    const int k = min(k0, kend - BK);  // past the end: a valid step, not used
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      f[v] = *reinterpret_cast<const uint4*>(ap + k + off(v));
+      if (REFINE) f[4 + v] = *reinterpret_cast<const uint4*>(ar + k + off(v));
+    }
+  };
+  const auto load_b = [&](int k0, uint4 (&f)[CT][REFINE ? 8 : 4]) __attribute__((always_inline)) {
+    const int k = min(k0, kend - BK);
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        f[t][v] = *reinterpret_cast<const uint4*>(bp[t] + k + off(v));
+        if (REFINE) f[t][4 + v] = *reinterpret_cast<const uint4*>(br[t] + k + off(v));
+      }
+  };
+  const auto turned = [&](uint4 v, bool o) __attribute__((always_inline)) {
+    if (!BDOUBLE) return v;
+    const uint4 w = times_minus_i(v, sizeof(S));
+    return uint4{o ? w.x : v.x, o ? w.y : v.y, o ? w.z : v.z, o ? w.w : v.w};
+  };
+  floatx16 acc[CT], cor[CT];
+#pragma unroll
+  for (int t = 0; t < CT; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      acc[t][e] = 0.f;
+      cor[t][e] = 0.f;
+    }
+  const auto mul = [&](const uint4& x, const uint4& y, const floatx16& c) __attribute__((always_inline)) {
+    return MODE == 0 ? mfma_vec<S>(x, y, c) : mfma_vec<S>(y, x, c);
+  };
+  const auto step = [&](const uint4 (&a)[REFINE ? 8 : 4], const uint4 (&b)[CT][REFINE ? 8 : 4])
+      __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int t = 0; t < CT; ++t) {
+        const uint4 x = turned(b[t][v], odd[t]);
+        if constexpr (REFINE && std::is_same<S, float>::value) {
+          // k_tn_mfma interleaves the three products k by k
+          const uint4 x2 = turned(b[t][4 + v], odd[t]);
+          const float4 fa4 = __builtin_bit_cast(float4, a[v]), fr4 = __builtin_bit_cast(float4, a[4 + v]);
+          const float4 fb4 = __builtin_bit_cast(float4, x), fs4 = __builtin_bit_cast(float4, x2);
+          const float av[4] = {fa4.x, fa4.y, fa4.z, fa4.w}, rv[4] = {fr4.x, fr4.y, fr4.z, fr4.w};
+          const float bv[4] = {fb4.x, fb4.y, fb4.z, fb4.w}, sv[4] = {fs4.x, fs4.y, fs4.z, fs4.w};
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const auto m = [&](float p, float q, floatx16 c) __attribute__((always_inline)) {
+              return MODE == 0 ? __builtin_amdgcn_mfma_f32_32x32x2f32(p, q, c, 0, 0, 0)
+                               : __builtin_amdgcn_mfma_f32_32x32x2f32(q, p, c, 0, 0, 0);
+            };
+            acc[t] = m(av[u], bv[u], acc[t]);
+            cor[t] = m(av[u], sv[u], cor[t]);
+            cor[t] = m(rv[u], bv[u], cor[t]);
+          }
+        } else {
+          acc[t] = mul(a[v], x, acc[t]);
+          if constexpr (REFINE) {
+            cor[t] = mul(a[v], turned(b[t][4 + v], odd[t]), cor[t]);
+            cor[t] = mul(a[4 + v], x, cor[t]);
+          }
+        }
+      }
+  };
+  if (kbeg < kend) {
+#pragma unroll
+    for (int d = 0; d < DA - 1; ++d) load_a(kbeg + d * BK, fa[d]);
+    load_b(kbeg, fb[0]);
+    // DA steps per round, so that every buffer index is a constant
+    for (int k0 = kbeg; k0 < kend; k0 += DA * BK) {
+#pragma unroll
+      for (int d = 0; d < DA; ++d) {
+        load_a(k0 + (d + DA - 1) * BK, fa[(d + DA - 1) % DA]);
+        load_b(k0 + (d + 1) * BK, fb[(d + 1) & 1]);
+        if (k0 + d * BK < kend) step(fa[d], fb[d & 1]);
+      }
+    }
+  }
+  if (MODE == 0) {
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+      const int n = 32 * t + l32;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int m = m0 + 8 * (e >> 2) + 4 * half + (e & 3);
+        if (m < M && n < N)
+          partial[((int64_t)split * M + m) * N + n] = (double)acc[t][e] + (REFINE ? (double)cor[t][e] : 0.0);
+      }
+    }
+  } else {
+    const int m = m0 + l32;
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) {
+        const int n = 32 * t + 8 * (e >> 2) + 4 * half + (e & 3);
+        if (m >= M || n >= N) continue;
+        const double re = (double)acc[t][e] + (REFINE ? (double)cor[t][e] : 0.0);
+        const double im = (double)acc[t][e + 1] + (REFINE ? (double)cor[t][e + 1] : 0.0);
+        const int64_t idx = (int64_t)(n >> 1) * ldo + m;
+        const double al = colalpha ? colalpha[n >> 1] : 1.0;
+        if (out_c64)
+          reinterpret_cast<float2*>(out)[idx] = make_float2((float)(-al * re), (float)(-al * im));
+        else
+          reinterpret_cast<double2*>(out)[idx] = make_double2(-al * re, -al * im);
+      }
+  }
+}
+
 // ---- split kernels ----------------------------------------------------------
 // xi (complex double, N_r x N, ld N_r) -> col form: row m = interleaved column m.
 template <typename S>
@@ -641,52 +825,93 @@ __global__ void __launch_bounds__(256) k_split_row(const double* __restrict__ xi
 }
 
 // phi (complex, ld) -> B source rows: row n = interleaved phi_n, padded to kc.
+// Memory-bound; a thread makes one 16-byte vector of each of p and r (one value
+// per thread with a 64-bit division each ran at 2.5 TB/s: 1037 us for 432
+// columns at 72^3 in FP16).
 template <typename S, typename TI>
-__global__ void k_split_phi(const TI* __restrict__ phi, int64_t ld, int64_t nr, int R, int64_t kc,
-                            S* __restrict__ p, S* __restrict__ r, const unsigned* __restrict__ smax) {
-  const int64_t total = (int64_t)R * kc;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t n = i / kc, k = i - n * kc;
-    const double sc = scale_of(smax, (int)n);
-    if constexpr (std::is_same<TI, float>::value) {
-      // FP32 input: the scaled value and its residual are exact in FP32
-      // (a power-of-two factor that stays finite; X - round(X) of an FP32 X),
-      // so the split is the same as in FP64, at FP32 speed
-      if (sc < 0x1p100) {
-        const float v = k < 2 * nr ? (float)sc * phi[n * 2 * ld + k] : 0.f;
-        const S hp = Prec<S>::round_f(v);
-        p[i] = hp;
-        r[i] = Prec<S>::round_f(v - Prec<S>::widen_f(hp));
-        continue;
+__device__ inline void split_column(const cpx<TI>* __restrict__ col, int n, int64_t nr, int64_t kc, S* __restrict__ p,
+                                    S* __restrict__ r, const unsigned* __restrict__ smax) {
+  constexpr int V = 16 / sizeof(S);
+  const double sc = scale_of(smax, n);
+  // FP32 input: the scaled value and its residual are exact in FP32 (a
+  // power-of-two factor that stays finite; X - round(X) of an FP32 X), so the
+  // split is the same as in FP64, at FP32 speed
+  const bool exact32 = std::is_same<TI, float>::value && sc < 0x1p100;
+  for (int64_t k = (blockIdx.x * (int64_t)256 + threadIdx.x) * V; k < kc; k += (int64_t)gridDim.x * 256 * V) {
+    alignas(16) S hp[V], hr[V];
+#pragma unroll
+    for (int u = 0; u < V / 2; ++u) {
+      const int64_t i = k / 2 + u;
+      const cpx<TI> v = i < nr ? col[i] : cpx<TI>{0, 0};
+      const TI xv[2] = {v.x, v.y};
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if (exact32) {
+          const float x = (float)sc * (float)xv[q];
+          hp[2 * u + q] = Prec<S>::round_f(x);
+          hr[2 * u + q] = Prec<S>::round_f(x - Prec<S>::widen_f(hp[2 * u + q]));
+        } else {
+          const double x = sc * (double)xv[q];
+          hp[2 * u + q] = Prec<S>::round(x);
+          hr[2 * u + q] = Prec<S>::round(x - Prec<S>::widen(hp[2 * u + q]));
+        }
       }
     }
-    const double v = k < 2 * nr ? sc * (double)phi[n * 2 * ld + k] : 0.0;
-    const S hp = Prec<S>::round(v);
-    p[i] = hp;
-    r[i] = Prec<S>::round(v - Prec<S>::widen(hp));
+    *reinterpret_cast<uint4*>(p + n * kc + k) = *reinterpret_cast<const uint4*>(hp);
+    *reinterpret_cast<uint4*>(r + n * kc + k) = *reinterpret_cast<const uint4*>(hr);
   }
 }
+template <typename S, typename TI>
+__global__ void __launch_bounds__(256) k_split_phi(const cpx<TI>* __restrict__ phi, int64_t ld, int64_t nr, int R,
+                                                   int64_t kc, S* __restrict__ p, S* __restrict__ r,
+                                                   const unsigned* __restrict__ smax) {
+  for (int n = blockIdx.y; n < R; n += gridDim.y) split_column<S, TI>(phi + (int64_t)n * ld, n, nr, kc, p, r, smax);
+}
+
+// Sum of element i over the split partials, partial viewed as [nsplit][count]:
+// 16 threads of a block (q = 0 .. 15) add splits q, q + 16, ... of the same
+// element in ascending order, then their sums are added in order of q.  Every
+// thread of the block must call it; the sum is valid where q == 0.
+__device__ inline double2 sum_splits(const double2* __restrict__ partial, int64_t count, int nsplit, int64_t i,
+                                     double2 (&red)[16][17]) {
+  const int el = threadIdx.x & 15, q = threadIdx.x >> 4;
+  double2 s = {0.0, 0.0};
+  if (i < count) {
+#pragma unroll 4
+    for (int t = q; t < nsplit; t += 16) {
+      const double2 v = partial[t * count + i];
+      s.x += v.x;
+      s.y += v.y;
+    }
+  }
+  red[q][el] = s;
+  __syncthreads();
+  if (q == 0)
+    for (int t = 1; t < 16; ++t) {
+      s.x += red[t][el].x;
+      s.y += red[t][el].y;
+    }
+  __syncthreads();
+  return s;
+}
+static unsigned sum_blocks(int64_t count) { return (unsigned)std::min<int64_t>((count + 15) / 16, 16384); }
 
 // Fixed-order FP64 sum of the C = xi^H phi split partials, written as the B
 // operand of y = -xi C: row 2n = (Re C(k,n), -Im C(k,n)) pairs, row 2n+1 =
 // (Im C(k,n), Re C(k,n)) pairs, padded to kn; split p / r.
 template <typename S>
-__global__ void k_reduce_cn(const double* __restrict__ partial, int nsplit, int n, int R, int64_t kn,
-                            S* __restrict__ p, S* __restrict__ r) {
-  const int64_t M = n, NN = 2 * (int64_t)R;
-  const int64_t total = (int64_t)R * (kn / 2);
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    // neighbouring threads take neighbouring right-hand sides: their partial
-    // sums are adjacent in memory (the reads are the bulk of the traffic)
+__global__ void __launch_bounds__(256) k_reduce_cn(const double2* __restrict__ partial, int nsplit, int n, int R,
+                                                   int64_t kn, S* __restrict__ p, S* __restrict__ r) {
+  __shared__ double2 red[16][17];
+  const int64_t count = (int64_t)n * R;
+  // neighbouring elements are neighbouring right-hand sides of the same k; the
+  // padding k >= n follows them
+  for (int64_t b0 = blockIdx.x * (int64_t)16; b0 < (int64_t)R * (kn / 2); b0 += (int64_t)gridDim.x * 16) {
+    const int64_t i = b0 + (threadIdx.x & 15);
+    const double2 c = sum_splits(partial, count, nsplit, i, red);
+    if (threadIdx.x >= 16 || i >= (int64_t)R * (kn / 2)) continue;
     const int64_t k = i / R, nc = i - k * R;
-    double cr = 0.0, ci = 0.0;
-    if (k < n) {
-      for (int s = 0; s < nsplit; ++s) {
-        cr += partial[((int64_t)s * M + k) * NN + 2 * nc];
-        ci += partial[((int64_t)s * M + k) * NN + 2 * nc + 1];
-      }
-    }
-    const double v[4] = {cr, -ci, ci, cr};
+    const double v[4] = {c.x, -c.y, c.y, c.x};
     const int64_t base0 = (2 * nc) * kn + 2 * k, base1 = (2 * nc + 1) * kn + 2 * k;
     const int64_t idx[4] = {base0, base0 + 1, base1, base1 + 1};
 #pragma unroll
@@ -704,22 +929,21 @@ __global__ void k_reduce_cn(const double* __restrict__ partial, int nsplit, int 
 // right-hand side's largest magnitude merged into cmax[nc] (zeroed first).
 // Then the split of t_nc C with t_nc the power of two of cmax[nc], and
 // colalpha[nc] = 1 / (s_xi t_nc) for the epilogue of y = -xi C.
-__global__ void k_sum_cn_scaled(const double* __restrict__ partial, int nsplit, int n, int R,
-                                const unsigned* __restrict__ xmax, const unsigned* __restrict__ pmax,
-                                double2* __restrict__ c64, unsigned* __restrict__ cmax) {
-  const int64_t M = n, NN = 2 * (int64_t)R;
+__global__ void __launch_bounds__(256) k_sum_cn_scaled(const double2* __restrict__ partial, int nsplit, int n, int R,
+                                                       const unsigned* __restrict__ xmax,
+                                                       const unsigned* __restrict__ pmax, double2* __restrict__ c64,
+                                                       unsigned* __restrict__ cmax) {
+  __shared__ double2 red[16][17];
   const double sx = scale_of(xmax, 0);
-  const int64_t total = (int64_t)n * R;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t k = i / R, nc = i - k * R;
-    double cr = 0.0, ci = 0.0;
-    for (int s = 0; s < nsplit; ++s) {
-      cr += partial[((int64_t)s * M + k) * NN + 2 * nc];
-      ci += partial[((int64_t)s * M + k) * NN + 2 * nc + 1];
-    }
-    const double f = 1.0 / (sx * scale_of(pmax, (int)nc));
-    c64[i] = double2{cr * f, ci * f};
-    atomicMax(cmax + nc, __float_as_uint((float)fmax(fabs(cr * f), fabs(ci * f))));
+  const int64_t count = (int64_t)n * R;
+  for (int64_t b0 = blockIdx.x * (int64_t)16; b0 < count; b0 += (int64_t)gridDim.x * 16) {
+    const int64_t i = b0 + (threadIdx.x & 15);
+    const double2 c = sum_splits(partial, count, nsplit, i, red);
+    if (threadIdx.x >= 16 || i >= count) continue;
+    const int nc = (int)(i % R);
+    const double f = 1.0 / (sx * scale_of(pmax, nc));
+    c64[i] = double2{c.x * f, c.y * f};
+    atomicMax(cmax + nc, __float_as_uint((float)fmax(fabs(c.x * f), fabs(c.y * f))));
   }
 }
 
@@ -789,8 +1013,8 @@ static fx_status prepare_split_t(fx_ace* a, AceSplit* sp, hipStream_t st) {
     FX_TRY(ace_alloc(a, 256, &sp->smax));
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, (unsigned*)sp->smax, 1);
     FX_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_absmax<double>), dim3(std::max(1, 4096 / std::max(n, 1)) , (unsigned)n), dim3(256), 0, st,
-                       (const double*)a->xi, 2 * nr, 2 * nr, 0, (unsigned*)sp->smax);
+    hipLaunchKernelGGL((k_absmax<double>), dim3(absmax_blocks(nr, n), (unsigned)n), dim3(256), 0, st,
+                       (const cpx<double>*)a->xi, nr, nr, 0, (unsigned*)sp->smax);
     FX_LAUNCH_CHECK();
     smax = (const unsigned*)sp->smax;
   }
@@ -837,32 +1061,38 @@ static fx_status apply_t(fx_ctx* ctx, Workspace* ws, fx_ace* a, AceSplit* sp, co
   const size_t pb = sizeof(S) * (size_t)R * sp->kc;
   FX_TRY(ws_get(ctx, ws, split_name<S>(0), pb, &php));
   FX_TRY(ws_get(ctx, ws, split_name<S>(1), pb, &phr));
-  unsigned* pmax = nullptr;
+  unsigned *pmax = nullptr, *cmax = nullptr;
   double* colalpha = nullptr;
   if (kScaled<S>) {
     void* t = nullptr;
-    FX_TRY(ws_get(ctx, ws, "mf_phimax", sizeof(unsigned) * (size_t)R, &t));
+    // largest magnitudes: R of phi, then R of C
+    FX_TRY(ws_get(ctx, ws, "mf_phimax", 2 * sizeof(unsigned) * (size_t)R, &t));
     pmax = (unsigned*)t;
+    cmax = pmax + R;
     FX_TRY(ws_get(ctx, ws, "mf_colalpha", sizeof(double) * (size_t)R, &t));
     colalpha = (double*)t;
-    hipLaunchKernelGGL(k_zero_u32, dim3((unsigned)std::min(64, (R + 255) / 256)), dim3(256), 0, st, pmax, R);
+    hipLaunchKernelGGL(k_zero_u32, dim3((unsigned)std::min(64, (2 * R + 255) / 256)), dim3(256), 0, st, pmax, 2 * R);
     FX_LAUNCH_CHECK();
-    const dim3 g((unsigned)std::max<int64_t>(1, std::min<int64_t>(64, (2 * nr + 65535) / 65536)), (unsigned)R);
+    const dim3 g(absmax_blocks(nr, R), (unsigned)R);
     if (in_dtype == FX_C128)
-      hipLaunchKernelGGL((k_absmax<double>), g, dim3(256), 0, st, (const double*)phi, 2 * ld_phi, 2 * nr, 1, pmax);
+      hipLaunchKernelGGL((k_absmax<double>), g, dim3(256), 0, st, (const cpx<double>*)phi, ld_phi, nr, 1, pmax);
     else
-      hipLaunchKernelGGL((k_absmax<float>), g, dim3(256), 0, st, (const float*)phi, 2 * ld_phi, 2 * nr, 1, pmax);
+      hipLaunchKernelGGL((k_absmax<float>), g, dim3(256), 0, st, (const cpx<float>*)phi, ld_phi, nr, 1, pmax);
     FX_LAUNCH_CHECK();
   }
-  const int64_t tp = (int64_t)R * sp->kc;
   int slot;
   FX_TRY(prof_begin(ctx, st, FX_K_SPLIT, (double)R * nr * (in_dtype == FX_C128 ? 16 : 8) + 2.0 * pb, &slot));
-  if (in_dtype == FX_C128)
-    hipLaunchKernelGGL((k_split_phi<S, double>), dim3((unsigned)std::min<int64_t>((tp + 255) / 256, 16384)),
-                       dim3(256), 0, st, (const double*)phi, ld_phi, nr, R, sp->kc, (S*)php, (S*)phr, pmax);
-  else
-    hipLaunchKernelGGL((k_split_phi<S, float>), dim3((unsigned)std::min<int64_t>((tp + 255) / 256, 16384)),
-                       dim3(256), 0, st, (const float*)phi, ld_phi, nr, R, sp->kc, (S*)php, (S*)phr, pmax);
+  {
+    constexpr int64_t kPerBlock = 256 * (16 / sizeof(S));
+    const dim3 g((unsigned)std::min<int64_t>((sp->kc + kPerBlock - 1) / kPerBlock, 4096),
+                 (unsigned)std::min(R, 32768));
+    if (in_dtype == FX_C128)
+      hipLaunchKernelGGL((k_split_phi<S, double>), g, dim3(256), 0, st, (const cpx<double>*)phi, ld_phi, nr, R, sp->kc,
+                         (S*)php, (S*)phr, (const unsigned*)pmax);
+    else
+      hipLaunchKernelGGL((k_split_phi<S, float>), g, dim3(256), 0, st, (const cpx<float>*)phi, ld_phi, nr, R, sp->kc,
+                         (S*)php, (S*)phr, (const unsigned*)pmax);
+  }
   FX_LAUNCH_CHECK();
   FX_TRY(prof_end(ctx, st, slot));
 
@@ -883,20 +1113,30 @@ static fx_status apply_t(fx_ctx* ctx, Workspace* ws, fx_ace* a, AceSplit* sp, co
     nsplit = (int)((sp->kc + kchunk - 1) / kchunk);
     void* part = nullptr;
     FX_TRY(ws_get(ctx, ws, "mf_partial", sizeof(double) * (size_t)nsplit * n * 2 * R, &part));
-    auto kern = k_tn_mfma<S, REFINE, true, 0>;
-    size_t lds_cn = lds;
-    if constexpr (sizeof(S) == 2) {
-      if (ace_direct_lds(0)) {
-        kern = k_tn_mfma_dl<S, REFINE, true, 0>;
-        lds_cn = 2 * dl_stage_bytes<S, REFINE, true>();
-      }
-    }
-    FX_TRY(allow_lds_mfma(kern, lds_cn));
+    // up to 32 right-hand sides: a wave per 32 rows instead of 128 x 128 tiles
+    const bool skinny = R <= 32;
     FX_TRY(prof_begin(ctx, st, FX_K_GEMM_CN, (REFINE ? 3.0 : 1.0) * 2.0 * n * 2.0 * R * (double)sp->kc, &slot));
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * nsplit)), dim3(256), lds_cn, st, n, 2 * R, (int)sp->kc,
-                       (int)kchunk, (const S*)sp->col_p, (const S*)sp->col_r, sp->kc, (const S*)php, (const S*)phr,
-                       sp->kc, (double*)part, (void*)nullptr, (int64_t)0, 0, 0.0, (const double*)nullptr, tiles_m,
-                       tiles_n);
+    if (skinny) {
+      const int tms = (n + 31) / 32;
+      const auto kern = R <= 16 ? k_tn_skinny<S, REFINE, true, 0, 1> : k_tn_skinny<S, REFINE, true, 0, 2>;
+      hipLaunchKernelGGL(kern, dim3((unsigned)(tms * nsplit)), dim3(64), 0, st, n, 2 * R, (int)kchunk, (int)sp->kc,
+                         (const S*)sp->col_p, (const S*)sp->col_r, sp->kc, (const S*)php, (const S*)phr, sp->kc,
+                         (double*)part, (void*)nullptr, (int64_t)0, 0, (const double*)nullptr, tms);
+    } else {
+      auto kern = k_tn_mfma<S, REFINE, true, 0>;
+      size_t lds_cn = lds;
+      if constexpr (sizeof(S) == 2) {
+        if (ace_direct_lds(0)) {
+          kern = k_tn_mfma_dl<S, REFINE, true, 0>;
+          lds_cn = 2 * dl_stage_bytes<S, REFINE, true>();
+        }
+      }
+      FX_TRY(allow_lds_mfma(kern, lds_cn));
+      hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * nsplit)), dim3(256), lds_cn, st, n, 2 * R, (int)sp->kc,
+                         (int)kchunk, (const S*)sp->col_p, (const S*)sp->col_r, sp->kc, (const S*)php, (const S*)phr,
+                         sp->kc, (double*)part, (void*)nullptr, (int64_t)0, 0, 0.0, (const double*)nullptr, tiles_m,
+                         tiles_n);
+    }
     FX_LAUNCH_CHECK();
     FX_TRY(prof_end(ctx, st, slot));
     // reduce -> B operand of the second product
@@ -907,43 +1147,45 @@ static fx_status apply_t(fx_ctx* ctx, Workspace* ws, fx_ace* a, AceSplit* sp, co
     const int64_t tr = (int64_t)R * (sp->kn / 2);
     FX_TRY(prof_begin(ctx, st, FX_K_REDUCE, 8.0 * nsplit * n * 2.0 * R + 2.0 * bb, &slot));
     if (kScaled<S>) {
-      void *c64 = nullptr, *cmax = nullptr;
+      void* c64 = nullptr;
       FX_TRY(ws_get(ctx, ws, "mf_c64", 16 * (size_t)n * R, &c64));
-      FX_TRY(ws_get(ctx, ws, "mf_cmax", sizeof(unsigned) * (size_t)R, &cmax));
-      hipLaunchKernelGGL(k_zero_u32, dim3((unsigned)std::min(64, (R + 255) / 256)), dim3(256), 0, st,
-                         (unsigned*)cmax, R);
-      FX_LAUNCH_CHECK();
-      const int64_t tc = (int64_t)n * R;
-      hipLaunchKernelGGL(k_sum_cn_scaled, dim3((unsigned)std::min<int64_t>((tc + 255) / 256, 16384)), dim3(256), 0,
-                         st, (const double*)part, nsplit, n, R, (const unsigned*)sp->smax, (const unsigned*)pmax,
-                         (double2*)c64, (unsigned*)cmax);
+      hipLaunchKernelGGL(k_sum_cn_scaled, dim3(sum_blocks((int64_t)n * R)), dim3(256), 0, st, (const double2*)part,
+                         nsplit, n, R, (const unsigned*)sp->smax, (const unsigned*)pmax, (double2*)c64, cmax);
       FX_LAUNCH_CHECK();
       hipLaunchKernelGGL((k_split_cn_scaled<S>), dim3((unsigned)std::min<int64_t>((tr + 255) / 256, 16384)),
                          dim3(256), 0, st, (const double2*)c64, n, R, sp->kn, (const unsigned*)sp->smax,
                          (const unsigned*)cmax, (S*)bp, (S*)br, colalpha);
     } else {
-      hipLaunchKernelGGL((k_reduce_cn<S>), dim3((unsigned)std::min<int64_t>((tr + 255) / 256, 16384)), dim3(256), 0,
-                         st, (const double*)part, nsplit, n, R, sp->kn, (S*)bp, (S*)br);
+      hipLaunchKernelGGL((k_reduce_cn<S>), dim3(sum_blocks(tr)), dim3(256), 0, st, (const double2*)part, nsplit, n, R,
+                         sp->kn, (S*)bp, (S*)br);
     }
     FX_LAUNCH_CHECK();
     FX_TRY(prof_end(ctx, st, slot));
     // y = -xi C: M = nr, N = 2R, K = kn
-    const int tm2 = (int)((nr + TBM - 1) / TBM), tn2 = (2 * R + TBN - 1) / TBN;
-    auto kern2 = k_tn_mfma<S, REFINE, false, 1>;
-    // the epilogue turns each wave's 32x32 tiles around in 32 x 33 doubles of LDS
-    size_t lds2 = std::max(lds, (size_t)4 * 32 * 33 * sizeof(double));
-    if constexpr (sizeof(S) == 2) {
-      if (ace_direct_lds(1)) {
-        kern2 = k_tn_mfma_dl<S, REFINE, false, 1>;
-        lds2 = std::max(2 * dl_stage_bytes<S, REFINE, false>(), (size_t)4 * 32 * 33 * sizeof(double));
-      }
-    }
-    FX_TRY(allow_lds_mfma(kern2, lds2));
     FX_TRY(prof_begin(ctx, st, FX_K_GEMM_NN, (REFINE ? 3.0 : 1.0) * 2.0 * (double)nr * 2.0 * R * (double)sp->kn, &slot));
-    hipLaunchKernelGGL(kern2, dim3((unsigned)(tm2 * tn2)), dim3(256), lds2, st, (int)nr, 2 * R, (int)sp->kn,
-                       (int)sp->kn, (const S*)sp->row_p, (const S*)sp->row_r, sp->kn, (const S*)bp, (const S*)br,
-                       sp->kn, (double*)nullptr, out, ld_out, out_dtype == FX_C64 ? 1 : 0, 1.0,
-                       (const double*)colalpha, tm2, tn2);
+    if (skinny) {
+      const int tms = (int)((nr + 31) / 32);
+      const auto kern = R <= 16 ? k_tn_skinny<S, REFINE, false, 1, 1> : k_tn_skinny<S, REFINE, false, 1, 2>;
+      hipLaunchKernelGGL(kern, dim3((unsigned)tms), dim3(64), 0, st, (int)nr, 2 * R, (int)sp->kn, (int)sp->kn,
+                         (const S*)sp->row_p, (const S*)sp->row_r, sp->kn, (const S*)bp, (const S*)br, sp->kn,
+                         (double*)nullptr, out, ld_out, out_dtype == FX_C64 ? 1 : 0, (const double*)colalpha, tms);
+    } else {
+      const int tm2 = (int)((nr + TBM - 1) / TBM), tn2 = (2 * R + TBN - 1) / TBN;
+      auto kern2 = k_tn_mfma<S, REFINE, false, 1>;
+      // the epilogue turns each wave's 32x32 tiles around in 32 x 33 doubles of LDS
+      size_t lds2 = std::max(lds, (size_t)4 * 32 * 33 * sizeof(double));
+      if constexpr (sizeof(S) == 2) {
+        if (ace_direct_lds(1)) {
+          kern2 = k_tn_mfma_dl<S, REFINE, false, 1>;
+          lds2 = std::max(2 * dl_stage_bytes<S, REFINE, false>(), (size_t)4 * 32 * 33 * sizeof(double));
+        }
+      }
+      FX_TRY(allow_lds_mfma(kern2, lds2));
+      hipLaunchKernelGGL(kern2, dim3((unsigned)(tm2 * tn2)), dim3(256), lds2, st, (int)nr, 2 * R, (int)sp->kn,
+                         (int)sp->kn, (const S*)sp->row_p, (const S*)sp->row_r, sp->kn, (const S*)bp, (const S*)br,
+                         sp->kn, (double*)nullptr, out, ld_out, out_dtype == FX_C64 ? 1 : 0, 1.0,
+                         (const double*)colalpha, tm2, tn2);
+    }
     FX_LAUNCH_CHECK();
     FX_TRY(prof_end(ctx, st, slot));
   }
