@@ -609,10 +609,11 @@ __global__ void __launch_bounds__(256, 2) k_tn_mfma_dl(int M, int N, int K, int 
 // in p and r form: 113 MB at 48^3, 128 factors); in 128 x 128 tiles seven
 // eighths of the matrix work is padding and 128 workgroups with two barriers
 // per step leave half the chip idle (70 us for 8 right-hand sides, 1.6 TB/s).
-// Each lane reads its operands straight from memory: the four (two for r and
-// p each) 16-byte pieces of a step of row l % 32 that lane l multiplies, so a
-// wave uses whole 128-byte lines over a step, A three steps ahead, B (a few
-// rows, from L2) one.  CT: 32-wide column tiles (1 or 2).
+// Each lane reads its operands straight from memory: the four 16-byte pieces
+// of a step of row l % 32 that lane l multiplies (of p and of r), so a wave
+// uses whole 128-byte lines over a step, A three steps ahead (one for two
+// column tiles and for the short reductions of MODE 1), B, a few rows in L2,
+// one.  CT: 32-wide column tiles (1 or 2).
 // The k terms of an element run in the order of k_tn_mfma over the same split
 // chunks, so a right-hand side's bits do not depend on which kernel ran.
 // MODE 0 as k_tn_mfma.  MODE 1 gives the matrix instruction B as its rows: lane
@@ -636,13 +637,13 @@ __device__ inline floatx16 mfma_vec(uint4 a, uint4 b, floatx16 c) {
 }
 
 template <typename S, bool REFINE, bool BDOUBLE, int MODE, int CT>
-__global__ void __launch_bounds__(64, 2) k_tn_skinny(int M, int N, int kchunk, int K, const S* __restrict__ Ap,
+__global__ void __launch_bounds__(64, (MODE == 1 ? 3 : 2)) k_tn_skinny(int M, int N, int kchunk, int K, const S* __restrict__ Ap,
                                                      const S* __restrict__ Ar, int64_t lda, const S* __restrict__ Bp,
                                                      const S* __restrict__ Br, int64_t ldb,
                                                      double* __restrict__ partial, void* __restrict__ out, int64_t ldo,
                                                      int out_c64, const double* __restrict__ colalpha, int tiles_m) {
   constexpr int BK = Prec<S>::BK;  // 128 bytes of a row
-  constexpr int DA = CT == 1 ? 4 : 2;  // A buffers: steps in flight plus one
+  constexpr int DA = CT == 1 && MODE == 0 ? 4 : 2;  // A buffers: steps in flight plus one
   const int lane = threadIdx.x, l32 = lane & 31, half = lane >> 5;
   const int tm = blockIdx.x % tiles_m, split = blockIdx.x / tiles_m;
   const int m0 = tm * 32;
@@ -1104,7 +1105,6 @@ static fx_status apply_t(fx_ctx* ctx, Workspace* ws, fx_ace* a, AceSplit* sp, co
     const int64_t ksteps = sp->kc / BK;
     // the split depends on the reduction length only, so a column's result
     // does not depend on how many right-hand sides share the launch
-    (void)tiles;
     // (up to 128 chunks of at least 16 steps: enough workgroups for a few
     // right-hand sides, where the output has only a handful of tiles)
     int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(128, ksteps / 16));
@@ -1113,10 +1113,14 @@ static fx_status apply_t(fx_ctx* ctx, Workspace* ws, fx_ace* a, AceSplit* sp, co
     nsplit = (int)((sp->kc + kchunk - 1) / kchunk);
     void* part = nullptr;
     FX_TRY(ws_get(ctx, ws, "mf_partial", sizeof(double) * (size_t)nsplit * n * 2 * R, &part));
-    // up to 32 right-hand sides: a wave per 32 rows instead of 128 x 128 tiles
-    const bool skinny = R <= 32;
+    // Up to 16 right-hand sides (one column tile) a wave per 32 rows instead of
+    // 128 x 128 tiles, up to 32 in FP32 or where the tiles would not fill the
+    // chip twice (measured, us, waves against tiles: 16-bit, 48^3, 128 factors,
+    // 8: 31 / 93, 32: 57 / 93; 72^3, 432 factors, 16: 372 / 410, 24: 576 / 410;
+    // FP32, 432 factors, 8: 795 / 2350, 32: 1694 / 2350).
+    const bool waves_cn = R <= 16 || (R <= 32 && (sizeof(S) == 4 || tiles * nsplit < 512));
     FX_TRY(prof_begin(ctx, st, FX_K_GEMM_CN, (REFINE ? 3.0 : 1.0) * 2.0 * n * 2.0 * R * (double)sp->kc, &slot));
-    if (skinny) {
+    if (waves_cn) {
       const int tms = (n + 31) / 32;
       const auto kern = R <= 16 ? k_tn_skinny<S, REFINE, true, 0, 1> : k_tn_skinny<S, REFINE, true, 0, 2>;
       hipLaunchKernelGGL(kern, dim3((unsigned)(tms * nsplit)), dim3(64), 0, st, n, 2 * R, (int)kchunk, (int)sp->kc,
@@ -1163,13 +1167,21 @@ static fx_status apply_t(fx_ctx* ctx, Workspace* ws, fx_ace* a, AceSplit* sp, co
     FX_TRY(prof_end(ctx, st, slot));
     // y = -xi C: M = nr, N = 2R, K = kn
     FX_TRY(prof_begin(ctx, st, FX_K_GEMM_NN, (REFINE ? 3.0 : 1.0) * 2.0 * (double)nr * 2.0 * R * (double)sp->kn, &slot));
-    if (skinny) {
-      const int tms = (int)((nr + 31) / 32);
-      const auto kern = R <= 16 ? k_tn_skinny<S, REFINE, false, 1, 1> : k_tn_skinny<S, REFINE, false, 1, 2>;
-      hipLaunchKernelGGL(kern, dim3((unsigned)tms), dim3(64), 0, st, (int)nr, 2 * R, (int)sp->kn, (int)sp->kn,
-                         (const S*)sp->row_p, (const S*)sp->row_r, sp->kn, (const S*)bp, (const S*)br, sp->kn,
-                         (double*)nullptr, out, ld_out, out_dtype == FX_C64 ? 1 : 0, (const double*)colalpha, tms);
-    } else {
+    // FP32, up to 32 right-hand sides: by waves too (8 right-hand sides with 432
+    // factors at 72^3 2233 -> 1020 us, 32 of them 2296 -> 1980); the 2-byte types
+    // keep the direct-to-LDS tiles (8: 303 against 417 us)
+    bool waves_out = false;
+    if constexpr (sizeof(S) == 4) {
+      waves_out = R <= 32;
+      if (waves_out) {
+        const int tms = (int)((nr + 31) / 32);
+        const auto kern = R <= 16 ? k_tn_skinny<S, REFINE, false, 1, 1> : k_tn_skinny<S, REFINE, false, 1, 2>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)tms), dim3(64), 0, st, (int)nr, 2 * R, (int)sp->kn, (int)sp->kn,
+                           (const S*)sp->row_p, (const S*)sp->row_r, sp->kn, (const S*)bp, (const S*)br, sp->kn,
+                           (double*)nullptr, out, ld_out, out_dtype == FX_C64 ? 1 : 0, (const double*)colalpha, tms);
+      }
+    }
+    if (!waves_out) {
       const int tm2 = (int)((nr + TBM - 1) / TBM), tn2 = (2 * R + TBN - 1) / TBN;
       auto kern2 = k_tn_mfma<S, REFINE, false, 1>;
       // the epilogue turns each wave's 32x32 tiles around in 32 x 33 doubles of LDS
