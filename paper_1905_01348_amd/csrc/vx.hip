@@ -228,8 +228,8 @@ struct PairPasses {
 // Halved apply for phi == psi (all N targets): each unordered pair {j, k} is
 // solved once, as (min, max), since v_kj = conj(v_jk) for a real, even kernel.
 // Orbitals are cut into blocks of B; block pairs (J <= K) run in ascending
-// order of J, then K.  For each, pass C runs twice: role 0 adds the pairs to
-// the targets of block K, role 1 (conjugated) to those of block J.  Every
+// order of J, then K.  For each, pass C takes both roles: role 0 adds the pairs
+// to the targets of block K, role 1 (conjugated) to those of block J.  Every
 // output column then receives its terms in ascending j, each term computed
 // from the ordered pair (min(j,k), max(j,k)), so the result does not depend
 // on B.  Diagonal block pairs hold only the B(B+1)/2 pairs j <= k.
@@ -249,7 +249,7 @@ static fx_status run_halved(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const P
   const bool out_c64 = a.out_dtype == FX_C64;
   const bool out_is_A = (sizeof(A) == 8) == !out_c64;
   const int jsplit = ct_jsplit(a, pass.g, true);
-  // partial sums live between the two roles of every block pair
+  // partial sums live between the block pairs
   cpx<A>* acc = nullptr;
   int64_t ld_acc = 0, gstride = 0;
   if (out_is_A && jsplit == 1) {
@@ -283,26 +283,20 @@ static fx_status run_halved(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const P
       FX_TRY(prof_begin(ctx, st, FX_K_VX_PENCIL_Z, 2.0 * vol, &slot));
       FX_TRY(pass.b(cb));
       FX_TRY(prof_end(ctx, st, slot));
-      // role 0: targets of block K; the first contribution to them is J = 0
+      // both roles: the first contribution to the targets of block K is J = 0,
+      // the last to those of block J is K = nblk - 1
       {
-        const int first = J == 0;
-        CtAcc<A> ca{acc, ld_acc, first, a.out, a.ld_out, out_c64 ? 1 : 0, 0, gstride};
-        const double accb = (double)kb * nr * ((first ? 0.0 : asz) + asz) * jsplit;
-        FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_INV, 2.0 * vol + accb, &slot));
-        FX_TRY(pass.c(cb, ca, 0));
+        const int first = J == 0, last = K == nblk - 1 && jsplit == 1;
+        CtAcc<A> ca{acc, ld_acc, first, a.out, a.ld_out, out_c64 ? 1 : 0, last, gstride};
+        // a diagonal batch's targets take both roles in one sum
+        const double in = (double)((tri ? 0 : jb) + (first ? 0 : kb)) * asz;
+        const double outb = (double)jb * (last ? osz : asz) + (tri ? 0.0 : kb * asz);
+        const double planes = tri ? 2.0 * npairs - jb : 2.0 * npairs;
+        FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_INV, 2.0 * planes * nr * sz + (in + outb) * nr * jsplit, &slot));
+        FX_TRY(pass.c(cb, ca, 2));
         FX_TRY(prof_end(ctx, st, slot));
       }
-      // role 1: targets of block J; their last contribution is K = nblk - 1
-      {
-        const int last = K == nblk - 1 && jsplit == 1;
-        CtAcc<A> ca{acc, ld_acc, 0, a.out, a.ld_out, out_c64 ? 1 : 0, last, gstride};
-        const double planes = tri ? (double)(npairs - jb) : (double)npairs;
-        const double accb = (double)jb * nr * (asz + (last ? osz : asz)) * jsplit;
-        FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_INV, 2.0 * planes * nr * sz + accb, &slot));
-        FX_TRY(pass.c(cb, ca, 1));
-        FX_TRY(prof_end(ctx, st, slot));
-      }
-      launches += 4;
+      launches += 3;
       solves += npairs;
     }
   }

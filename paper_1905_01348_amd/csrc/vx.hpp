@@ -139,7 +139,7 @@ template <typename T>
 fx_status ct_pass_a(fx_ctx* ctx, hipStream_t st, int n, const CtBatch<T>& b);
 template <typename T>
 fx_status ct_pass_b(fx_ctx* ctx, hipStream_t st, int n, const CtBatch<T>& b);
-// role 0: targets are the batch's k; role 1: targets are its j (halved apply)
+// role 0: targets are the batch's k; role 1: targets are its j (halved apply); 2: both
 template <typename T, typename A>
 fx_status ct_pass_c(fx_ctx* ctx, hipStream_t st, int n, const CtBatch<T>& b, const CtAcc<A>& c, int role);
 

@@ -37,7 +37,7 @@ __global__ void __launch_bounds__(NT, (PassAWaves<T, PIPE, NT>::value)) k_pass_a
                                                                   const cpx<T>* __restrict__ phi, int64_t ld_phi,
                                                                   cpx<T>* __restrict__ work, int j0, int nj, int k0,
                                                                   int tri, int nitems, const cpx<T>* __restrict__ twg,
-                                                                  int zsplit, TrajSegs segs) {
+                                                                  int split, TrajSegs segs) {
   constexpr int NXY = N * N, SX = N + 1, EPT = CeilDiv<NXY, NT>::value;
   constexpr size_t NR = (size_t)NXY * N;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -46,8 +46,8 @@ __global__ void __launch_bounds__(NT, (PassAWaves<T, PIPE, NT>::value)) k_pass_a
   const int tid = threadIdx.x;
   for (int i = tid; i < N; i += NT) tw[i] = twg[i];
   cpx<T> va[EPT], vb[EPT];
-  const ItemMap im = item_map(N, nitems / N, zsplit & 1, gridDim.x, blockIdx.x);
-  const bool kBlocked = (zsplit >> 2) & 1;
+  const ItemMap im = item_map(N, nitems / N, split & 3, gridDim.x, blockIdx.x);
+  const bool kBlocked = (split >> 2) & 1;
   // VEC with whole pairs of values per thread: each thread takes two
   // consecutive plane values per load (16-byte loads, half the load
   // instructions); value i of the thread is plane element elem(i)
@@ -315,13 +315,17 @@ __global__ void __launch_bounds__(NT) k_pass_b_pt(cpx<T>* __restrict__ work, con
 }
 
 // ---- pass C: inverse FFT y and x, times psi_j, j-sum in registers --------------
-// One item = (target tt of the batch, plane z).  Role 0 (CONJ false): the
-// targets are the batch's k (output column t0 + kk) and the sum runs over its
-// j in ascending order, adding psi_{m0+jj} * v_{jk}.  Role 1 (CONJ true, the
-// second half of a halved apply): the targets are the batch's j and the sum
-// runs over its k in ascending order, adding psi_{m0+kk} * conj(v_{jk}),
-// which is v_{kj} since the kernel is real and even.  On a diagonal batch
-// (tri) role 0 takes jj <= kk and role 1 kk > jj.
+// One item = (target tt of the batch, plane z).  Role 0: the targets are the
+// batch's k (output column k0 + kk) and the sum runs over its j in ascending
+// order, adding psi_{j0+jj} * v_{jk}.  Role 1 (the second half of a halved
+// apply): the targets are the batch's j and the sum runs over its k in
+// ascending order, adding psi_{k0+kk} * conj(v_{jk}), which is v_{kj} since the
+// kernel is real and even.  On a diagonal batch (tri) role 0 takes jj <= kk and
+// role 1 kk > jj.  Role 2 is both in one launch: a diagonal batch's targets take
+// their role 0 terms, then their role 1 terms, in one running sum (two launches
+// of up to N and up to N - 1 terms each become one of N: 24^3, 16 orbitals in
+// FP64, C passes 70 -> 38 us of an apply of 112 -> 80); on another batch the targets of the two roles are
+// items side by side.
 // FORM 0: the plain form; 1 (STG): the next work plane (this item's next
 // term, or the next item's first)
 // is copied into a second LDS buffer while the current one is transformed, so
@@ -344,13 +348,14 @@ struct PassCDouble {
                                                    (FORM == 0 && kBytes <= 40 * 1024));
 };
 
-template <typename T, typename A, int N, bool CONJ, int NT, bool NTS, int FORM>
+template <typename T, typename A, int N, bool HALVED, int NT, bool NTS, int FORM>
 __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mult, int64_t ld_mult,
                                                                   const cpx<T>* __restrict__ work, int nj, int nk,
-                                                                  int tri, int m0, int t0, int nitems, cpx<A>* acc,
-                                                                  int64_t ld_acc, int first, void* out, int64_t ld_out,
-                                                                  int out_c64, int last, const cpx<T>* __restrict__ twg,
-                                                                  int zsplit, TrajSegs segs, int jsplit, int64_t gstride) {
+                                                                  int tri, int role, int j0, int k0, int nitems,
+                                                                  cpx<A>* acc, int64_t ld_acc, int first_in, void* out,
+                                                                  int64_t ld_out, int out_c64, int last_in,
+                                                                  const cpx<T>* __restrict__ twg, int split,
+                                                                  TrajSegs segs, int jsplit, int64_t gstride) {
   constexpr int NXY = N * N, SX = N + 1, EPT = CeilDiv<NXY, NT>::value;
   constexpr size_t NR = (size_t)NXY * N;
   constexpr bool STG = FORM == 1, WX = FORM == 2;
@@ -364,17 +369,17 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
   for (int i = tid; i < N; i += NT) tw[i] = twg[i];
   __syncthreads();
   // units: (target tt, sum group g) as tt * jsplit + g
-  const ItemMap im = item_map(N, nitems / N, zsplit, gridDim.x, blockIdx.x);
+  const ItemMap im = item_map(N, nitems / N, split, gridDim.x, blockIdx.x);
   // terms l = lo, lo + jsplit, ... < hi of target tt in group g: the terms
   // whose orbital m0 + l is g modulo jsplit, in ascending order
-  auto range = [&](int tt_, int g_, int* lo_, int* hi_) __attribute__((always_inline)) {
-    int lo = CONJ ? (tri ? tt_ + 1 : 0) : 0;
-    *hi_ = CONJ ? nk : (tri ? tt_ + 1 : nj);
-    const int r = (m0 + lo) % jsplit;
+  auto range = [&](int tt_, int g_, bool cj_, int* lo_, int* hi_) __attribute__((always_inline)) {
+    int lo = cj_ ? (tri ? tt_ + 1 : 0) : 0;
+    *hi_ = cj_ ? nk : (tri ? tt_ + 1 : nj);
+    const int r = ((cj_ ? k0 : j0) + lo) % jsplit;
     *lo_ = lo + (g_ >= r ? g_ - r : g_ - r + jsplit);
   };
-  auto plane_ptr = [&](int tt_, int l_, int z_) __attribute__((always_inline)) {
-    const int pl = CONJ ? plane_of(tt_, l_, nj, tri) : plane_of(l_, tt_, nj, tri);
+  auto plane_ptr = [&](int tt_, int l_, bool cj_, int z_) __attribute__((always_inline)) {
+    const int pl = cj_ ? plane_of(tt_, l_, nj, tri) : plane_of(l_, tt_, nj, tri);
     return work + (size_t)pl * NR + (size_t)z_ * NXY;
   };
   bool staged = false;  // STG: stg holds (or is receiving) this item's first term
@@ -407,8 +412,16 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
   for (int li = im.first; li < im.total; li += im.step) {
     int u, z;
     im.at(li, &u, &z);
-    const int tt = u / jsplit, g = u - tt * jsplit;
-    const int t = t0 + tt;
+    int tt = u / jsplit;
+    const int g = u - tt * jsplit;
+    // the roles of this item's target: cj0 .. cj1
+    bool cj0 = HALVED && role == 1, cj1 = HALVED && role != 0;
+    if (HALVED && role == 2 && !tri) {
+      cj0 = cj1 = tt >= nk;
+      if (cj0) tt -= nk;
+    }
+    const int t = (cj1 ? j0 : k0) + tt;  // (on a diagonal batch the two are the same)
+    const int first = first_in && !cj0, last = last_in && (cj1 || !HALVED || role == 0);
     cpx<A>* accg = acc + g * gstride;  // this group's partial sums
     if constexpr (kRegX) {
       cpx<A> a[LX::IT][LX::R];
@@ -420,58 +433,61 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
           a[it][m] = cpx<A>{0, 0};
           if (!first && LX::owns(tid, it)) a[it][m] = accg[t * ld_acc + (size_t)z * NXY + rpos(it, m)];
         }
-      int lo, hi;
-      range(tt, g, &lo, &hi);
-      for (int l = lo; l < hi; l += jsplit) {
-        const cpx<T>* pm = seg_psi<T>(segs, mult, t) + (int64_t)(m0 + l) * ld_mult + (size_t)z * NXY;
-        constexpr int R0 = Plan2<N>::R0, R1 = Plan2<N>::R1;
-        cpx<T>* sl = s + (kDbl ? par * N * SX : 0);
-        // (16-byte paired loads here measured slower: 3.08 against 2.76 ms
-        // per launch at 96^3, with a quarter of the threads idle in this stage)
-        ct_stage_io<R1, false, T, N, R1, N, SX, 1, NT, true, false, N, 1, NTS>(sl, plane_ptr(tt, l, z), nullptr, tw,
-                                                                              tid);
-        __syncthreads();
-        if constexpr (!kLateOrbital) {
+      for (int cj = cj0; cj <= (int)cj1; ++cj) {
+        const A sgn = cj ? (A)-1 : (A)1;
+        int lo, hi;
+        range(tt, g, cj, &lo, &hi);
+        for (int l = lo; l < hi; l += jsplit) {
+          const cpx<T>* pm = seg_psi<T>(segs, mult, t) + (int64_t)((cj ? k0 : j0) + l) * ld_mult + (size_t)z * NXY;
+          constexpr int R0 = Plan2<N>::R0, R1 = Plan2<N>::R1;
+          cpx<T>* sl = s + (kDbl ? par * N * SX : 0);
+          // (16-byte paired loads here measured slower: 3.08 against 2.76 ms
+          // per launch at 96^3, with a quarter of the threads idle in this stage)
+          ct_stage_io<R1, false, T, N, R1, N, SX, 1, NT, true, false, N, 1, NTS>(sl, plane_ptr(tt, l, cj, z), nullptr, tw,
+                                                                                tid);
+          __syncthreads();
+          if constexpr (!kLateOrbital) {
+#pragma unroll
+            for (int it = 0; it < LX::IT; ++it)
+#pragma unroll
+              for (int m = 0; m < LX::R; ++m)
+                if (LX::owns(tid, it)) vp[it][m] = pm[rpos(it, m)];
+          }
+          ct_stage<R0, false, T, N, N, N, SX, 1, NT>(sl, tw, tid);
+          __syncthreads();
+          cpx<T> x[LX::IT][LX::R];
+          if constexpr (WX) {
+            LX::template inv_x_wave<SX>(sl, tw, tid, x[0]);
+          } else {
+            ct_stage<R1, false, T, N, R1, N, 1, SX, NT>(sl, tw, tid);
+            __syncthreads();
+            LX::template inv_from_lds<SX>(sl, tw, tid, x);
+          }
+          // FP64 (wave-level form): the orbital values once the transform's
+          // registers are free
+          if constexpr (kLateOrbital) {
+#pragma unroll
+            for (int it = 0; it < LX::IT; ++it)
+#pragma unroll
+              for (int m = 0; m < LX::R; ++m)
+                if (LX::owns(tid, it)) vp[it][m] = pm[rpos(it, m)];
+          }
 #pragma unroll
           for (int it = 0; it < LX::IT; ++it)
 #pragma unroll
             for (int m = 0; m < LX::R; ++m)
-              if (LX::owns(tid, it)) vp[it][m] = pm[rpos(it, m)];
+              if (LX::owns(tid, it)) {
+                const cpx<A> va{(A)x[it][m].x, HALVED ? sgn * (A)x[it][m].y : (A)x[it][m].y};
+                a[it][m] = cfma(a[it][m], cpx<A>{(A)vp[it][m].x, (A)vp[it][m].y}, va);
+              }
+          // the last stage's reads before the next term's writes of the plane:
+          // with two planes, the next term writes the other one, and the term
+          // after it waits at that term's barriers
+          if constexpr (kDbl)
+            par ^= 1;
+          else
+            __syncthreads();
         }
-        ct_stage<R0, false, T, N, N, N, SX, 1, NT>(sl, tw, tid);
-        __syncthreads();
-        cpx<T> x[LX::IT][LX::R];
-        if constexpr (WX) {
-          LX::template inv_x_wave<SX>(sl, tw, tid, x[0]);
-        } else {
-          ct_stage<R1, false, T, N, R1, N, 1, SX, NT>(sl, tw, tid);
-          __syncthreads();
-          LX::template inv_from_lds<SX>(sl, tw, tid, x);
-        }
-        // FP64 (wave-level form): the orbital values once the transform's
-        // registers are free
-        if constexpr (kLateOrbital) {
-#pragma unroll
-          for (int it = 0; it < LX::IT; ++it)
-#pragma unroll
-            for (int m = 0; m < LX::R; ++m)
-              if (LX::owns(tid, it)) vp[it][m] = pm[rpos(it, m)];
-        }
-#pragma unroll
-        for (int it = 0; it < LX::IT; ++it)
-#pragma unroll
-          for (int m = 0; m < LX::R; ++m)
-            if (LX::owns(tid, it)) {
-              const cpx<A> va{(A)x[it][m].x, CONJ ? -(A)x[it][m].y : (A)x[it][m].y};
-              a[it][m] = cfma(a[it][m], cpx<A>{(A)vp[it][m].x, (A)vp[it][m].y}, va);
-            }
-        // the last stage's reads before the next term's writes of the plane:
-        // with two planes, the next term writes the other one, and the term
-        // after it waits at that term's barriers
-        if constexpr (kDbl)
-          par ^= 1;
-        else
-          __syncthreads();
       }
 #pragma unroll
       for (int it = 0; it < LX::IT; ++it)
@@ -499,99 +515,103 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
       if (!first && (NXY % NT == 0 || e < NXY)) a[i] = accg[t * ld_acc + (size_t)z * NXY + e];
     }
     constexpr int R0 = Plan2<N>::R0, R1 = Plan2<N>::R1;
-    int lo, hi;
-    range(tt, g, &lo, &hi);
-    for (int l = lo; l < hi; l += jsplit) {
-      // (multi-trajectory launches are never halved: role 0, target t's own orbitals)
-      const cpx<T>* pm = seg_psi<T>(segs, mult, t) + (int64_t)(m0 + l) * ld_mult + (size_t)z * NXY;
-      cpx<T>* sl = s + (kDbl ? par * N * SX : 0);
-      if (STG) {
-        if (!staged) plane_to_lds<T, N, NT, NTS>(plane_ptr(tt, l, z), stg, tid);
-        __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the copy has landed
-        __syncthreads();                // ... and every other wave's
-        // first inverse y stage from the staged plane
-        ct_stage_io<R1, false, T, N, R1, N, SX, 1, NT, true, false, N, 1, false>(sl, stg, nullptr, tw, tid);
-        __syncthreads();  // stg is free again
-        // orbital plane first: waiting for it must not wait for the copy below
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-          const int e = tid + i * NT;
-          if (NXY % NT == 0 || e < NXY) vp[i] = pm[e];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // start copying the next term: this item's, else the next item's first
-        staged = false;
-        if (l + jsplit < hi) {
-          plane_to_lds<T, N, NT, NTS>(plane_ptr(tt, l + jsplit, z), stg, tid);
-          staged = true;
-        } else if (li + im.step < im.total) {
-          int u2, z2, lo2, hi2;
-          im.at(li + im.step, &u2, &z2);
-          const int tt2 = u2 / jsplit;
-          range(tt2, u2 - tt2 * jsplit, &lo2, &hi2);
-          if (lo2 < hi2) {
-            plane_to_lds<T, N, NT, NTS>(plane_ptr(tt2, lo2, z2), stg, tid);
-            staged = true;
-          }
-        }
-      } else {
-        // first inverse y stage straight from the work plane
-        ct_stage_io<R1, false, T, N, R1, N, SX, 1, NT, true, false, N, 1, NTS>(sl, plane_ptr(tt, l, z), nullptr, tw,
-                                                                              tid);
-        __syncthreads();
-        if (!kLateOrbital) {
+    for (int cj = cj0; cj <= (int)cj1; ++cj) {
+      const A sgn = cj ? (A)-1 : (A)1;
+      int lo, hi;
+      range(tt, g, cj, &lo, &hi);
+      for (int l = lo; l < hi; l += jsplit) {
+        // (multi-trajectory launches are never halved: role 0, target t's own orbitals)
+        const cpx<T>* pm = seg_psi<T>(segs, mult, t) + (int64_t)((cj ? k0 : j0) + l) * ld_mult + (size_t)z * NXY;
+        cpx<T>* sl = s + (kDbl ? par * N * SX : 0);
+        if (STG) {
+          if (!staged) plane_to_lds<T, N, NT, NTS>(plane_ptr(tt, l, cj, z), stg, tid);
+          __builtin_amdgcn_s_waitcnt(0);  // this wave's part of the copy has landed
+          __syncthreads();                // ... and every other wave's
+          // first inverse y stage from the staged plane
+          ct_stage_io<R1, false, T, N, R1, N, SX, 1, NT, true, false, N, 1, false>(sl, stg, nullptr, tw, tid);
+          __syncthreads();  // stg is free again
+          // orbital plane first: waiting for it must not wait for the copy below
 #pragma unroll
           for (int i = 0; i < EPT; ++i) {
             const int e = tid + i * NT;
             if (NXY % NT == 0 || e < NXY) vp[i] = pm[e];
           }
-        }
-      }
-      ct_stage<R0, false, T, N, N, N, SX, 1, NT>(sl, tw, tid);
-      __syncthreads();
-      // inverse x: its two stages (ct_fft's), the orbital plane loaded between
-      // them in FP64
-      ct_stage<R1, false, T, N, R1, N, 1, SX, NT>(sl, tw, tid);
-      __syncthreads();
-      if (!STG && kLateOrbital) {
+          __builtin_amdgcn_sched_barrier(0);
+          // start copying the next term: this item's, else the next item's first
+          // (launches of one role: role 2 has no staged form)
+          staged = false;
+          if (l + jsplit < hi) {
+            plane_to_lds<T, N, NT, NTS>(plane_ptr(tt, l + jsplit, cj, z), stg, tid);
+            staged = true;
+          } else if (li + im.step < im.total) {
+            int u2, z2, lo2, hi2;
+            im.at(li + im.step, &u2, &z2);
+            const int tt2 = u2 / jsplit;
+            range(tt2, u2 - tt2 * jsplit, cj, &lo2, &hi2);
+            if (lo2 < hi2) {
+              plane_to_lds<T, N, NT, NTS>(plane_ptr(tt2, lo2, cj, z2), stg, tid);
+              staged = true;
+            }
+          }
+        } else {
+          // first inverse y stage straight from the work plane
+          ct_stage_io<R1, false, T, N, R1, N, SX, 1, NT, true, false, N, 1, NTS>(sl, plane_ptr(tt, l, cj, z), nullptr, tw,
+                                                                                tid);
+          __syncthreads();
+          if (!kLateOrbital) {
 #pragma unroll
-        for (int i = 0; i < kEarly; ++i) {
-          const int e = tid + i * NT;
-          if (NXY % NT == 0 || e < NXY) vp[i] = pm[e];
-        }
-      }
-      ct_stage<R0, false, T, N, N, N, 1, SX, NT>(sl, tw, tid);
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        const int e = tid + i * NT;
-        // FP64: the second half of the orbital values, once the last stage's
-        // registers are free
-        if (!STG && kLateOrbital && i == kEarly) {
-#pragma unroll
-          for (int i2 = kEarly; i2 < EPT; ++i2) {
-            const int e2 = tid + i2 * NT;
-            if (NXY % NT == 0 || e2 < NXY) vp[i2] = pm[e2];
+            for (int i = 0; i < EPT; ++i) {
+              const int e = tid + i * NT;
+              if (NXY % NT == 0 || e < NXY) vp[i] = pm[e];
+            }
           }
         }
-        if (NXY % NT == 0 || e < NXY) {
-          const cpx<T> v = sl[(e / N) * SX + e % N];
-          const cpx<A> va{(A)v.x, CONJ ? -(A)v.y : (A)v.y};
-          // FP32 transforms: four FMAs per term; FP64: product then sum (the
-          // FMA chain costs the FP64 kernel registers it does not have)
-          if constexpr (sizeof(T) == 4)
-            a[i] = cfma(a[i], cpx<A>{(A)vp[i].x, (A)vp[i].y}, va);
-          else
-            a[i] = cadd(a[i], cmul(cpx<A>{(A)vp[i].x, (A)vp[i].y}, va));
-        }
-      }
-      // (STG: the barrier at the top of the next term orders these reads
-      // before the next writes of s; kDbl: the next term writes the other
-      // plane)
-      if constexpr (kDbl)
-        par ^= 1;
-      else if (!STG)
+        ct_stage<R0, false, T, N, N, N, SX, 1, NT>(sl, tw, tid);
         __syncthreads();
+        // inverse x: its two stages (ct_fft's), the orbital plane loaded between
+        // them in FP64
+        ct_stage<R1, false, T, N, R1, N, 1, SX, NT>(sl, tw, tid);
+        __syncthreads();
+        if (!STG && kLateOrbital) {
+#pragma unroll
+          for (int i = 0; i < kEarly; ++i) {
+            const int e = tid + i * NT;
+            if (NXY % NT == 0 || e < NXY) vp[i] = pm[e];
+          }
+        }
+        ct_stage<R0, false, T, N, N, N, 1, SX, NT>(sl, tw, tid);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+          const int e = tid + i * NT;
+          // FP64: the second half of the orbital values, once the last stage's
+          // registers are free
+          if (!STG && kLateOrbital && i == kEarly) {
+#pragma unroll
+            for (int i2 = kEarly; i2 < EPT; ++i2) {
+              const int e2 = tid + i2 * NT;
+              if (NXY % NT == 0 || e2 < NXY) vp[i2] = pm[e2];
+            }
+          }
+          if (NXY % NT == 0 || e < NXY) {
+            const cpx<T> v = sl[(e / N) * SX + e % N];
+            const cpx<A> va{(A)v.x, HALVED ? sgn * (A)v.y : (A)v.y};
+            // FP32 transforms: four FMAs per term; FP64: product then sum (the
+            // FMA chain costs the FP64 kernel registers it does not have)
+            if constexpr (sizeof(T) == 4)
+              a[i] = cfma(a[i], cpx<A>{(A)vp[i].x, (A)vp[i].y}, va);
+            else
+              a[i] = cadd(a[i], cmul(cpx<A>{(A)vp[i].x, (A)vp[i].y}, va));
+          }
+        }
+        // (STG: the barrier at the top of the next term orders these reads
+        // before the next writes of s; kDbl: the next term writes the other
+        // plane)
+        if constexpr (kDbl)
+          par ^= 1;
+        else if (!STG)
+          __syncthreads();
+      }
     }
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
@@ -655,7 +675,7 @@ static bool pass_a_vec_ok(const CtBatch<T>& b) {
 template <typename T, int N, int NT, bool WX = false>
 static fx_status pass_a_shape(fx_ctx* ctx, hipStream_t st, const CtBatch<T>& b) {
   const size_t lds = ((size_t)N * (N + 1) + N) * sizeof(cpx<T>);
-  // the blocked pair order (bit 2 of zsplit) for the FP32 form with
+  // the blocked pair order (bit 2 of the split argument) for the FP32 form with
   // coalesced loads only: the wave-level forms measured slower with it
   // (FP32 at 72^3: 0.705 -> 0.800 ms per launch; FP64 at 96^3: 2.53 -> 2.66)
   // the prefetching form exists for FP32 only (FP64 has no registers to spare)
@@ -671,7 +691,8 @@ static fx_status pass_a_shape(fx_ctx* ctx, hipStream_t st, const CtBatch<T>& b) 
   int grid = 0;
   FX_TRY(ct_prepare(ctx, kern, NT, lds, items, true, &grid));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, b.psi, b.ld_psi, b.phi, b.ld_phi, b.work, b.j0, b.nj, b.k0,
-                     b.tri, items, b.tw, b.zsplit & (sizeof(T) == 4 && !WX ? 5 : 1), b.segs);
+                     b.tri, items, b.tw,
+                     item_split(N, items / N, b.zsplit & 1, grid) | (sizeof(T) == 4 && !WX ? b.zsplit & 4 : 0), b.segs);
   FX_LAUNCH_CHECK();
   return FX_OK;
 }
@@ -755,19 +776,24 @@ template <typename T, typename A, int N, int NT, int FORM>
 static fx_status pass_c_shape(fx_ctx* ctx, hipStream_t st, const CtBatch<T>& b, const CtAcc<A>& c, int role) {
   const size_t lds = PassCDouble<T, N, NT, FORM>::value ? PassCDouble<T, N, NT, FORM>::kBytes
                                                          : pass_c_lds<T, N>(FORM == 1);
-  const int items = (role ? b.nj : b.nk) * b.jsplit * N;
+  if (FORM == 1 && role == 2) {  // the staged form runs one role per launch
+    CtAcc<A> c0 = c, c1 = c;
+    c0.last = 0;
+    c1.first = 0;
+    FX_TRY((pass_c_shape<T, A, N, NT, FORM>(ctx, st, b, c0, 0)));
+    return pass_c_shape<T, A, N, NT, FORM>(ctx, st, b, c1, 1);
+  }
+  const int targets = role == 0 ? b.nk : role == 1 ? b.nj : b.tri ? b.nk : b.nk + b.nj;
+  const int items = targets * b.jsplit * N;
   auto kern = role ? (b.nts ? k_pass_c_ct<T, A, N, true, NT, true, FORM> : k_pass_c_ct<T, A, N, true, NT, false, FORM>)
                    : (b.nts ? k_pass_c_ct<T, A, N, false, NT, true, FORM> : k_pass_c_ct<T, A, N, false, NT, false, FORM>);
   int grid = 0;
   FX_TRY(ct_prepare(ctx, kern, NT, lds, items, true, &grid));
-  if (role)
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, b.phi, b.ld_phi, (const cpx<T>*)b.work, b.nj, b.nk, b.tri,
-                       b.k0, b.j0, items, c.acc, c.ld_acc, c.first, c.out, c.ld_out, c.out_c64, c.last, b.tw, (b.zsplit >> 1) & 1,
-                       TrajSegs{}, b.jsplit, c.gstride);
-  else
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, b.psi, b.ld_psi, (const cpx<T>*)b.work, b.nj, b.nk, b.tri,
-                       b.j0, b.k0, items, c.acc, c.ld_acc, c.first, c.out, c.ld_out, c.out_c64, c.last, b.tw, (b.zsplit >> 1) & 1,
-                       b.segs, b.jsplit, c.gstride);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, role ? b.phi : b.psi, role ? b.ld_phi : b.ld_psi,
+                     (const cpx<T>*)b.work, b.nj, b.nk, b.tri, role, b.j0, b.k0, items, c.acc, c.ld_acc, c.first,
+                     c.out, c.ld_out, c.out_c64, c.last, b.tw,
+                     item_split(N, items / N, (b.zsplit >> 1) & 1, grid), role ? TrajSegs{} : b.segs, b.jsplit,
+                     c.gstride);
   FX_LAUNCH_CHECK();
   return FX_OK;
 }

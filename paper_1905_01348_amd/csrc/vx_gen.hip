@@ -29,7 +29,7 @@ __global__ void __launch_bounds__(kGenAThreads, 4) k_gen_a(const cpx<T>* __restr
                                                           const cpx<T>* __restrict__ phi, int64_t ld_phi,
                                                           cpx<T>* __restrict__ work, int j0, int nj, int k0, int tri,
                                                           int npairs, PassGeom g, const cpx<T>* __restrict__ twx_g,
-                                                          const cpx<T>* __restrict__ twy_g, int zsplit, TrajSegs segs) {
+                                                          const cpx<T>* __restrict__ twy_g, int split, TrajSegs segs) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cpx<T>* s = reinterpret_cast<cpx<T>*>(smem_raw);
   cpx<T>* twx = s + plane_lds_elems(g);
@@ -39,11 +39,11 @@ __global__ void __launch_bounds__(kGenAThreads, 4) k_gen_a(const cpx<T>* __restr
   for (int i = tid; i < g.ny; i += nthr) twy[i] = twy_g[i];
   const int nxy = g.nx * g.ny;
   const size_t nr = (size_t)nxy * g.nz;
-  const ItemMap im = item_map(g.nz, npairs, zsplit & 1, gridDim.x, blockIdx.x);
+  const ItemMap im = item_map(g.nz, npairs, split & 3, gridDim.x, blockIdx.x);
   for (int li = im.first; li < im.total; li += im.step) {
     int p, z;
     im.at(li, &p, &z);
-    p = unit_plane(p, npairs, nj, tri, (zsplit >> 2) & 1);
+    p = unit_plane(p, npairs, nj, tri, (split >> 2) & 1);
     int jj, kk;
     pair_of(p, nj, tri, &jj, &kk);
     const cpx<T>* a = seg_psi<T>(segs, psi, k0 + kk) + (int64_t)(j0 + jj) * ld_psi + (size_t)z * nxy;
@@ -88,9 +88,9 @@ __global__ void __launch_bounds__(kPencilThreads) k_gen_b(cpx<T>* __restrict__ w
 
 // ---- pass C ------------------------------------------------------------------
 // One item = (target tt of the batch, sum group gr, plane z).  Role 0: targets
-// t0 + kk, terms psi_{m0+jj} v_{jk}; role 1 (conj): targets t0 + jj, terms
-// psi_{m0+kk} conj(v_{jk}); on a diagonal batch role 0 takes jj <= kk, role 1
-// kk > jj (see k_pass_c_ct).  R: radix of the last inverse x stage, IT its
+// k0 + kk, terms psi_{j0+jj} v_{jk}; role 1: targets j0 + jj, terms psi_{k0+kk}
+// conj(v_{jk}); on a diagonal batch role 0 takes jj <= kk, role 1 kk > jj; role
+// 2: both (see k_pass_c_ct).  R: radix of the last inverse x stage, IT its
 // butterflies per thread; their R IT sums per thread stay in registers over
 // the batch's terms.  Two LDS planes, alternating by term, where dbl is set
 // (they then take at most 40 KB): a term's first stage need not wait for the
@@ -100,9 +100,9 @@ constexpr int kGenCThreads = 768;  // launch bound: 170 registers a thread
 template <typename T, typename A, int R, int IT, int RMAX>
 __global__ void __launch_bounds__(kGenCThreads, (sizeof(T) == 4 && R * IT <= 8 ? 4 : 3))
     k_gen_c(const cpx<T>* __restrict__ mult, int64_t ld_mult, const cpx<T>* __restrict__ work, int nj, int nk, int tri,
-            int conj, int m0, int t0, int units, cpx<A>* acc, int64_t ld_acc, int first, void* out, int64_t ld_out,
-            int out_c64, int last, PassGeom g, const cpx<T>* __restrict__ twx_g, const cpx<T>* __restrict__ twy_g,
-            int zsplit, TrajSegs segs, int jsplit, int64_t gstride, int dbl) {
+            int role, int j0, int k0, int units, cpx<A>* acc, int64_t ld_acc, int first_in, void* out, int64_t ld_out,
+            int out_c64, int last_in, PassGeom g, const cpx<T>* __restrict__ twx_g, const cpx<T>* __restrict__ twy_g,
+            int split, TrajSegs segs, int jsplit, int64_t gstride, int dbl) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cpx<T>* s = reinterpret_cast<cpx<T>*>(smem_raw);
   const int plane = plane_lds_elems(g);
@@ -118,18 +118,24 @@ __global__ void __launch_bounds__(kGenCThreads, (sizeof(T) == 4 && R * IT <= 8 ?
   // the orbital values once the transform's registers are free: FP32 with sums
   // of up to 8 values then keeps four waves per SIMD (64^3: 1200 -> 850 us)
   constexpr bool kLate = sizeof(T) == 8 || R * IT > 4;
-  const A sgn = conj ? (A)-1 : (A)1;
   int pos[IT];
 #pragma unroll
   for (int it = 0; it < IT; ++it) pos[it] = row_last_pos(g, tid + it * nthr);
   const auto owns = [&](int it) __attribute__((always_inline)) { return tid + it * nthr < total; };
-  const ItemMap im = item_map(g.nz, units, zsplit, gridDim.x, blockIdx.x);
+  const ItemMap im = item_map(g.nz, units, split, gridDim.x, blockIdx.x);
   int par = 0;
   for (int li = im.first; li < im.total; li += im.step) {
     int u, z;
     im.at(li, &u, &z);
-    const int tt = u / jsplit, gr = u - tt * jsplit;
-    const int t = t0 + tt;
+    int tt = u / jsplit;
+    const int gr = u - tt * jsplit;
+    bool cj0 = role == 1, cj1 = role != 0;
+    if (role == 2 && !tri) {
+      cj0 = cj1 = tt >= nk;
+      if (cj0) tt -= nk;
+    }
+    const int t = (cj1 ? j0 : k0) + tt;
+    const int first = first_in && !cj0, last = last_in && (cj1 || role == 0);
     cpx<A>* accg = acc + gr * gstride + t * ld_acc + (size_t)z * nxy;
     cpx<A> a[IT][R];
 #pragma unroll
@@ -139,43 +145,47 @@ __global__ void __launch_bounds__(kGenCThreads, (sizeof(T) == 4 && R * IT <= 8 ?
         a[it][m] = cpx<A>{0, 0};
         if (!first && owns(it)) a[it][m] = accg[pos[it] + m * span];
       }
-    // terms lo, lo + jsplit, ... < hi: those whose orbital m0 + l is gr mod jsplit
-    int lo = conj ? (tri ? tt + 1 : 0) : 0;
-    const int hi = conj ? nk : (tri ? tt + 1 : nj);
-    const int r = (m0 + lo) % jsplit;
-    lo += gr >= r ? gr - r : gr - r + jsplit;
-    for (int l = lo; l < hi; l += jsplit) {
-      const cpx<T>* pm = seg_psi<T>(segs, mult, t) + (int64_t)(m0 + l) * ld_mult + (size_t)z * nxy;
-      const int pl = conj ? plane_of(tt, l, nj, tri) : plane_of(l, tt, nj, tri);
-      cpx<T>* sl = s + (dbl && par ? plane : 0);
-      cpx<T> vp[IT][R];
-      const auto orbital = [&]() __attribute__((always_inline)) {
+    for (int cj = cj0; cj <= (int)cj1; ++cj) {
+      const A sgn = cj ? (A)-1 : (A)1;
+      // terms lo, lo + jsplit, ... < hi: those whose orbital m0 + l is gr mod jsplit
+      const int m0 = cj ? k0 : j0;
+      int lo = cj ? (tri ? tt + 1 : 0) : 0;
+      const int hi = cj ? nk : (tri ? tt + 1 : nj);
+      const int r = (m0 + lo) % jsplit;
+      lo += gr >= r ? gr - r : gr - r + jsplit;
+      for (int l = lo; l < hi; l += jsplit) {
+        const cpx<T>* pm = seg_psi<T>(segs, mult, t) + (int64_t)(m0 + l) * ld_mult + (size_t)z * nxy;
+        const int pl = cj ? plane_of(tt, l, nj, tri) : plane_of(l, tt, nj, tri);
+        cpx<T>* sl = s + (dbl && par ? plane : 0);
+        cpx<T> vp[IT][R];
+        const auto orbital = [&]() __attribute__((always_inline)) {
+#pragma unroll
+          for (int it = 0; it < IT; ++it)
+#pragma unroll
+            for (int m = 0; m < R; ++m)
+              if (owns(it)) vp[it][m] = pm[pos[it] + m * span];
+        };
+        pass_c_fft<T, RMAX>(work + (size_t)pl * nr + (size_t)z * nxy, sl, twx, twy, g, tid, nthr, DeviceSync{},
+                      [&]() __attribute__((always_inline)) {
+                        if (!kLate) orbital();
+                      });
+        cpx<T> x[IT][R];
+#pragma unroll
+        for (int it = 0; it < IT; ++it)
+          if (owns(it)) row_last_stage<R, T>(sl, twx, g, tid + it * nthr, x[it]);
+        if (kLate) orbital();
 #pragma unroll
         for (int it = 0; it < IT; ++it)
 #pragma unroll
           for (int m = 0; m < R; ++m)
-            if (owns(it)) vp[it][m] = pm[pos[it] + m * span];
-      };
-      pass_c_fft<T, RMAX>(work + (size_t)pl * nr + (size_t)z * nxy, sl, twx, twy, g, tid, nthr, DeviceSync{},
-                    [&]() __attribute__((always_inline)) {
-                      if (!kLate) orbital();
-                    });
-      cpx<T> x[IT][R];
-#pragma unroll
-      for (int it = 0; it < IT; ++it)
-        if (owns(it)) row_last_stage<R, T>(sl, twx, g, tid + it * nthr, x[it]);
-      if (kLate) orbital();
-#pragma unroll
-      for (int it = 0; it < IT; ++it)
-#pragma unroll
-        for (int m = 0; m < R; ++m)
-          if (owns(it))
-            a[it][m] = cfma(a[it][m], cpx<A>{(A)vp[it][m].x, (A)vp[it][m].y},
-                            cpx<A>{(A)x[it][m].x, sgn * (A)x[it][m].y});
-      if (dbl)
-        par ^= 1;
-      else
-        __syncthreads();
+            if (owns(it))
+              a[it][m] = cfma(a[it][m], cpx<A>{(A)vp[it][m].x, (A)vp[it][m].y},
+                              cpx<A>{(A)x[it][m].x, sgn * (A)x[it][m].y});
+        if (dbl)
+          par ^= 1;
+        else
+          __syncthreads();
+      }
     }
 #pragma unroll
     for (int it = 0; it < IT; ++it)
@@ -247,7 +257,8 @@ fx_status gen_pass_a(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridT
   int grid = 0;
   FX_TRY(gen_grid(ctx, kern, nthr, lds, (int64_t)b.npairs * g.nz, &grid));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(nthr), lds, st, b.psi, b.ld_psi, b.phi, b.ld_phi, b.work, b.j0, b.nj, b.k0,
-                     b.tri, b.npairs, g, (const cpx<T>*)tb->tw[0], (const cpx<T>*)tb->tw[1], b.zsplit & 5, b.segs);
+                     b.tri, b.npairs, g, (const cpx<T>*)tb->tw[0], (const cpx<T>*)tb->tw[1],
+                     item_split(g.nz, b.npairs, b.zsplit & 1, grid) | (b.zsplit & 4), b.segs);
   FX_LAUNCH_CHECK();
   return FX_OK;
 }
@@ -294,15 +305,15 @@ static fx_status gen_c_launch(fx_ctx* ctx, hipStream_t st, const PassGeom& g, co
   const size_t lds = (dbl ? 2 : 1) * plane + tw;
   const int total = g.ny * g.ax.st[0].nb;
   const int nthr = round64((total + IT - 1) / IT);
-  const int units = (role ? b.nj : b.nk) * b.jsplit;
+  const int units = (role == 0 ? b.nk : role == 1 ? b.nj : b.tri ? b.nk : b.nk + b.nj) * b.jsplit;
   const auto kern = k_gen_c<T, A, R, IT, RMAX>;
   int grid = 0;
   FX_TRY(gen_grid(ctx, kern, nthr, lds, (int64_t)units * g.nz, &grid));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(nthr), lds, st, role ? b.phi : b.psi, role ? b.ld_phi : b.ld_psi,
-                     (const cpx<T>*)b.work, b.nj, b.nk, b.tri, role, role ? b.k0 : b.j0, role ? b.j0 : b.k0, units,
+                     (const cpx<T>*)b.work, b.nj, b.nk, b.tri, role, b.j0, b.k0, units,
                      c.acc, c.ld_acc, c.first, c.out, c.ld_out, c.out_c64, c.last, g, (const cpx<T>*)tb->tw[0],
-                     (const cpx<T>*)tb->tw[1], (b.zsplit >> 1) & 1, role ? TrajSegs{} : b.segs, b.jsplit, c.gstride,
-                     dbl);
+                     (const cpx<T>*)tb->tw[1], item_split(g.nz, units, (b.zsplit >> 1) & 1, grid),
+                     role ? TrajSegs{} : b.segs, b.jsplit, c.gstride, dbl);
   FX_LAUNCH_CHECK();
   return FX_OK;
 }

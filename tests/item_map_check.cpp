@@ -20,8 +20,9 @@ int main() {
           if (G >= kXcds) G -= G % kXcds;
           std::vector<int> seen(units * nz, 0);
           int share[kXcds] = {0};
+          const int split = item_split(nz, units, zsplit, G);
           for (int b = 0; b < G; ++b) {
-            const ItemMap m = item_map(nz, units, zsplit, G, b);
+            const ItemMap m = item_map(nz, units, split, G, b);
             for (int li = m.first; li < m.total; li += m.step) {
               int u, z;
               m.at(li, &u, &z);
