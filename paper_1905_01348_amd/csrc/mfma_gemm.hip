@@ -34,6 +34,7 @@ namespace fx {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 
 // ---- rounding ---------------------------------------------------------------
@@ -143,9 +144,13 @@ __device__ inline uint4 times_minus_i(uint4 v, int elem_bytes) {
 }
 
 // ---------------------------------------------------------------------------
-// TN GEMM on matrix cores.  256 threads = 4 waves in a 2x2 arrangement, each
-// wave a 64x64 block of D made of 2x2 MFMA 32x32 tiles.  Workgroup tile
-// 128 x 128, K step BK.
+// TN GEMM on matrix cores, FP32 operands (k_tn_pair takes the 2-byte types).
+// 256 threads = 4 waves in a 2x2 arrangement, each wave a 64x64 block of D made
+// of 2x2 MFMA 32x32 tiles.  Workgroup tile 128 x 128, K step BK.  Held to two
+// waves per SIMD (accumulators in the unified register file), so that two
+// workgroups share a CU and one's barriers and loads overlap the other's matrix
+// work: at 96^3, N = R = 1024 this took the products with the residual from
+// 67-68% to 73-82% of the FP32 peak (the output product spills a few registers).
 //   A: rows m (M of them), A[m*lda + k];  B: rows n (N of them), B[n*ldb + k].
 //   BDOUBLE: B holds N/2 source rows; LDS row 2c is source row c and row
 //            2c+1 is source row c times -i (see header comment).
@@ -153,6 +158,16 @@ __device__ inline uint4 times_minus_i(uint4 v, int elem_bytes) {
 //   MODE 1: write y(r=m, n/2) component n&1 = -alpha * D to a complex output.
 // ---------------------------------------------------------------------------
 constexpr int TBM = 128, TBN = 128;
+
+// Position of this block in the order of (tile_n, tile_m, split), n fastest.
+// Blocks are dealt to the 8 XCDs round-robin; each XCD takes a run of
+// consecutive positions, so that the tiles in flight on it share rows of A and
+// B in its L2.  (The run used to be taken for a multiple of 8 blocks only: with
+// 3556, 432 factors and right-hand sides at 72^3, 97% of the L2 reads missed.)
+__device__ inline int xcd_block() {
+  const int n = gridDim.x, b = blockIdx.x, x = b & 7, rest = n & 7;
+  return x * (n >> 3) + min(x, rest) + (b >> 3);
+}
 
 // Order of a wave's own LDS accesses across lanes: the wave's LDS
 // instructions execute in issue order, so only the compiler has to be kept
@@ -162,16 +177,6 @@ __device__ inline void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-
-// Held to two waves per SIMD (accumulators in the unified register file), so
-// that two workgroups share a CU and one's barriers and loads overlap the
-// other's matrix work: at 96^3, N = R = 1024 this took the BF16+residual
-// GEMMs from 20% to 37% of the BF16 peak and the FP32+residual ones from
-// 67-68% to 73-82% of the FP32 peak (the output GEMM spills a few registers).
-template <typename S>
-struct MfmaWaves {
-  static constexpr int value = 2;
-};
 
 // Epilogue of the TN GEMM kernels: D tile element e of MFMA tile (i, j) of a
 // wave is row i*32 + 8*(e/4) + 4*(lane/32) + e%4, column j*32 + lane%32 of the
@@ -234,11 +239,12 @@ __device__ inline void tn_epilogue(floatx16 (&acc)[2][2], floatx16 (&cor)[2][2],
 }
 
 template <typename S, bool REFINE, bool BDOUBLE, int MODE>
-__global__ void __launch_bounds__(256, (MfmaWaves<S>::value)) k_tn_mfma(int M, int N, int K, int kchunk, const S* __restrict__ Ap,
+__global__ void __launch_bounds__(256, 2) k_tn_mfma(int M, int N, int K, int kchunk, const S* __restrict__ Ap,
                                                  const S* __restrict__ Ar, int64_t lda, const S* __restrict__ Bp,
                                                  const S* __restrict__ Br, int64_t ldb, double* __restrict__ partial,
                                                  void* __restrict__ out, int64_t ldo, int out_c64, double alpha,
                                                  const double* __restrict__ colalpha, int tiles_m, int tiles_n) {
+  static_assert(sizeof(S) == 4, "FP32 operands");
   constexpr int BK = Prec<S>::BK;
   constexpr int LDK = BK + Prec<S>::PAD;
   constexpr int EPV = 16 / sizeof(S);  // elements per 16-byte vector
@@ -251,13 +257,7 @@ __global__ void __launch_bounds__(256, (MfmaWaves<S>::value)) k_tn_mfma(int M, i
   S* sAr = sm + 2 * TBM * LDK;
   S* sBr = sm + 3 * TBM * LDK;
 
-  // block -> (tile_m, tile_n, split); consecutive blocks on one XCD share
-  // the A row-tile: the hardware deals blocks to the 8 XCDs round-robin.
-  const int nblk = gridDim.x;
-  const int bid = blockIdx.x;
-  const int per_xcd = (nblk + 7) / 8;
-  int lid = (bid % 8) * per_xcd + bid / 8;
-  if (nblk % 8 != 0) lid = bid;  // keep the mapping a bijection
+  const int lid = xcd_block();
   const int tn = lid % tiles_n;
   const int rest = lid / tiles_n;
   const int tm = rest % tiles_m;
@@ -342,88 +342,36 @@ __global__ void __launch_bounds__(256, (MfmaWaves<S>::value)) k_tn_mfma(int M, i
     if (k0 + BK < kend) gload(k0 + BK);
     const int ar = wm * 64 + (lane & 31);
     const int br = wn * 64 + (lane & 31);
-    if constexpr (sizeof(S) == 4) {
-      // MFMA u of group q takes k = 4q + u (lanes 0-31) and BK/2 + 4q + u
-      // (lanes 32-63): any order of the step's k terms gives the same sum up
-      // to rounding, and this one lets each lane fetch the operands of four
-      // MFMAs with one 16-byte LDS read (rows 36 floats apart fill the 32
-      // banks in each group of 8 lanes; 4-byte reads of 32 rows did not)
+    // MFMA u of group q takes k = 4q + u (lanes 0-31) and BK/2 + 4q + u
+    // (lanes 32-63): any order of the step's k terms gives the same sum up
+    // to rounding, and this one lets each lane fetch the operands of four
+    // MFMAs with one 16-byte LDS read (rows 36 floats apart fill the 32
+    // banks in each group of 8 lanes; 4-byte reads of 32 rows did not)
 #pragma unroll
-      for (int q = 0; q < BK / 8; ++q) {
-        const int kc = (lane >> 5) * (BK / 2) + 4 * q;
-        float4 a[2], b[2], a2[2], b2[2];
+    for (int q = 0; q < BK / 8; ++q) {
+      const int kc = (lane >> 5) * (BK / 2) + 4 * q;
+      float4 a[2], b[2], a2[2], b2[2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          a[t] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(sAp) + (ar + 32 * t) * LDK + kc);
-          b[t] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(sBp) + (br + 32 * t) * LDK + kc);
-          if (REFINE) {
-            a2[t] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(sAr) + (ar + 32 * t) * LDK + kc);
-            b2[t] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(sBr) + (br + 32 * t) * LDK + kc);
-          }
+      for (int t = 0; t < 2; ++t) {
+        a[t] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(sAp) + (ar + 32 * t) * LDK + kc);
+        b[t] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(sBp) + (br + 32 * t) * LDK + kc);
+        if (REFINE) {
+          a2[t] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(sAr) + (ar + 32 * t) * LDK + kc);
+          b2[t] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(sBr) + (br + 32 * t) * LDK + kc);
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][u], b[j][u], acc[i][j], 0, 0, 0);
-              if (REFINE) {
-                cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][u], b2[j][u], cor[i][j], 0, 0, 0);
-                cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a2[i][u], b[j][u], cor[i][j], 0, 0, 0);
-              }
-            }
       }
-    } else if constexpr (std::is_same<S, _Float16>::value) {
 #pragma unroll
-      for (int kk = 0; kk < BK / 16; ++kk) {
-        const int kc = kk * 16 + (lane >> 5) * 8;
-        halfx8 a[2], b[2], a2[2], b2[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          a[t] = __builtin_bit_cast(halfx8, *reinterpret_cast<const uint4*>(sAp + (ar + 32 * t) * LDK + kc));
-          b[t] = __builtin_bit_cast(halfx8, *reinterpret_cast<const uint4*>(sBp + (br + 32 * t) * LDK + kc));
-          if (REFINE) {
-            a2[t] = __builtin_bit_cast(halfx8, *reinterpret_cast<const uint4*>(sAr + (ar + 32 * t) * LDK + kc));
-            b2[t] = __builtin_bit_cast(halfx8, *reinterpret_cast<const uint4*>(sBr + (br + 32 * t) * LDK + kc));
-          }
-        }
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], b[j], acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][u], b[j][u], acc[i][j], 0, 0, 0);
             if (REFINE) {
-              cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], b2[j], cor[i][j], 0, 0, 0);
-              cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2[i], b[j], cor[i][j], 0, 0, 0);
+              cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][u], b2[j][u], cor[i][j], 0, 0, 0);
+              cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a2[i][u], b[j][u], cor[i][j], 0, 0, 0);
             }
           }
-      }
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < BK / 16; ++kk) {
-        const int kc = kk * 16 + (lane >> 5) * 8;
-        bf16x8 a[2], b[2], a2[2], b2[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          a[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(sAp + (ar + 32 * t) * LDK + kc));
-          b[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(sBp + (br + 32 * t) * LDK + kc));
-          if (REFINE) {
-            a2[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(sAr + (ar + 32 * t) * LDK + kc));
-            b2[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(sBr + (br + 32 * t) * LDK + kc));
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-            if (REFINE) {
-              cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b2[j], cor[i][j], 0, 0, 0);
-              cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2[i], b[j], cor[i][j], 0, 0, 0);
-            }
-          }
-      }
     }
     __syncthreads();
   }
@@ -433,64 +381,80 @@ __global__ void __launch_bounds__(256, (MfmaWaves<S>::value)) k_tn_mfma(int M, i
 }
 
 // ---------------------------------------------------------------------------
-// The same TN GEMM for the 2-byte operand types (BF16, FP16) with the operand
-// tiles loaded straight into LDS: 16-byte global_load_lds (no staging
-// registers, no LDS store instructions), two LDS buffers so that the next K
-// step's loads run while the current one is multiplied, one barrier per K
-// step.  K steps of DL_BK = 32 elements: a tile row is 64 bytes (4 chunks of
-// 8 elements), stored without padding; row r keeps global chunk g in slot
-// g ^ ((r >> 2) & 3), so that the 16-byte operand reads of 16 consecutive
-// rows (one pass of the LDS) fall on distinct banks.  With BDOUBLE only the
-// N/2 source rows are stored; an odd B row is its source row times -i, made
-// when the operand is read.  Same results as k_tn_mfma up to the order of
-// the k terms within a step.
-constexpr int DL_BK = 32;
+// The TN GEMM for the 2-byte operand types (BF16, FP16), real and imaginary
+// part of a right-hand side together.  256 threads = 4 waves, 2 x 2; workgroup
+// tile 128 rows of A by 64 right-hand sides, a wave 64 by 32.  Only the source
+// rows of B (row ldb * c of right-hand side c) are stored and read: the second
+// column tile of a wave multiplies the same fragments turned in registers,
+// (a, b) -> (b, -a) in MODE 0 and (-b, a) in MODE 1, so that tile j = 0 holds
+// the real and j = 1 the imaginary parts, lane by lane.
+// Per K step of 64 a wave has 48 matrix instructions (1540 cycles) and reads 24
+// fragments (32 with both parts stored), one 16-deep slice ahead of their use;
+// the next step's tiles are loaded into registers meanwhile, and two workgroups
+// a CU cover each other's barriers.  (Tiles loaded straight to LDS instead need
+// all fragments of a step in registers first, since an LDS read waits for such
+// loads: with steps of 64 they spill, with 32 the loads have too little time.)
+// A tile row is 128 bytes, eight 16-byte chunks without padding; row r keeps
+// global chunk g in slot g ^ ((r >> 1) & 7), so that the reads of 16
+// consecutive rows fall on distinct banks.  Waves whose rows or right-hand
+// sides are all past the edge load, but multiply nothing (432 factors fill 3.4
+// row tiles).
+//   MODE 0: FP64 partial sums, partial[(split*M + m)*N + 2c], + 1 (as a pair).
+//   MODE 1: y(r = m, c) = -colalpha[c] D.
+// The k terms of an element run in order, 16 per matrix instruction, as in
+// k_tn_skinny.
+// What bounds it now is the chip's power: 432 factors and right-hand sides at
+// 72^3 in FP16 with the residual, first product 2627 -> 2053 us, output product
+// 2423 -> 1766 (875 and 1020 TFLOP/s executed; a large library product in BF16
+// reaches 1190).  The last 11% of cycles saved went into a lower clock (1.92 ->
+// 1.83 GHz).  Without the residual 1250 -> 704 and 1010 -> 739 us.
+// ---------------------------------------------------------------------------
+constexpr int PBK = 64, PROWB = 128;                     // K step: elements, bytes of a row
+constexpr int kPairA = TBM * PROWB, kPairB = 64 * PROWB;  // one operand tile
 
-__device__ inline int dl_swz(int row) { return (row >> 2) & 3; }
+template <bool REFINE>
+constexpr size_t pair_lds_bytes() {
+  return std::max<size_t>((size_t)(REFINE ? 2 : 1) * (kPairA + kPairB), (size_t)4 * 16 * 33 * sizeof(double2));
+}
 
-__device__ inline void dl_load16(const void* g, unsigned char* lds_wave_base) {
+__device__ inline void lds_load16(const void* g, unsigned char* lds_wave_base) {
   __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds_wave_base, 16, 0, 0);
 }
 
-template <typename S, bool BDOUBLE>
-struct DlShape {
-  static constexpr int ROWB = DL_BK * (int)sizeof(S);  // 64 bytes
-  static constexpr int AB = TBM * ROWB;                // one A operand tile
-  static constexpr int BROWS = BDOUBLE ? TBN / 2 : TBN;
-  static constexpr int BB = BROWS * ROWB;              // one B operand tile
-};
-template <typename S, bool REFINE, bool BDOUBLE>
-constexpr size_t dl_stage_bytes() {
-  return (size_t)(REFINE ? 2 : 1) * (DlShape<S, BDOUBLE>::AB + DlShape<S, BDOUBLE>::BB);
+template <typename S>
+__device__ inline floatx16 mfma16(u32x4 a, u32x4 b, floatx16 c) {
+  if constexpr (std::is_same<S, _Float16>::value)
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a), __builtin_bit_cast(halfx8, b), c, 0,
+                                                  0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                   0, 0);
 }
 
-template <typename S, bool REFINE, bool BDOUBLE, int MODE>
-__global__ void __launch_bounds__(256, 2) k_tn_mfma_dl(int M, int N, int K, int kchunk, const S* __restrict__ Ap,
-                                                      const S* __restrict__ Ar, int64_t lda, const S* __restrict__ Bp,
-                                                      const S* __restrict__ Br, int64_t ldb, double* __restrict__ partial,
-                                                      void* __restrict__ out, int64_t ldo, int out_c64, double alpha,
-                                                      const double* __restrict__ colalpha, int tiles_m, int tiles_n) {
+template <typename S, bool REFINE, int MODE>
+__global__ void __launch_bounds__(256, 2) k_tn_pair(int M, int R, int K, int kchunk, const S* __restrict__ Ap,
+                                                    const S* __restrict__ Ar, int64_t lda, const S* __restrict__ Bp,
+                                                    const S* __restrict__ Br, int64_t ldb,
+                                                    double* __restrict__ partial, void* __restrict__ out, int64_t ldo,
+                                                    int out_c64, const double* __restrict__ colalpha, int tiles_m,
+                                                    int tiles_n) {
   static_assert(sizeof(S) == 2, "2-byte operands");
-  using D = DlShape<S, BDOUBLE>;
   constexpr int NOPS = REFINE ? 2 : 1;
-  constexpr int STAGE = (int)dl_stage_bytes<S, REFINE, BDOUBLE>();
   extern __shared__ __align__(16) unsigned char smem_raw[];
+  unsigned char* tA = smem_raw;
+  unsigned char* tB = smem_raw + NOPS * kPairA;
 
-  const int nblk = gridDim.x;
-  const int bid = blockIdx.x;
-  const int per_xcd = (nblk + 7) / 8;
-  int lid = (bid % 8) * per_xcd + bid / 8;
-  if (nblk % 8 != 0) lid = bid;
-  const int tn = lid % tiles_n;
-  const int rest = lid / tiles_n;
-  const int tm = rest % tiles_m;
-  const int split = rest / tiles_m;
-  const int m0 = tm * TBM, n0 = tn * TBN;
-  const int kbeg = split * kchunk;
-  const int kend = min(K, kbeg + kchunk);
+  const int lid = xcd_block();
+  const int tn = lid % tiles_n, rest = lid / tiles_n;
+  const int tm = rest % tiles_m, split = rest / tiles_m;
+  const int m0 = tm * TBM, c0 = tn * 64;
+  const int kbeg = split * kchunk, kend = min(K, kbeg + kchunk);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave & 1, wn = wave >> 1;
+  const int half = lane >> 5, l32 = lane & 31;
+  // nothing of this wave's tile is part of the output
+  const bool idle = c0 + wn * 32 >= R || m0 + wm * 64 >= M;
 
   floatx16 acc[2][2], cor[2][2];
 #pragma unroll
@@ -503,104 +467,148 @@ __global__ void __launch_bounds__(256, 2) k_tn_mfma_dl(int M, int N, int K, int 
         cor[i][j][e] = 0.f;
       }
 
-  // loads of the K step at k0 into buffer b: each wave-instruction fills 1 KB
-  // (16 rows); lane l lands in row l / 4, slot l % 4 of it.  Rows past the
-  // edge load a clamped, valid row: they only reach outputs that are not
-  // written.
-  const int lrow = lane >> 2, lslot = lane & 3;
-  auto issue = [&](int k0, int b) __attribute__((always_inline)) {
-    unsigned char* base = smem_raw + b * STAGE;
+  // each wave instruction fills 1 KB (8 rows): lane l lands in row l / 8, slot
+  // l % 8 of it.  Rows past the edge load a clamped, valid row: they only reach
+  // outputs that are not written.
+  // (byte offsets within a tile: rows are at most 2 * 96^3 elements, so 32 bits hold them)
+  uint32_t offa[4], offb[2];
 #pragma unroll
-    for (int q = 0; q < TBM / 64; ++q) {
-      const int ch = wave + 4 * q, row = ch * 16 + lrow;
-      const int m = min(m0 + row, M - 1);
-      const int64_t off = (int64_t)m * lda + k0 + (lslot ^ dl_swz(row)) * 8;
-      dl_load16(Ap + off, base + ch * 1024);
-      if (REFINE) dl_load16(Ar + off, base + D::AB + ch * 1024);
-    }
-    const int nlim = BDOUBLE ? N / 2 : N;
-    const int nb = BDOUBLE ? n0 / 2 : n0;
+  for (int q = 0; q < 4; ++q) {
+    const int row = (wave + 4 * q) * 8 + (lane >> 3), slot = (lane & 7) ^ ((row >> 1) & 7);
+    offa[q] = (uint32_t)min(row, M - 1 - m0) * (uint32_t)lda * 2u + slot * 16u;
+    if (q < 2) offb[q] = (uint32_t)min(row, R - 1 - c0) * (uint32_t)ldb * 2u + slot * 16u;
+  }
+  // (buffer addressing: one offset register per row instead of a 64-bit pointer
+  // per row and operand)
+  const auto rsrc = [](const S* base) __attribute__((always_inline)) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<S*>(base), 0, 0xffffffff, 0x00027000);
+  };
+  const __amdgpu_buffer_rsrc_t gA[2] = {rsrc(Ap + (int64_t)m0 * lda), rsrc((REFINE ? Ar : Ap) + (int64_t)m0 * lda)};
+  const __amdgpu_buffer_rsrc_t gB[2] = {rsrc(Bp + (int64_t)c0 * ldb), rsrc((REFINE ? Br : Bp) + (int64_t)c0 * ldb)};
+  u32x4 ra[NOPS][4], rb[NOPS][2];
+  const auto gload = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < D::BROWS / 64; ++q) {
-      const int ch = wave + 4 * q, row = ch * 16 + lrow;
-      const int nn = min(nb + row, nlim - 1);
-      const int64_t off = (int64_t)nn * ldb + k0 + (lslot ^ dl_swz(row)) * 8;
-      dl_load16(Bp + off, base + NOPS * D::AB + ch * 1024);
-      if (REFINE) dl_load16(Br + off, base + NOPS * D::AB + D::BB + ch * 1024);
+    for (int o = 0; o < NOPS; ++o) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) ra[o][q] = __builtin_amdgcn_raw_buffer_load_b128(gA[o], offa[q], k0 * 2, 0);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) rb[o][q] = __builtin_amdgcn_raw_buffer_load_b128(gB[o], offb[q], k0 * 2, 0);
     }
   };
-  auto frag = [&](const unsigned char* t, int row, int g) __attribute__((always_inline)) {
-    return *reinterpret_cast<const uint4*>(t + row * D::ROWB + ((g ^ dl_swz(row)) << 4));
+  const auto sstore = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int o = 0; o < NOPS; ++o) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<u32x4*>(tA + o * kPairA + (wave + 4 * q) * 1024 + lane * 16) = ra[o][q];
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        *reinterpret_cast<u32x4*>(tB + o * kPairB + (wave + 4 * q) * 1024 + lane * 16) = rb[o][q];
+    }
   };
-  auto bfrag = [&](const unsigned char* t, int br, int g) __attribute__((always_inline)) {
-    if (!BDOUBLE) return frag(t, br, g);
-    const uint4 v = frag(t, br >> 1, g);
-    const uint4 w = times_minus_i(v, 2);
-    const bool odd = br & 1;
-    return uint4{odd ? w.x : v.x, odd ? w.y : v.y, odd ? w.z : v.z, odd ? w.w : v.w};
+  const auto frag = [&](const unsigned char* t, int row, int g) __attribute__((always_inline)) {
+    return *reinterpret_cast<const u32x4*>(t + row * PROWB + ((g ^ ((row >> 1) & 7)) << 4));
+  };
+  const auto turned = [](u32x4 v) __attribute__((always_inline)) {
+    constexpr uint32_t sign = MODE == 0 ? 0x80000000u : 0x8000u;
+    return (v << 16 | v >> 16) ^ sign;
   };
 
-  const int nsteps = (kend - kbeg) / DL_BK;
-  if (nsteps > 0) issue(kbeg, 0);
-  for (int st = 0; st < nsteps; ++st) {
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's loads of step st have landed
-    __syncthreads();                // ... every wave's; and step st - 1's reads are done
-    const unsigned char* base = smem_raw + (st & 1) * STAGE;
-    const unsigned char* tAp = base;
-    const unsigned char* tAr = base + D::AB;
-    const unsigned char* tBp = base + NOPS * D::AB;
-    const unsigned char* tBr = tBp + D::BB;
-    // every operand of the step is read before the next step's loads are
-    // issued: a read of LDS after those loads would wait for them
-    uint4 a[2][2], b[2][2], a2[2][2], b2[2][2];  // [kk][t]
+  if (kbeg < kend) gload(kbeg);
+  for (int k0 = kbeg; idle && k0 < kend; k0 += PBK) {
+    sstore();
+    __syncthreads();
+    if (k0 + PBK < kend) gload(k0 + PBK);
+    __syncthreads();
+  }
+  u32x4 a[2][2][NOPS], b[2][NOPS];  // [kk & 1]: fragments, read one 16-deep slice ahead
+  const auto fread = [&](int kk) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kk = 0; kk < DL_BK / 16; ++kk) {
-      const int g = kk * 2 + (lane >> 5);
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int ar = wm * 64 + (lane & 31) + 32 * t;
-        const int br = wn * 64 + (lane & 31) + 32 * t;
-        a[kk][t] = frag(tAp, ar, g);
-        b[kk][t] = bfrag(tBp, br, g);
-        if (REFINE) {
-          a2[kk][t] = frag(tAr, ar, g);
-          b2[kk][t] = bfrag(tBr, br, g);
-        }
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (st + 1 < nsteps) issue(kbeg + (st + 1) * DL_BK, (st + 1) & 1);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kk = 0; kk < DL_BK / 16; ++kk)
+    for (int o = 0; o < NOPS; ++o) {
+      b[kk & 1][o] = frag(tB + o * kPairB, wn * 32 + l32, kk * 2 + half);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
+        a[kk & 1][i][o] = frag(tA + o * kPairA, wm * 64 + 32 * i + l32, kk * 2 + half);
+    }
+  };
+  for (int k0 = kbeg; !idle && k0 < kend; k0 += PBK) {
+    sstore();
+    __syncthreads();
+    fread(0);
+    if (k0 + PBK < kend) gload(k0 + PBK);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          if constexpr (std::is_same<S, _Float16>::value) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                __builtin_bit_cast(halfx8, a[kk][i]), __builtin_bit_cast(halfx8, b[kk][j]), acc[i][j], 0, 0, 0);
-            if (REFINE) {
-              cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                  __builtin_bit_cast(halfx8, a[kk][i]), __builtin_bit_cast(halfx8, b2[kk][j]), cor[i][j], 0, 0, 0);
-              cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                  __builtin_bit_cast(halfx8, a2[kk][i]), __builtin_bit_cast(halfx8, b[kk][j]), cor[i][j], 0, 0, 0);
-            }
-          } else {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                __builtin_bit_cast(bf16x8, a[kk][i]), __builtin_bit_cast(bf16x8, b[kk][j]), acc[i][j], 0, 0, 0);
-            if (REFINE) {
-              cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                  __builtin_bit_cast(bf16x8, a[kk][i]), __builtin_bit_cast(bf16x8, b2[kk][j]), cor[i][j], 0, 0, 0);
-              cor[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                  __builtin_bit_cast(bf16x8, a2[kk][i]), __builtin_bit_cast(bf16x8, b[kk][j]), cor[i][j], 0, 0, 0);
-            }
-          }
+    for (int kk = 0; kk < PBK / 16; ++kk) {
+      if (kk + 1 < PBK / 16) fread(kk + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      const int f = kk & 1;
+      u32x4 bt[NOPS];
+#pragma unroll
+      for (int o = 0; o < NOPS; ++o) bt[o] = turned(b[f][o]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        acc[i][0] = mfma16<S>(a[f][i][0], b[f][0], acc[i][0]);
+        if constexpr (REFINE) cor[i][0] = mfma16<S>(a[f][i][0], b[f][1], cor[i][0]);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        acc[i][1] = mfma16<S>(a[f][i][0], bt[0], acc[i][1]);
+        if constexpr (REFINE) cor[i][1] = mfma16<S>(a[f][i][0], bt[1], cor[i][1]);
+      }
+      if constexpr (REFINE) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          cor[i][0] = mfma16<S>(a[f][i][1], b[f][0], cor[i][0]);
+          cor[i][1] = mfma16<S>(a[f][i][1], bt[0], cor[i][1]);
         }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
   }
-  __syncthreads();  // the epilogue reuses the LDS
-  tn_epilogue<REFINE, MODE>(acc, cor, smem_raw, lane, wave, wm, wn, m0, n0, M, N, split, partial, out, ldo, out_c64,
-                            alpha, colalpha);
+
+  const int c = c0 + wn * 32 + l32;
+  const auto value = [&](int i, int j, int e) __attribute__((always_inline)) {
+    return (double)acc[i][j][e] + (REFINE ? (double)cor[i][j][e] : 0.0);
+  };
+  if (MODE == 0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int m = m0 + wm * 64 + i * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+        if (m < M && c < R)
+          *reinterpret_cast<double2*>(partial + (((int64_t)split * M + m) * R + c) * 2) =
+              double2{value(i, 0, e), value(i, 1, e)};
+      }
+    return;
+  }
+  // the output runs along m (r) for each target: each wave turns its tiles
+  // around, 16 rows at a time, in its own slice of the (now idle) LDS
+  const double al = c < R ? (colalpha ? colalpha[c] : 1.0) : 0.0;
+  double2* stg = reinterpret_cast<double2*>(smem_raw) + wave * 16 * 33;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int e = 8 * h; e < 8 * h + 8; ++e)
+        stg[(8 * ((e >> 2) & 1) + 4 * half + (e & 3)) * 33 + l32] = double2{-al * value(i, 0, e), -al * value(i, 1, e)};
+      wave_lds_sync();
+      const int ml = lane & 15, m = m0 + wm * 64 + i * 32 + 16 * h + ml;
+#pragma unroll
+      for (int it = 0; it < 8; ++it) {
+        const int tl = (lane >> 4) + 4 * it, t = c0 + wn * 32 + tl;
+        const double2 v = stg[ml * 33 + tl];
+        if (m < M && t < R) {
+          const int64_t idx = (int64_t)t * ldo + m;
+          if (out_c64)
+            reinterpret_cast<float2*>(out)[idx] = make_float2((float)v.x, (float)v.y);
+          else
+            reinterpret_cast<double2*>(out)[idx] = v;
+        }
+      }
+      wave_lds_sync();
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -627,12 +635,8 @@ __device__ inline floatx16 mfma_vec(uint4 a, uint4 b, floatx16 c) {
     c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, c, 0, 0, 0);
     c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, c, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, c, 0, 0, 0);
-  } else if constexpr (std::is_same<S, _Float16>::value) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a), __builtin_bit_cast(halfx8, b), c, 0,
-                                                  0, 0);
   } else {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
-                                                   0, 0);
+    return mfma16<S>(__builtin_bit_cast(u32x4, a), __builtin_bit_cast(u32x4, b), c);
   }
 }
 
@@ -1037,18 +1041,6 @@ fx_status ace_prepare_split(fx_ace* a, fx_prec prec, hipStream_t st) {
   return FX_OK;
 }
 
-// Which GEMMs of the 2-byte forms run the direct-to-LDS kernel: the output
-// GEMM y = -xi C (measured faster: at 96^3, N = R = 1024, 34 -> 36% of the
-// BF16 matrix peak with the residual step, 25 -> 29% without), not C =
-// xi^H phi, whose -i rows made at read time cost more VALU work than the
-// staged kernel's LDS stores (35 -> 26%).  FX_ACE_DL = 0 uses neither, 2
-// both (for comparison).
-static bool ace_direct_lds(int mode) {
-  const char* e = getenv("FX_ACE_DL");
-  const int v = e ? atoi(e) : 1;
-  return v == 2 || (v == 1 && mode == 1);
-}
-
 template <typename S, bool REFINE>
 static fx_status apply_t(fx_ctx* ctx, Workspace* ws, fx_ace* a, AceSplit* sp, const void* phi, int R, int64_t ld_phi,
                          void* out, int64_t ld_out, fx_dtype in_dtype, fx_dtype out_dtype, hipStream_t st) {
@@ -1097,7 +1089,7 @@ static fx_status apply_t(fx_ctx* ctx, Workspace* ws, fx_ace* a, AceSplit* sp, co
   FX_LAUNCH_CHECK();
   FX_TRY(prof_end(ctx, st, slot));
 
-  const size_t lds = (size_t)(REFINE ? 4 : 2) * TBM * LDK * sizeof(S);
+  [[maybe_unused]] const size_t lds = (size_t)(REFINE ? 4 : 2) * TBM * LDK * sizeof(S);
   // C = xi^H phi: M = n, N = 2R, K = kc, split over K
   {
     const int tiles_m = (n + TBM - 1) / TBM, tiles_n = (2 * R + TBN - 1) / TBN;
@@ -1113,33 +1105,37 @@ static fx_status apply_t(fx_ctx* ctx, Workspace* ws, fx_ace* a, AceSplit* sp, co
     nsplit = (int)((sp->kc + kchunk - 1) / kchunk);
     void* part = nullptr;
     FX_TRY(ws_get(ctx, ws, "mf_partial", sizeof(double) * (size_t)nsplit * n * 2 * R, &part));
-    // Up to 16 right-hand sides (one column tile) a wave per 32 rows instead of
-    // 128 x 128 tiles, up to 32 in FP32 or where the tiles would not fill the
-    // chip twice (measured, us, waves against tiles: 16-bit, 48^3, 128 factors,
-    // 8: 31 / 93, 32: 57 / 93; 72^3, 432 factors, 16: 372 / 410, 24: 576 / 410;
-    // FP32, 432 factors, 8: 795 / 2350, 32: 1694 / 2350).
-    const bool waves_cn = R <= 16 || (R <= 32 && (sizeof(S) == 4 || tiles * nsplit < 512));
+    // Few right-hand sides by a wave per 32 rows instead of workgroup tiles.  FP32:
+    // up to 32 (us, waves against tiles: 432 factors at 72^3, 8 of them 795 / 2350,
+    // 32: 1694 / 2350).  2-byte types, up to 16: while the tiles leave half the chip
+    // idle (with the residual: 128 factors at 48^3, 8: 31 / 43, 216 at 72^3 193 /
+    // 166, 432 336 / 264; without it the waves hold out longer, 216 84 / 97, 432
+    // 147 / 136); 17 to 32: while the waves do (64 factors at 48^3, 24: 34 / 42,
+    // 128 51 / 46).
+    const int tms = (n + 31) / 32;
+    const bool waves_cn = sizeof(S) == 4 ? R <= 32
+                          : R <= 16     ? tiles * nsplit < (REFINE ? 192 : 384)
+                                        : R <= 32 && tms * nsplit < 512;
     FX_TRY(prof_begin(ctx, st, FX_K_GEMM_CN, (REFINE ? 3.0 : 1.0) * 2.0 * n * 2.0 * R * (double)sp->kc, &slot));
     if (waves_cn) {
-      const int tms = (n + 31) / 32;
       const auto kern = R <= 16 ? k_tn_skinny<S, REFINE, true, 0, 1> : k_tn_skinny<S, REFINE, true, 0, 2>;
       hipLaunchKernelGGL(kern, dim3((unsigned)(tms * nsplit)), dim3(64), 0, st, n, 2 * R, (int)kchunk, (int)sp->kc,
                          (const S*)sp->col_p, (const S*)sp->col_r, sp->kc, (const S*)php, (const S*)phr, sp->kc,
                          (double*)part, (void*)nullptr, (int64_t)0, 0, (const double*)nullptr, tms);
     } else {
-      auto kern = k_tn_mfma<S, REFINE, true, 0>;
-      size_t lds_cn = lds;
-      if constexpr (sizeof(S) == 2) {
-        if (ace_direct_lds(0)) {
-          kern = k_tn_mfma_dl<S, REFINE, true, 0>;
-          lds_cn = 2 * dl_stage_bytes<S, REFINE, true>();
-        }
-      }
-      FX_TRY(allow_lds_mfma(kern, lds_cn));
-      hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * nsplit)), dim3(256), lds_cn, st, n, 2 * R, (int)sp->kc,
-                         (int)kchunk, (const S*)sp->col_p, (const S*)sp->col_r, sp->kc, (const S*)php, (const S*)phr,
-                         sp->kc, (double*)part, (void*)nullptr, (int64_t)0, 0, 0.0, (const double*)nullptr, tiles_m,
-                         tiles_n);
+      const auto launch = [&](auto kern, size_t bytes, auto... rest) -> fx_status {
+        FX_TRY(allow_lds_mfma(kern, bytes));
+        hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * nsplit)), dim3(256), bytes, st, n, sizeof(S) == 2 ? R : 2 * R,
+                           (int)sp->kc, (int)kchunk, (const S*)sp->col_p, (const S*)sp->col_r, sp->kc, (const S*)php,
+                           (const S*)phr, sp->kc, (double*)part, (void*)nullptr, (int64_t)0, 0, rest..., tiles_m,
+                           tiles_n);
+        return FX_OK;
+      };
+      const double* no_scale = nullptr;
+      if constexpr (sizeof(S) == 2)
+        FX_TRY(launch(k_tn_pair<S, REFINE, 0>, pair_lds_bytes<REFINE>(), no_scale));
+      else
+        FX_TRY(launch(k_tn_mfma<S, REFINE, true, 0>, lds, 1.0, no_scale));
     }
     FX_LAUNCH_CHECK();
     FX_TRY(prof_end(ctx, st, slot));
@@ -1183,20 +1179,25 @@ static fx_status apply_t(fx_ctx* ctx, Workspace* ws, fx_ace* a, AceSplit* sp, co
     }
     if (!waves_out) {
       const int tm2 = (int)((nr + TBM - 1) / TBM), tn2 = (2 * R + TBN - 1) / TBN;
-      auto kern2 = k_tn_mfma<S, REFINE, false, 1>;
-      // the epilogue turns each wave's 32x32 tiles around in 32 x 33 doubles of LDS
-      size_t lds2 = std::max(lds, (size_t)4 * 32 * 33 * sizeof(double));
+      const dim3 grid((unsigned)(tm2 * tn2)), blk(256);
+      const int c64 = out_dtype == FX_C64 ? 1 : 0;
       if constexpr (sizeof(S) == 2) {
-        if (ace_direct_lds(1)) {
-          kern2 = k_tn_mfma_dl<S, REFINE, false, 1>;
-          lds2 = std::max(2 * dl_stage_bytes<S, REFINE, false>(), (size_t)4 * 32 * 33 * sizeof(double));
-        }
+        const auto kern = k_tn_pair<S, REFINE, 1>;
+        const size_t bytes = pair_lds_bytes<REFINE>();
+        FX_TRY(allow_lds_mfma(kern, bytes));
+        // (row 2c of B: the even rows)
+        hipLaunchKernelGGL(kern, grid, blk, bytes, st, (int)nr, R, (int)sp->kn, (int)sp->kn, (const S*)sp->row_p,
+                           (const S*)sp->row_r, sp->kn, (const S*)bp, (const S*)br, 2 * sp->kn, (double*)nullptr, out,
+                           ld_out, c64, (const double*)colalpha, tm2, tn2);
+      } else {
+        const auto kern = k_tn_mfma<S, REFINE, false, 1>;
+        // the epilogue turns each wave's 32x32 tiles around in 32 x 33 doubles of LDS
+        const size_t bytes = std::max(lds, (size_t)4 * 32 * 33 * sizeof(double));
+        FX_TRY(allow_lds_mfma(kern, bytes));
+        hipLaunchKernelGGL(kern, grid, blk, bytes, st, (int)nr, 2 * R, (int)sp->kn, (int)sp->kn, (const S*)sp->row_p,
+                           (const S*)sp->row_r, sp->kn, (const S*)bp, (const S*)br, sp->kn, (double*)nullptr, out,
+                           ld_out, c64, 1.0, (const double*)colalpha, tm2, tn2);
       }
-      FX_TRY(allow_lds_mfma(kern2, lds2));
-      hipLaunchKernelGGL(kern2, dim3((unsigned)(tm2 * tn2)), dim3(256), lds2, st, (int)nr, 2 * R, (int)sp->kn,
-                         (int)sp->kn, (const S*)sp->row_p, (const S*)sp->row_r, sp->kn, (const S*)bp, (const S*)br,
-                         sp->kn, (double*)nullptr, out, ld_out, out_dtype == FX_C64 ? 1 : 0, 1.0,
-                         (const double*)colalpha, tm2, tn2);
     }
     FX_LAUNCH_CHECK();
     FX_TRY(prof_end(ctx, st, slot));
