@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "fft.hpp"
+#include "item_map.hpp"
 #include "mfma_gemm.hpp"
 #include "vx.hpp"
 
@@ -159,16 +160,6 @@ __device__ inline uint4 times_minus_i(uint4 v, int elem_bytes) {
 // ---------------------------------------------------------------------------
 constexpr int TBM = 128, TBN = 128;
 
-// Position of this block in the order of (tile_n, tile_m, split), n fastest.
-// Blocks are dealt to the 8 XCDs round-robin; each XCD takes a run of
-// consecutive positions, so that the tiles in flight on it share rows of A and
-// B in its L2.  (The run used to be taken for a multiple of 8 blocks only: with
-// 3556, 432 factors and right-hand sides at 72^3, 97% of the L2 reads missed.)
-__device__ inline int xcd_block() {
-  const int n = gridDim.x, b = blockIdx.x, x = b & 7, rest = n & 7;
-  return x * (n >> 3) + min(x, rest) + (b >> 3);
-}
-
 // Order of a wave's own LDS accesses across lanes: the wave's LDS
 // instructions execute in issue order, so only the compiler has to be kept
 // from moving accesses across this point.
@@ -257,7 +248,7 @@ __global__ void __launch_bounds__(256, 2) k_tn_mfma(int M, int N, int K, int kch
   S* sAr = sm + 2 * TBM * LDK;
   S* sBr = sm + 3 * TBM * LDK;
 
-  const int lid = xcd_block();
+  const int lid = xcd_run(gridDim.x, blockIdx.x);  // n tiles fastest, then m, then splits
   const int tn = lid % tiles_n;
   const int rest = lid / tiles_n;
   const int tm = rest % tiles_m;
@@ -444,7 +435,7 @@ __global__ void __launch_bounds__(256, 2) k_tn_pair(int M, int R, int K, int kch
   unsigned char* tA = smem_raw;
   unsigned char* tB = smem_raw + NOPS * kPairA;
 
-  const int lid = xcd_block();
+  const int lid = xcd_run(gridDim.x, blockIdx.x);  // n tiles fastest, then m, then splits
   const int tn = lid % tiles_n, rest = lid / tiles_n;
   const int tm = rest % tiles_m, split = rest / tiles_m;
   const int m0 = tm * TBM, c0 = tn * 64;

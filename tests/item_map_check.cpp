@@ -39,6 +39,14 @@ int main() {
               if (s > 1.05 * units * nz / kXcds + G / kXcds)
                 return std::printf("nz %d units %d zsplit %d G %d: share %d\n", nz, units, zsplit, G, s), 1;
         }
+  for (int n = 1; n < 300; ++n) {
+    std::vector<int> seen(n, 0);
+    for (int b = 0; b < n; ++b) {
+      const int p = xcd_run(n, b);
+      if (p < 0 || p >= n || seen[p]++) return std::printf("xcd_run(%d, %d) = %d\n", n, b, p), 1;
+      if (b >= kXcds && p != xcd_run(n, b - kXcds) + 1) return std::printf("no run at %d of %d\n", b, n), 1;
+    }
+  }
   std::printf("ok\n");
   return 0;
 }
