@@ -386,7 +386,17 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
   // FP64: the orbital plane is loaded only before the last x stage, so that
   // its registers are not live through the y stages beside the accumulators
   // (loaded early it spills at 96^2)
-  constexpr bool kLateOrbital = sizeof(T) == 8;
+  // (not where a thread's part of the next plane fits a few registers, see kAhead)
+  constexpr int R1 = Plan2<N>::R1, kIn = StageIters<R1, N, N, NT>::value;
+  // The next term's work plane loaded into registers while the current one is
+  // transformed, where that takes at most 16 of them: a request's or a small
+  // application's few workgroups per CU otherwise wait for HBM in every term
+  // (us per apply: 24^3, 16 orbitals on themselves in FP64 40 -> 35, 64 on 32
+  // 158 -> 148, 128 on themselves in FP32 548 -> 495; 48^3, 128 on 8 with 384
+  // threads 383 -> 350).  With 24 registers the waves lost cost more: 48^3 FP32
+  // at 256 threads 4.72 -> 5.09 ms, FP64 at 384 threads 7.34 -> 8.60.
+  constexpr bool kAhead = FORM == 0 && kIn * R1 * sizeof(cpx<T>) <= 64;
+  constexpr bool kLateOrbital = sizeof(T) == 8 && !kAhead;
   // of those, the values loaded before the last x stage: half, the other half
   // once the stage's registers are free (all of them beside the stage spilled
   // 164 bytes per lane at 96^2, half of them 132; 2.73 -> 2.51 ms per launch)
@@ -514,11 +524,16 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
       a[i] = cpx<A>{0, 0};
       if (!first && (NXY % NT == 0 || e < NXY)) a[i] = accg[t * ld_acc + (size_t)z * NXY + e];
     }
-    constexpr int R0 = Plan2<N>::R0, R1 = Plan2<N>::R1;
+    constexpr int R0 = Plan2<N>::R0;
     for (int cj = cj0; cj <= (int)cj1; ++cj) {
       const A sgn = cj ? (A)-1 : (A)1;
       int lo, hi;
       range(tt, g, cj, &lo, &hi);
+      cpx<T> nx[kIn][R1];  // kAhead
+      const auto ahead = [&](int l_) __attribute__((always_inline)) {
+        ct_bfly_load<R1, T, N, R1, N, NT, true, N, 1, SX, 1, NTS>(nx, plane_ptr(tt, l_, cj, z), tid);
+      };
+      if (kAhead && lo < hi) ahead(lo);
       for (int l = lo; l < hi; l += jsplit) {
         // (multi-trajectory launches are never halved: role 0, target t's own orbitals)
         const cpx<T>* pm = seg_psi<T>(segs, mult, t) + (int64_t)((cj ? k0 : j0) + l) * ld_mult + (size_t)z * NXY;
@@ -555,8 +570,13 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
           }
         } else {
           // first inverse y stage straight from the work plane
-          ct_stage_io<R1, false, T, N, R1, N, SX, 1, NT, true, false, N, 1, NTS>(sl, plane_ptr(tt, l, cj, z), nullptr, tw,
-                                                                                tid);
+          if constexpr (kAhead) {
+            ct_bfly_run<R1, false, T, N, R1, N, NT>(nx, tw, tid);
+            ct_bfly_store<R1, T, N, R1, N, NT, false, N, 1, SX, 1, NTS>(nx, sl, tid);
+          } else {
+            ct_stage_io<R1, false, T, N, R1, N, SX, 1, NT, true, false, N, 1, NTS>(sl, plane_ptr(tt, l, cj, z), nullptr,
+                                                                                  tw, tid);
+          }
           __syncthreads();
           if (!kLateOrbital) {
 #pragma unroll
@@ -565,6 +585,7 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
               if (NXY % NT == 0 || e < NXY) vp[i] = pm[e];
             }
           }
+          if (kAhead && l + jsplit < hi) ahead(l + jsplit);
         }
         ct_stage<R0, false, T, N, N, N, SX, 1, NT>(sl, tw, tid);
         __syncthreads();
