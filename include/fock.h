@@ -242,10 +242,12 @@ typedef struct fx_vx_config {
   int32_t c_split;     /* plane-inverse pass: S sum groups per target (1, 2, 4 or 8;
                           0 automatic: 1 for phi == psi, else as many as give eight
                           targets on this grid the resident workgroups, at least four
-                          orbitals each; 1 if the budget cannot hold the sums).  The terms of orbital j go to group
-                          j mod S, each group summed in ascending j, the groups added in
-                          order at the end: S times the pass's work items for calls with
-                          few targets, at S partial sums per target of device memory.
+                          orbitals each, and two where they are up to a quarter more than
+                          those; 1 if the budget cannot hold the sums).  The terms of
+                          orbital j go to group j mod S, each group summed in ascending j,
+                          the groups added in order at the end: S times the pass's work
+                          items for calls with few targets, at S partial sums per target
+                          of device memory.
                           The result depends on S (rounding) but not on the batch size
                           or on which targets share a launch */
 } fx_vx_config;

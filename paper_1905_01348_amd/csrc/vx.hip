@@ -159,7 +159,11 @@ static int ct_c_variant(const VxArgs& a) {
 // 27 orbitals x 11 targets at 32 x 36 x 24: one sum leaves 264 items of 27
 // terms one after the other, 182 us, four groups 71 and 7 to add them; at 64^3
 // two groups gain nothing and their partial sums cost the other passes 130 of
-// 2440 us.
+// 2440 us.  Two groups also where eight targets are up to a quarter more than
+// the resident workgroups, so that the second round is a short one (96 orbitals
+// at 48 x 64 x 72 in FP64, 512 resident: 8 targets 4423 -> 4133 us, 16 8107 ->
+// 7739, 32 14630 -> 14920; at half more, 96 x 96 x 48, the partial sums cost as
+// much as they save).
 static int ct_jsplit(const VxArgs& a, const PassGeom& g, bool square) {
   if (a.no_alloc || a.add) return 1;
   if (a.c_split == 1 || a.c_split == 2 || a.c_split == 4 || a.c_split == 8) return a.c_split;
@@ -168,6 +172,9 @@ static int ct_jsplit(const VxArgs& a, const PassGeom& g, bool square) {
   const int64_t most = std::min<int64_t>(a.n_psi / 4, 256 * std::max(1, 12 / waves) / (8 * g.nz));
   int s = 1;
   while (s < 8 && 2 * s <= most) s *= 2;
+  // a second round of workgroups that is nearly empty for eight targets
+  const int64_t items = 8 * (int64_t)g.nz, resident = 256 * std::max(1, 12 / waves);
+  if (s == 1 && items > resident && 4 * items <= 5 * resident && a.n_psi >= 32) s = 2;
   return s;
 }
 
