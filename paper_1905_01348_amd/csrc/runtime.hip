@@ -66,6 +66,7 @@ fx_status ctx_alloc(fx_ctx* ctx, size_t bytes, void** out) {
   hipError_t e = hipMalloc(out, bytes);
   if (e != hipSuccess) {
     *out = nullptr;
+    (void)hipGetLastError();  // or a caller that goes on with less memory meets it at its next launch check
     FX_FAIL(FX_ERR_OOM, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
   }
   ctx->in_use += bytes;
@@ -128,11 +129,17 @@ fx_status ws_get(fx_ctx* ctx, Workspace* ws, const char* name, size_t bytes, voi
             "run the same call once outside capture first",
             name, bytes);
   if (b.ptr) {
+    // a growth beyond the budget leaves the buffer, and the graphs that use it, as they are
+    if (ctx->in_use - b.bytes + bytes > ctx->budget)
+      FX_FAIL(FX_ERR_OOM, "HBM budget exceeded: workspace '%s' of %zu bytes, %zu in use beside it > %zu budget", name,
+              bytes, ctx->in_use - b.bytes, ctx->budget);
     // the old buffer may still be in use by queued work
     FX_HIP(hipDeviceSynchronize());
     ctx_free(ctx, b.ptr, b.bytes);
     b.ptr = nullptr;
     b.bytes = 0;
+    // its address is no longer this workspace's, whether or not the new buffer can be had
+    ctx->ws_gen++;
   }
   FX_TRY(ctx_alloc(ctx, bytes, &b.ptr));
   b.bytes = bytes;

@@ -1,0 +1,82 @@
+"""Workspaces that cannot grow: cached graphs never replay on memory that was given back.
+
+A buffer that has to grow is freed before the larger one is allocated; a graph
+captured before uses its address, so the graph is stale from the moment of the
+free, also where the larger allocation then fails.  A growth that the budget
+refuses leaves the buffer, and the graphs that use it, as they are.
+"""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from paper_1905_01348_amd import Context
+from paper_1905_01348_amd import fock as F
+from tests.gpu_util import dev, host, say
+
+pytestmark = pytest.mark.gpu
+
+N3, L3 = (24, 24, 24), (10.26,) * 3
+
+
+def test_graphs_are_stale_once_their_buffer_is_freed():
+    psi = dev(synth.make_orbitals(400, N3, L3, 8, dtype=np.complex64))
+    few, many = psi[:2].clone(), psi[:6].clone()
+    kw = dict(n=N3, L=L3, kernel="hse", omega=0.106, prec="fp32acc64")
+    ctx = Context(0)
+    try:
+        ctx.graph_cache(4)
+        out = torch.empty((2,) + N3, dtype=torch.complex128, device="cuda")
+        ctx.apply_vx(psi, few, out=out, **kw)
+        ref = host(out)
+        ctx.apply_vx(psi, few, out=out, **kw)
+        assert ctx.graph_cache_stats()[:2] == (1, 1)
+        say("growth of the pair volume that fails after the old one is freed")
+        F.debug_fail_alloc(1)
+        with pytest.raises(F.FockError) as ei:
+            ctx.apply_vx(psi, many, **kw)
+        F.debug_fail_alloc(0)
+        assert ei.value.status == F.FX_ERR_OOM
+        out.zero_()
+        ctx.apply_vx(psi, few, out=out, **kw)
+        torch.cuda.synchronize()
+        hits, misses, _ = ctx.graph_cache_stats()
+        assert (hits, misses) == (1, 3)  # the failed call and this one
+        assert np.array_equal(host(out), ref)
+    finally:
+        F.debug_fail_alloc(0)
+        ctx.close()
+
+
+def test_growth_beyond_the_budget_keeps_the_buffer():
+    psi = dev(synth.make_orbitals(401, N3, L3, 6))
+    phi = dev(synth.random_grid_vectors(402, N3, 200).astype(np.complex64))
+    kw = dict(n=N3, L=L3, kernel="hse", omega=0.106)
+
+    def make(budget):
+        ctx = Context(0, hbm_budget_bytes=budget)
+        ace = ctx.build_ace(psi, **kw)
+        out = torch.empty((2,) + N3, dtype=torch.complex64, device="cuda")
+        ace.apply(phi[:2], prec="ace_fp64", out=out)
+        return ctx, ace, out
+
+    ctx, ace, _ = make(0)
+    peak = ctx.memory()[1]
+    ace.free()
+    ctx.close()
+    # room for two right-hand sides but not for the 44 MB that 200 widen to
+    ctx, ace, out = make(peak + (8 << 20))
+    ctx.graph_cache(4)
+    ace.apply(phi[:2], prec="ace_fp64", out=out)
+    ref = host(out)
+    assert ctx.graph_cache_stats()[:2] == (0, 1)
+    with pytest.raises(F.FockError) as ei:
+        ace.apply(phi, prec="ace_fp64")
+    assert ei.value.status == F.FX_ERR_OOM
+    out.zero_()
+    ace.apply(phi[:2], prec="ace_fp64", out=out)
+    torch.cuda.synchronize()
+    assert ctx.graph_cache_stats()[:2] == (1, 2)
+    assert np.array_equal(host(out), ref)
+    ace.free()
+    ctx.close()
