@@ -145,8 +145,14 @@ fx_status fx_memory(const fx_ctx* ctx, size_t* in_use, size_t* peak);
  *       the same pointer as psi (then phi_k = psi_k for k < n_phi).
  * out:  device, n_phi columns, stride ld_out, dtype out_dtype; overwritten.
  * prec: FX_PREC_FP64, FX_PREC_FP32 or FX_PREC_FP32_ACC64.  The j-sum runs in
- *       ascending j in the accumulation precision, so results are bitwise
- *       repeatable and independent of how the pairs are batched.
+ *       the accumulation precision and in a fixed order: ascending j, or, with
+ *       S > 1 sum groups (fx_vx_config.c_split; by itself on small grids and
+ *       grids off the specialised edges), ascending j within each of S
+ *       interleaved groups, whose sums are added in order of the group.  S
+ *       depends on the grid and n_psi (and the configuration), not on n_phi
+ *       or on memory, so results are bitwise repeatable and independent of how
+ *       the pairs are batched, of the budget, and of the other targets of the
+ *       call.
  * When phi == psi with n_phi == n_psi and ld_phi == ld_psi on a cubic grid of
  *       edge 24, 48, 72 or 96 (and, for FP64 and FP32, on other grids with
  *       enough orbitals), each unordered pair is solved once (the kernel
@@ -240,16 +246,18 @@ typedef struct fx_vx_config {
                           order, 0-terminated; radices from {2,3,4,6,8,9,12} with
                           product n; an all-zero row is the default schedule */
   int32_t c_split;     /* plane-inverse pass: S sum groups per target (1, 2, 4 or 8;
-                          0 automatic: 1 for phi == psi, else as many as give eight
-                          targets on this grid the resident workgroups, at least four
-                          orbitals each, and two where they are up to a quarter more than
-                          those; 1 if the budget cannot hold the sums).  The terms of
+                          0 automatic: 1 where each unordered pair is solved once, else as
+                          many as give eight targets on this grid the resident
+                          workgroups, at least four orbitals each, and two where they
+                          are up to a quarter more than those).  The terms of
                           orbital j go to group j mod S, each group summed in ascending j,
                           the groups added in order at the end: S times the pass's work
                           items for calls with few targets, at S partial sums per target
-                          of device memory.
-                          The result depends on S (rounding) but not on the batch size
-                          or on which targets share a launch */
+                          of device memory (where a quarter of the budget cannot hold
+                          them, blocks of targets are smaller, or the groups run one
+                          after the other).
+                          The result depends on S (rounding) but not on the batch size,
+                          on memory, or on which targets share a launch */
 } fx_vx_config;
 
 /*

@@ -168,7 +168,9 @@ static int ct_c_variant(const VxArgs& a) {
 // ny nx / R butterflies in its last stage, R the first x radix), with at least
 // four terms each.  The count of targets must not enter, since served requests
 // are merged; the phi == psi form keeps one running sum (its partial sums then
-// need no memory beyond `out`), as does the allocation-free form.
+// need no memory beyond `out`), as does the allocation-free form.  Nor must
+// memory enter: where it is short, blocks shrink or the groups run one after
+// the other (run_batches).
 // 27 orbitals x 11 targets at 32 x 36 x 24: one sum leaves 264 items of 27
 // terms one after the other, 182 us, four groups 71 and 7 to add them; at 64^3
 // two groups gain nothing and their partial sums cost the other passes 130 of
@@ -260,6 +262,19 @@ struct PairPasses {
   }
 };
 
+// A batch of the call `a`: its launch configuration and tables beside what it covers.
+template <typename T>
+static CtBatch<T> make_batch(const VxArgs& a, const GridTables* tb, const cpx<T>* psi, int64_t ld_psi, const cpx<T>* phi,
+                             int64_t ld_phi, cpx<T>* work, int j0, int nj, int k0, int nk, int npairs, int tri,
+                             int jsplit) {
+  CtBatch<T> b{psi, ld_psi, phi, ld_phi, work, j0, nj, k0, nk, npairs, reinterpret_cast<const cpx<T>*>(tb->tw[0]),
+               reinterpret_cast<const T*>(tb->kfold), tb->fold[0], tri, a.a_pipe > 0 ? 1 : 0, ct_b_variant(a),
+               ct_c_variant(a), (a.a_var >= 1 && a.a_var <= 3) ? a.a_var : 0, a.nt_hint != 0 ? 1 : 0, ct_zsplit()};
+  b.segs = a.segs;
+  b.jsplit = jsplit;
+  return b;
+}
+
 // Halved apply for phi == psi (all N targets): each unordered pair {j, k} is
 // solved once, as (min, max), since v_kj = conj(v_jk) for a real, even kernel.
 // Orbitals are cut into blocks of B; block pairs (J <= K) run in ascending
@@ -297,8 +312,6 @@ static fx_status run_halved(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const P
     ld_acc = nr;
     gstride = (int64_t)N * nr;
   }
-  const cpx<T>* tw = reinterpret_cast<const cpx<T>*>(tb->tw[0]);
-  const T* kf = reinterpret_cast<const T*>(tb->kfold);
   const double sz = sizeof(cpx<T>), asz = sizeof(cpx<A>), osz = out_c64 ? 8.0 : 16.0;
   int64_t launches = 0, solves = 0;
   for (int J = 0; J < nblk; ++J) {
@@ -307,9 +320,8 @@ static fx_status run_halved(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const P
       const int k0 = K * B, kb = std::min(B, N - k0);
       const int tri = J == K;
       const int npairs = tri ? jb * (jb + 1) / 2 : jb * kb;
-      CtBatch<T> cb{psi, ld_psi, psi, ld_psi, reinterpret_cast<cpx<T>*>(work), j0, jb, k0, kb, npairs, tw, kf,
-                    tb->fold[0], tri, a.a_pipe > 0 ? 1 : 0, ct_b_variant(a), ct_c_variant(a), (a.a_var >= 1 && a.a_var <= 3) ? a.a_var : 0, a.nt_hint != 0 ? 1 : 0, ct_zsplit()};
-      cb.jsplit = jsplit;
+      const CtBatch<T> cb = make_batch<T>(a, tb, psi, ld_psi, psi, ld_psi, reinterpret_cast<cpx<T>*>(work), j0, jb, k0,
+                                          kb, npairs, tri, jsplit);
       const double vol = (double)npairs * nr * sz;
       int slot;
       FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_FWD, 2.0 * vol, &slot));
@@ -351,6 +363,78 @@ static fx_status run_halved(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const P
   return FX_OK;
 }
 
+// total += x over one target, written to `out` (the total's own column, or the result's)
+template <typename A>
+__global__ void __launch_bounds__(256) k_add_group(const cpx<A>* total, const cpx<A>* x, int64_t nr, void* out,
+                                                   int out_c64) {
+  for (int64_t e = blockIdx.x * (int64_t)256 + threadIdx.x; e < nr; e += (int64_t)gridDim.x * 256) {
+    const cpx<A> v = cadd(total[e], x[e]);
+    if (out_c64)
+      reinterpret_cast<cpx<float>*>(out)[e] = cpx<float>{(float)v.x, (float)v.y};
+    else
+      reinterpret_cast<cpx<double>*>(out)[e] = cpx<double>{(double)v.x, (double)v.y};
+  }
+}
+
+// Sum groups where a quarter of the budget cannot hold a pair volume and the S
+// partial sums of one target: target by target and group by group, a pair at a
+// time, each group's running sum added to the total when it is complete.  The
+// same additions in the same order as with all groups at once, so the same
+// bits, in one partial sum of memory (two where `out` is of another type).
+template <typename T, typename A>
+static fx_status run_groups_in_turn(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const PairPasses<T, A>& pass,
+                                    const GridTables* tb, const cpx<T>* psi, int64_t ld_psi, const cpx<T>* phi,
+                                    int64_t ld_phi, int jsplit, hipStream_t st, VxStats* stats) {
+  const int64_t nr = (int64_t)a.cell->n[0] * a.cell->n[1] * a.cell->n[2];
+  const int out_c64 = a.out_dtype == FX_C64, A_c64 = sizeof(A) == 4;
+  const int nsum = out_c64 == A_c64 ? 1 : 2;
+  const double sz = sizeof(cpx<T>), asz = sizeof(cpx<A>);
+  void* work = nullptr;
+  FX_TRY(ws_get(ctx, ws, "vx_work", (size_t)nr * (nsum * sizeof(cpx<A>) + sizeof(cpx<T>)), &work));
+  cpx<A>* const x = reinterpret_cast<cpx<A>*>(work);
+  cpx<T>* const vol = reinterpret_cast<cpx<T>*>(x + nsum * nr);
+  const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((nr + 255) / 256, 8 * std::max(ctx->n_cu, 1)));
+  const int groups = std::min(jsplit, a.n_psi);  // (any others are empty)
+  int64_t launches = 0;
+  for (int k = 0; k < a.n_phi; ++k) {
+    char* const col = (char*)a.out + (size_t)k * a.ld_out * dtype_size(a.out_dtype);
+    cpx<A>* const total = nsum == 1 ? reinterpret_cast<cpx<A>*>(col) : x + nr;
+    for (int g = 0; g < groups; ++g) {
+      // (the passes find a target's sum by its column k)
+      CtAcc<A> ca{(g ? x : total) - k * nr, nr, 1, a.out, a.ld_out, out_c64, 0};
+      int slot;
+      for (int j = g; j < a.n_psi; j += jsplit, ca.first = 0) {
+        const CtBatch<T> cb = make_batch<T>(a, tb, psi, ld_psi, phi, ld_phi, vol, j, 1, k, 1, 1, 0, 1);
+        FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_FWD, 2.0 * nr * sz, &slot));
+        FX_TRY(pass.a(cb));
+        FX_TRY(prof_end(ctx, st, slot));
+        FX_TRY(prof_begin(ctx, st, FX_K_VX_PENCIL_Z, 2.0 * nr * sz, &slot));
+        FX_TRY(pass.b(cb));
+        FX_TRY(prof_end(ctx, st, slot));
+        FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_INV, nr * (2.0 * sz + (ca.first ? asz : 2.0 * asz)), &slot));
+        FX_TRY(pass.c(cb, ca, 0));
+        FX_TRY(prof_end(ctx, st, slot));
+        launches += 3;
+      }
+      if (g == 0) continue;
+      const bool end = g == groups - 1;
+      FX_TRY(prof_begin(ctx, st, FX_K_REDUCE, 3.0 * nr * asz, &slot));
+      hipLaunchKernelGGL((k_add_group<A>), dim3(blocks), dim3(256), 0, st, (const cpx<A>*)total, (const cpx<A>*)x, nr,
+                         end ? (void*)col : (void*)total, end ? out_c64 : A_c64);
+      FX_LAUNCH_CHECK();
+      FX_TRY(prof_end(ctx, st, slot));
+      ++launches;
+    }
+  }
+  if (stats) {
+    stats->nk = 1;
+    stats->nj = 1;
+    stats->launches = launches;
+    stats->solves = (int64_t)a.n_psi * a.n_phi;
+  }
+  return FX_OK;
+}
+
 template <typename T, typename A>
 static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const GridTables* tb,
                              const cpx<T>* psi, int64_t ld_psi, const cpx<T>* phi, int64_t ld_phi, hipStream_t st,
@@ -377,42 +461,62 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
   const bool square = psi == phi && ld_psi == ld_phi && a.n_psi == a.n_phi;
   if (square && a.halve != 0 && (use_ct || a.halve > 0 || gen_halved(a, g)))
     return run_halved<T, A>(ctx, ws, a, pass, tb, psi, ld_psi, pairs_cap, st, stats);
+  const bool out_c64 = a.out_dtype == FX_C64;
+  const bool out_is_A = (sizeof(A) == 8) == !out_c64;
+  const int jsplit = a.n_psi > 1 ? ct_jsplit(a, g, false) : 1;
+  // (a multiple of 256, so that the pair volumes behind them are aligned)
+  const size_t sum_bytes = jsplit > 1 ? ((size_t)jsplit * nr * sizeof(cpx<A>) + 255) & ~(size_t)255 : 0;
   // Batch shape: up to 16 orbitals per batch first (the plane-inverse pass
   // reads and writes its partial sums once per batch), then as many targets
   // as fit, balanced over the target blocks, then any leftover capacity
-  // back to orbitals.
-  int nj = (int)std::min<int64_t>(a.n_psi, std::min<int64_t>(16, pairs_cap));
-  if (a.force_nj > 0) nj = std::min(nj, a.force_nj);
-  const int64_t nk_max = std::max<int64_t>(1, pairs_cap / nj);
-  const int64_t kblocks = (a.n_phi + nk_max - 1) / nk_max;
-  const int nk = (int)((a.n_phi + kblocks - 1) / kblocks);
-  if (a.force_nj <= 0) nj = (int)std::min<int64_t>(a.n_psi, std::max<int64_t>(nj, pairs_cap / nk));
+  // back to orbitals.  With sum groups a target also takes sum_bytes of `room`.
+  int nj = 0, nk = 0;
+  const auto shape = [&](size_t room) {
+    nj = (int)std::min<int64_t>(a.n_psi, std::min<int64_t>(16, pairs_cap));
+    if (sum_bytes) nj = (int)std::min<int64_t>(nj, (int64_t)((room - sum_bytes) / pair_bytes));
+    if (a.force_nj > 0) nj = std::min(nj, a.force_nj);
+    int64_t nk_max = std::max<int64_t>(1, pairs_cap / nj);
+    if (sum_bytes) nk_max = std::min<int64_t>(nk_max, (int64_t)(room / (nj * pair_bytes + sum_bytes)));
+    const int64_t kblocks = (a.n_phi + nk_max - 1) / nk_max;
+    nk = (int)((a.n_phi + kblocks - 1) / kblocks);
+    if (a.force_nj > 0) return;
+    int64_t pairs = pairs_cap;
+    if (sum_bytes) pairs = std::min<int64_t>(pairs, (int64_t)((room - nk * sum_bytes) / pair_bytes));
+    nj = (int)std::min<int64_t>(a.n_psi, std::max<int64_t>(nj, pairs / nk));
+  };
+  // The groups' partial sums of a block of targets lie before its pair volumes in
+  // the work buffer.  Where the two do not fit a quarter of the budget, what is
+  // left of it, or under capture the buffer that is there, a block has fewer
+  // targets or orbitals, never fewer groups: the bits do not depend on memory.
+  // (With less left than the pairs alone need the request stands, and is
+  // FX_ERR_OOM: a server then hands back idle workspaces.)
+  if (jsplit > 1) {
+    const auto it = ws->bufs.find("vx_work");
+    const size_t have = it == ws->bufs.end() ? 0 : it->second.bytes, left = ctx->budget - ctx->in_use + have;
+    const size_t least = (size_t)std::min<int64_t>(pairs_cap, (int64_t)a.n_psi * a.n_phi) * pair_bytes;
+    size_t room = ctx->budget / 4;
+    if (ctx->capturing)
+      room = std::min(room, have);
+    else if (least <= left)
+      room = std::min(room, left);
+    if (sum_bytes + pair_bytes > room)
+      return run_groups_in_turn<T, A>(ctx, ws, a, pass, tb, psi, ld_psi, phi, ld_phi, jsplit, st, stats);
+    shape(room);
+  } else {
+    shape(0);
+  }
+  const size_t sums = nk * sum_bytes;
   void* work = nullptr;
-  FX_TRY(ws_get(ctx, ws, "vx_work", (size_t)nk * nj * pair_bytes, &work));
-  const bool out_c64 = a.out_dtype == FX_C64;
-  const bool out_is_A = (sizeof(A) == 8) == !out_c64;
+  FX_TRY(ws_get(ctx, ws, "vx_work", sums + (size_t)nk * nj * pair_bytes, &work));
+  cpx<T>* const volumes = reinterpret_cast<cpx<T>*>((char*)work + sums);
   const bool multi_j = nj < a.n_psi;
   cpx<A>* acc = nullptr;
   int64_t ld_acc = 0, gstride = 0;
-  int jsplit = ct_jsplit(a, g, false);
   if (jsplit > 1) {
-    // the groups' partial sums of a block of targets, added into out after its
-    // last batch; a budget that cannot hold them gets one sum (where the groups
-    // were not asked for)
-    void* p = nullptr;
-    const fx_status s = ws_get(ctx, ws, "vx_acc", (size_t)jsplit * nk * nr * sizeof(cpx<A>), &p);
-    if (s == FX_ERR_OOM && !a.c_split) {
-      clear_error();
-      jsplit = 1;
-    } else if (s != FX_OK) {
-      return s;
-    }
-    acc = reinterpret_cast<cpx<A>*>(p);
+    // added into out after a block's last batch
+    acc = reinterpret_cast<cpx<A>*>(work);
     ld_acc = nr;
     gstride = (int64_t)nk * nr;
-  }
-  if (jsplit > 1) {
-    // nothing to carry in out
   } else if (a.add) {
     // the one batch of each target starts from the caller's columns
     if (multi_j || sizeof(A) != 8) FX_FAIL(FX_ERR_INVALID, "a start value needs one orbital and FP64 sums");
@@ -429,9 +533,6 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
       ld_acc = nr;
     }
   }
-  const cpx<T>* twx = reinterpret_cast<const cpx<T>*>(tb->tw[0]);
-  const T* kf = reinterpret_cast<const T*>(tb->kfold);
-
   int64_t launches = 0;
   for (int k0 = 0; k0 < a.n_phi; k0 += nk) {
     const int kb = std::min(nk, a.n_phi - k0);
@@ -448,8 +549,8 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
                           ((first ? 0.0 : (double)sizeof(cpx<A>)) +
                            (last ? (out_c64 ? 8.0 : 16.0) : (double)sizeof(cpx<A>)));
       int slot;
-      CtBatch<T> cb{psi, ld_psi, phi, ld_phi, reinterpret_cast<cpx<T>*>(work), j0, jb, k0, kb, npairs, twx, kf,
-                    tb->fold[0], 0, a.a_pipe > 0 ? 1 : 0, ct_b_variant(a), ct_c_variant(a), (a.a_var >= 1 && a.a_var <= 3) ? a.a_var : 0, a.nt_hint != 0 ? 1 : 0, ct_zsplit(), a.segs, jsplit};
+      const CtBatch<T> cb =
+          make_batch<T>(a, tb, psi, ld_psi, phi, ld_phi, volumes, j0, jb, k0, kb, npairs, 0, jsplit);
       CtAcc<A> ca{jsplit > 1 ? acc - (int64_t)k0 * ld_acc : acc, ld_acc, first, a.out, a.ld_out, out_c64 ? 1 : 0,
                   jsplit > 1 ? 0 : last, gstride};
       FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_FWD, 2.0 * vol, &slot));
