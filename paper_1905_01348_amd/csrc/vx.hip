@@ -42,7 +42,8 @@ __global__ void __launch_bounds__(256) k_convert(const cpx<TI>* __restrict__ in0
 // spans, a workgroup each, and one workgroup adds all the spans' sums: with a
 // workgroup per column and one thread adding the columns, 16 columns at 24^3
 // took 16.6 + 4.5 us, 85 at 48^3 207 + 9 us; now 4.7 + 4.0 and 53 + 8 us (4.2
-// TB/s).  Scratch memory that cannot hold the spans' sums gets one per column.
+// TB/s).  The scratch region of the allocation-free form gets one span per column
+// where it cannot hold more.
 static int ex_parts(int64_t nr) { return (int)std::min<int64_t>(64, std::max<int64_t>(1, nr / 2048)); }
 
 __device__ inline double block_sum256(double v) {
@@ -765,14 +766,10 @@ fx_status vx_apply(fx_ctx* ctx, Workspace* ws, const VxArgs& a_in, hipStream_t s
                                       st, stats)));
   }
   if (a.ex_dev) {
+    // the spans' sums in the work buffer, which the passes no longer need: no
+    // allocation whose failure could change their number, and with it the bits
     void* part = nullptr;
-    fx_status s = ws_get(ctx, ws, "vx_expart", (size_t)a.n_phi * parts * sizeof(double), &part);
-    if (s == FX_ERR_OOM && parts > 1) {
-      clear_error();
-      parts = 1;
-      s = ws_get(ctx, ws, "vx_expart", (size_t)a.n_phi * sizeof(double), &part);
-    }
-    FX_TRY(s);
+    FX_TRY(ws_get(ctx, ws, "vx_work", (size_t)a.n_phi * parts * sizeof(double), &part));
     const bool p64 = a.in_dtype == FX_C128, o64 = a.out_dtype == FX_C128;
     dim3 grid((unsigned)(a.n_phi * parts)), blk(256);
     if (p64 && o64)

@@ -3,7 +3,8 @@
 A buffer that has to grow is freed before the larger one is allocated; a graph
 captured before uses its address, so the graph is stale from the moment of the
 free, also where the larger allocation then fails.  A growth that the budget
-refuses leaves the buffer, and the graphs that use it, as they are.
+refuses leaves the buffer, and the graphs that use it, as they are.  E_X needs
+no memory beside the applied operator's, so its bits do not depend on memory.
 """
 import numpy as np
 import pytest
@@ -80,3 +81,22 @@ def test_growth_beyond_the_budget_keeps_the_buffer():
     assert np.array_equal(host(out), ref)
     ace.free()
     ctx.close()
+
+
+def test_energy_takes_no_memory_of_its_own():
+    psi = dev(synth.random_grid_vectors(403, N3, 16))
+    kw = dict(n=N3, L=L3, kernel="coulomb", prec="fp64")
+    ref = Context(0)
+    ctx = Context(0)
+    try:
+        for k in range(1, 17):  # the first k columns (psi itself, so that E_X is defined)
+            _, ex = ref.apply_vx(psi, psi[:k], energy=True, **kw)
+            ctx.apply_vx(psi, psi[:k], **kw)
+            F.debug_fail_alloc(1)  # no allocation may be left for the energy
+            _, got = ctx.apply_vx(psi, psi[:k], energy=True, **kw)
+            F.debug_fail_alloc(0)
+            assert float(got) == float(ex), k
+    finally:
+        F.debug_fail_alloc(0)
+        ref.close()
+        ctx.close()
