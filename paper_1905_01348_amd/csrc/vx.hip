@@ -472,26 +472,35 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
   // as fit, balanced over the target blocks, then any leftover capacity
   // back to orbitals.  With sum groups a target also takes sum_bytes of `room`.
   int nj = 0, nk = 0;
-  const auto shape = [&](size_t room) {
+  const auto shape = [&](size_t room) {  // (0: without the groups' sums)
     nj = (int)std::min<int64_t>(a.n_psi, std::min<int64_t>(16, pairs_cap));
-    if (sum_bytes) nj = (int)std::min<int64_t>(nj, (int64_t)((room - sum_bytes) / pair_bytes));
+    if (room) nj = (int)std::min<int64_t>(nj, (int64_t)((room - sum_bytes) / pair_bytes));
     if (a.force_nj > 0) nj = std::min(nj, a.force_nj);
     int64_t nk_max = std::max<int64_t>(1, pairs_cap / nj);
-    if (sum_bytes) nk_max = std::min<int64_t>(nk_max, (int64_t)(room / (nj * pair_bytes + sum_bytes)));
+    if (room) nk_max = std::min<int64_t>(nk_max, (int64_t)(room / (nj * pair_bytes + sum_bytes)));
     const int64_t kblocks = (a.n_phi + nk_max - 1) / nk_max;
     nk = (int)((a.n_phi + kblocks - 1) / kblocks);
     if (a.force_nj > 0) return;
     int64_t pairs = pairs_cap;
-    if (sum_bytes) pairs = std::min<int64_t>(pairs, (int64_t)((room - nk * sum_bytes) / pair_bytes));
+    if (room) pairs = std::min<int64_t>(pairs, (int64_t)((room - nk * sum_bytes) / pair_bytes));
     nj = (int)std::min<int64_t>(a.n_psi, std::max<int64_t>(nj, pairs / nk));
   };
+  // Groups in rounds (ROUNDS of k_pass_c_ct) where all orbitals fit one batch and
+  // the targets' planes alone occupy half the resident workgroups (24^3: 32
+  // targets, where both forms take the same time).
+  int rounds = 0;
+  if (jsplit > 1 && use_ct && ct_rounds_supported(g.nx, ct_c_variant(a)) && a.n_psi >= jsplit) {
+    shape(0);
+    const int waves = (g.ny * g.ax.st[0].nb + 63) / 64;
+    rounds = nj == a.n_psi && 2 * (int64_t)nk * g.nz >= 256 * std::max(1, 12 / waves);
+  }
   // The groups' partial sums of a block of targets lie before its pair volumes in
   // the work buffer.  Where the two do not fit a quarter of the budget, what is
   // left of it, or under capture the buffer that is there, a block has fewer
   // targets or orbitals, never fewer groups: the bits do not depend on memory.
   // (With less left than the pairs alone need the request stands, and is
   // FX_ERR_OOM: a server then hands back idle workspaces.)
-  if (jsplit > 1) {
+  if (jsplit > 1 && !rounds) {
     const auto it = ws->bufs.find("vx_work");
     const size_t have = it == ws->bufs.end() ? 0 : it->second.bytes, left = ctx->budget - ctx->in_use + have;
     const size_t least = (size_t)std::min<int64_t>(pairs_cap, (int64_t)a.n_psi * a.n_phi) * pair_bytes;
@@ -503,17 +512,18 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
     if (sum_bytes + pair_bytes > room)
       return run_groups_in_turn<T, A>(ctx, ws, a, pass, tb, psi, ld_psi, phi, ld_phi, jsplit, st, stats);
     shape(room);
-  } else {
+  } else if (!rounds) {
     shape(0);
   }
-  const size_t sums = nk * sum_bytes;
+  const size_t sums = rounds ? 0 : nk * sum_bytes;
   void* work = nullptr;
   FX_TRY(ws_get(ctx, ws, "vx_work", sums + (size_t)nk * nj * pair_bytes, &work));
   cpx<T>* const volumes = reinterpret_cast<cpx<T>*>((char*)work + sums);
   const bool multi_j = nj < a.n_psi;
   cpx<A>* acc = nullptr;
   int64_t ld_acc = 0, gstride = 0;
-  if (jsplit > 1) {
+  const bool grouped = jsplit > 1 && !rounds;  // partial sums in memory
+  if (grouped) {
     // added into out after a block's last batch
     acc = reinterpret_cast<cpx<A>*>(work);
     ld_acc = nr;
@@ -550,10 +560,10 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
                           ((first ? 0.0 : (double)sizeof(cpx<A>)) +
                            (last ? (out_c64 ? 8.0 : 16.0) : (double)sizeof(cpx<A>)));
       int slot;
-      const CtBatch<T> cb =
-          make_batch<T>(a, tb, psi, ld_psi, phi, ld_phi, volumes, j0, jb, k0, kb, npairs, 0, jsplit);
-      CtAcc<A> ca{jsplit > 1 ? acc - (int64_t)k0 * ld_acc : acc, ld_acc, first, a.out, a.ld_out, out_c64 ? 1 : 0,
-                  jsplit > 1 ? 0 : last, gstride};
+      CtBatch<T> cb = make_batch<T>(a, tb, psi, ld_psi, phi, ld_phi, volumes, j0, jb, k0, kb, npairs, 0, jsplit);
+      cb.rounds = rounds;
+      CtAcc<A> ca{grouped ? acc - (int64_t)k0 * ld_acc : acc, ld_acc, first, a.out, a.ld_out, out_c64 ? 1 : 0,
+                  grouped ? 0 : last, gstride};
       FX_TRY(prof_begin(ctx, st, FX_K_VX_PLANE_FWD, 2.0 * vol, &slot));
       FX_TRY(pass.a(cb));
       FX_TRY(prof_end(ctx, st, slot));
@@ -564,7 +574,7 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
       FX_TRY(pass.c(cb, ca, 0));
       FX_TRY(prof_end(ctx, st, slot));
       launches += 3;
-      if (jsplit > 1 && last) {
+      if (grouped && last) {
         const double osz = out_c64 ? 8.0 : 16.0;
         FX_TRY(prof_begin(ctx, st, FX_K_REDUCE, (double)kb * nr * (jsplit * sizeof(cpx<A>) + osz), &slot));
         FX_TRY(combine_groups<A>(ctx, st, ca.acc, gstride, ld_acc, jsplit, k0, kb, nr, a.out, a.ld_out, out_c64 ? 1 : 0));

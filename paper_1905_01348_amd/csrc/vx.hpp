@@ -120,10 +120,12 @@ struct CtBatch {
                     // wave-level form)
   TrajSegs segs;    // per-target orbital blocks (multi-trajectory launches; n == 0: psi for all)
   int jsplit = 1;   // plane-inverse pass: terms of orbital j go to sum group j mod jsplit
+  int rounds = 0;   // the groups of a target one after the other, added in registers (needs all orbitals in the
+                    // batch, ct_rounds_supported, and one role)
 };
-// Partial sums of the plane-inverse pass.  With jsplit groups, group g of
-// target t lives at acc + g * gstride + t * ld_acc and `last` is never set:
-// the groups are added afterwards (vx_combine_groups).
+// Partial sums of the plane-inverse pass.  With jsplit groups (and no rounds),
+// group g of target t lives at acc + g * gstride + t * ld_acc and `last` is
+// never set: the groups are added afterwards (combine_groups).
 template <typename A>
 struct CtAcc {
   cpx<A>* acc;
@@ -135,6 +137,8 @@ struct CtAcc {
   int64_t gstride = 0;
 };
 bool ct_supported(const fx_cell* cell);
+// Whether the specialised plane-inverse form c_var of edge n can take the sum groups in rounds.
+bool ct_rounds_supported(int n, int c_var);
 template <typename T>
 fx_status ct_pass_a(fx_ctx* ctx, hipStream_t st, int n, const CtBatch<T>& b);
 template <typename T>

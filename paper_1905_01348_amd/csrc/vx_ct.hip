@@ -348,7 +348,14 @@ struct PassCDouble {
                                                    (FORM == 0 && kBytes <= 40 * 1024));
 };
 
-template <typename T, typename A, int N, bool HALVED, int NT, bool NTS, int FORM>
+// ROUNDS: the sum groups of a target one after the other within an item, added in
+// registers (edge 24, the one specialised edge whose automatic groups are more
+// than one).  A block with targets enough to fill the chip gets the groups' bits
+// without their partial sums in memory, which cost it more than the groups gain
+// (us per apply, FP64, 16 orbitals: 256 targets 923 -> 777, 64 213 -> 196, 32 112
+// -> 111; 64 orbitals, 128 targets 1715 -> 1530).  Only the order of the work
+// differs: a target's bits are those of the groups in memory.
+template <typename T, typename A, int N, bool HALVED, int NT, bool NTS, int FORM, bool ROUNDS = false>
 __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mult, int64_t ld_mult,
                                                                   const cpx<T>* __restrict__ work, int nj, int nk,
                                                                   int tri, int role, int j0, int k0, int nitems,
@@ -368,7 +375,8 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
   const int tid = threadIdx.x;
   for (int i = tid; i < N; i += NT) tw[i] = twg[i];
   __syncthreads();
-  // units: (target tt, sum group g) as tt * jsplit + g
+  static_assert(!ROUNDS || (!HALVED && FORM == 0), "groups in rounds: one role, plain form");
+  // units: (target tt, sum group g) as tt * jsplit + g, or the targets (ROUNDS)
   const ItemMap im = item_map(N, nitems / N, split, gridDim.x, blockIdx.x);
   // terms l = lo, lo + jsplit, ... < hi of target tt in group g: the terms
   // whose orbital m0 + l is g modulo jsplit, in ascending order
@@ -422,8 +430,8 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
   for (int li = im.first; li < im.total; li += im.step) {
     int u, z;
     im.at(li, &u, &z);
-    int tt = u / jsplit;
-    const int g = u - tt * jsplit;
+    int tt = ROUNDS ? u : u / jsplit;
+    const int g = ROUNDS ? 0 : u - tt * jsplit;
     // the roles of this item's target: cj0 .. cj1
     bool cj0 = HALVED && role == 1, cj1 = HALVED && role != 0;
     if (HALVED && role == 2 && !tri) {
@@ -525,10 +533,12 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
       if (!first && (NXY % NT == 0 || e < NXY)) a[i] = accg[t * ld_acc + (size_t)z * NXY + e];
     }
     constexpr int R0 = Plan2<N>::R0;
-    for (int cj = cj0; cj <= (int)cj1; ++cj) {
+    cpx<A> total[ROUNDS ? EPT : 1];
+    // the item's roles, or its target's sum groups
+    for (int cj = cj0, p = 0; ROUNDS ? p < jsplit : cj <= (int)cj1; ROUNDS ? ++p : ++cj) {
       const A sgn = cj ? (A)-1 : (A)1;
       int lo, hi;
-      range(tt, g, cj, &lo, &hi);
+      range(tt, ROUNDS ? p : g, cj, &lo, &hi);
       cpx<T> nx[kIn][R1];  // kAhead
       const auto ahead = [&](int l_) __attribute__((always_inline)) {
         ct_bfly_load<R1, T, N, R1, N, NT, true, N, 1, SX, 1, NTS>(nx, plane_ptr(tt, l_, cj, z), tid);
@@ -633,6 +643,13 @@ __global__ void __launch_bounds__(NT) k_pass_c_ct(const cpx<T>* __restrict__ mul
         else if (!STG)
           __syncthreads();
       }
+      if constexpr (ROUNDS) {  // this group's sum is complete
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+          total[i] = p ? cadd(total[i], a[i]) : a[i];
+          a[i] = p + 1 < jsplit ? cpx<A>{0, 0} : total[i];
+        }
+      }
     }
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
@@ -665,6 +682,8 @@ bool ct_supported(const fx_cell* cell) {
     default: return false;
   }
 }
+
+bool ct_rounds_supported(int n, int c_var) { return n == 24 && c_var != 3 && c_var != 4; }
 
 template <typename K>
 static fx_status ct_prepare(fx_ctx* ctx, K kernel, int nthr, size_t lds, int items, bool persistent, int* grid) {
@@ -793,7 +812,7 @@ constexpr size_t pass_c_lds(bool stg) {
   return ((size_t)N * (N + 1) + N + (stg ? (size_t)N * N : 0)) * sizeof(cpx<T>);
 }
 
-template <typename T, typename A, int N, int NT, int FORM>
+template <typename T, typename A, int N, int NT, int FORM, bool ROUNDS = false>
 static fx_status pass_c_shape(fx_ctx* ctx, hipStream_t st, const CtBatch<T>& b, const CtAcc<A>& c, int role) {
   const size_t lds = PassCDouble<T, N, NT, FORM>::value ? PassCDouble<T, N, NT, FORM>::kBytes
                                                          : pass_c_lds<T, N>(FORM == 1);
@@ -805,8 +824,9 @@ static fx_status pass_c_shape(fx_ctx* ctx, hipStream_t st, const CtBatch<T>& b, 
     return pass_c_shape<T, A, N, NT, FORM>(ctx, st, b, c1, 1);
   }
   const int targets = role == 0 ? b.nk : role == 1 ? b.nj : b.tri ? b.nk : b.nk + b.nj;
-  const int items = targets * b.jsplit * N;
-  auto kern = role ? (b.nts ? k_pass_c_ct<T, A, N, true, NT, true, FORM> : k_pass_c_ct<T, A, N, true, NT, false, FORM>)
+  const int items = targets * (ROUNDS ? 1 : b.jsplit) * N;
+  auto kern = ROUNDS ? (b.nts ? k_pass_c_ct<T, A, N, false, NT, true, FORM, ROUNDS> : k_pass_c_ct<T, A, N, false, NT, false, FORM, ROUNDS>)
+              : role ? (b.nts ? k_pass_c_ct<T, A, N, true, NT, true, FORM> : k_pass_c_ct<T, A, N, true, NT, false, FORM>)
                    : (b.nts ? k_pass_c_ct<T, A, N, false, NT, true, FORM> : k_pass_c_ct<T, A, N, false, NT, false, FORM>);
   int grid = 0;
   FX_TRY(ct_prepare(ctx, kern, NT, lds, items, true, &grid));
@@ -828,6 +848,10 @@ static fx_status pass_c_n(fx_ctx* ctx, hipStream_t st, const CtBatch<T>& b, cons
   constexpr bool kWx = RowStage<T, N, S::NT_C2>::kWave;
   if constexpr (kWx)
     if (b.c_var == 5) return pass_c_shape<T, A, N, S::NT_C2, 2>(ctx, st, b, c, role);
+  if constexpr (N == 24)
+    if (b.rounds)
+      return b.c_var == 1 ? pass_c_shape<T, A, N, S::NT_P, 0, true>(ctx, st, b, c, role)
+                          : pass_c_shape<T, A, N, S::NT_C2, 0, true>(ctx, st, b, c, role);
   if (b.c_var == 3 && kStg) return pass_c_shape<T, A, N, S::NT_C2, kStg ? 1 : 0>(ctx, st, b, c, role);
   if (b.c_var == 4 && kStg) return pass_c_shape<T, A, N, S::NT_P, kStg ? 1 : 0>(ctx, st, b, c, role);
   if (b.c_var == 2 || b.c_var == 3 || b.c_var == 5) return pass_c_shape<T, A, N, S::NT_C2, 0>(ctx, st, b, c, role);

@@ -24,10 +24,10 @@ def _bits(t):
     return host(torch.view_as_real(t))
 
 
-# (grid, orbitals, targets, groups): as many as fill the chip, few orbitals, the most groups, and two where eight
-# targets are a little more than the resident workgroups
+# (grid, orbitals, targets, groups): as many as fill the chip, few orbitals, the most groups, two where eight
+# targets are a little more than the resident workgroups, and a block large enough for the groups in rounds
 @pytest.mark.parametrize("n3,N,R,groups", [((32, 36, 24), 27, 11, 4), ((24, 24, 24), 16, 9, 4), ((24, 24, 24), 7, 3, 1),
-                                           ((9, 8, 27), 33, 70, 8), ((96, 64, 36), 32, 2, 2)])
+                                           ((9, 8, 27), 33, 70, 8), ((96, 64, 36), 32, 2, 2), ((24, 24, 24), 18, 40, 4)])
 @pytest.mark.parametrize("prec", ["fp64", "fp32acc64", "fp32"])
 def test_automatic_groups(n3, N, R, groups, prec, monkeypatch):
     L3 = tuple(0.43 * n for n in n3)
@@ -82,3 +82,23 @@ def test_automatic_groups(n3, N, R, groups, prec, monkeypatch):
             assert np.array_equal(_bits(out), _bits(got)), what
         assert small.graph_cache_stats()[:2] == (1, 1), what
         small.close()
+
+
+@pytest.mark.parametrize("c_variant", [1, 2, 3, 5])
+@pytest.mark.parametrize("prec", ["fp64", "fp32acc64", "fp32"])
+def test_groups_in_rounds_by_variant(c_variant, prec):
+    """24^3: the groups of a block of 40 targets one after the other in registers (the staged form 3: in memory)
+    and those of a few targets in memory give a target the same bits, for a count of orbitals that the groups
+    do not divide."""
+    n3, L3, N, R = (24, 24, 24), (10.26,) * 3, 11, 40
+    cdt = np.complex128 if prec == "fp64" else np.complex64
+    P, Q = dev(synth.random_grid_vectors(82, n3, N).astype(cdt)), dev(synth.random_grid_vectors(83, n3, R).astype(cdt))
+    ctx, kw = Context(0), dict(n=n3, L=L3, kernel="coulomb", prec=prec)
+    for s in (2, 4, 8):
+        ctx.set_vx_config({"kernels": 1, "c_variant": c_variant, "c_split": s}, n=n3, prec=prec)
+        say("rounds", prec, c_variant, s)
+        block, some = ctx.apply_vx(P, Q, **kw), ctx.apply_vx(P, Q[7:12], **kw)
+        assert np.array_equal(_bits(block)[7:12], _bits(some)), s
+    ref = oracle.apply_vx(host(P), host(Q[7:9]), n3, L3, "coulomb")
+    assert rel_err(host(block[7:9]), ref) <= TOL[prec]
+    ctx.close()
