@@ -206,6 +206,143 @@ __global__ void __launch_bounds__(kGenCThreads, (sizeof(T) == 4 && R * IT <= 8 ?
   }
 }
 
+constexpr int kFlatThreads = 512;  // launch bound of the form with a thread per plane value
+
+// Item li: plane z of output column t = (first column of its block) + tt, sum
+// group gr, roles cj0 .. cj1.
+struct GenItem {
+  int t, tt, gr, z;
+  bool cj0, cj1;
+};
+__device__ inline GenItem gen_item(const ItemMap& im, int li, int jsplit, int role, int tri, int nk, int j0, int k0) {
+  GenItem m;
+  int u;
+  im.at(li, &u, &m.z);
+  m.tt = u / jsplit;
+  m.gr = u - m.tt * jsplit;
+  m.cj0 = role == 1;
+  m.cj1 = role != 0;
+  if (role == 2 && !tri) {
+    m.cj0 = m.cj1 = m.tt >= nk;
+    if (m.cj0) m.tt -= nk;
+  }
+  m.t = (m.cj1 ? j0 : k0) + m.tt;
+  return m;
+}
+// Its terms in role cj: lo, lo + jsplit, ... < hi, those whose orbital m0 + l is gr mod jsplit.
+__device__ inline void gen_terms(const GenItem& m, int cj, int jsplit, int tri, int nj, int nk, int m0, int* lo, int* hi) {
+  const int l = cj ? (tri ? m.tt + 1 : 0) : 0;
+  *hi = cj ? nk : (tri ? m.tt + 1 : nj);
+  const int r = (m0 + l) % jsplit;
+  *lo = l + (m.gr >= r ? m.gr - r : m.gr - r + jsplit);
+}
+template <typename A>
+__device__ inline void gen_store(void* out, size_t off, int out_c64, cpx<A> v) {
+  if (out_c64)
+    reinterpret_cast<cpx<float>*>(out)[off] = cpx<float>{(float)v.x, (float)v.y};
+  else
+    reinterpret_cast<cpx<double>*>(out)[off] = cpx<double>{(double)v.x, (double)v.y};
+}
+
+// The same for an x axis of one stage (edges up to 12) where a butterfly per
+// thread leaves most of a wave idle: the last stage, the loads and the sums would
+// fall to one thread per row (8 x 8 plane: 8 threads of 64), with the 12 values of
+// a radix-12 row in FP64 spilling 400 bytes.  Here a thread owns EPT plane values
+// from the load of the work plane to the sums, which it takes from LDS after the
+// last stage, and loads the next term's values while the current one is
+// transformed (gen_c_flat has the rule).
+template <typename T, typename A, int EPT>
+__global__ void __launch_bounds__(kFlatThreads, 4)
+    k_gen_c_flat(const cpx<T>* __restrict__ mult, int64_t ld_mult, const cpx<T>* __restrict__ work, int nj, int nk,
+                 int tri, int role, int j0, int k0, int units, cpx<A>* acc, int64_t ld_acc, int first_in, void* out,
+                 int64_t ld_out, int out_c64, int last_in, PassGeom g, const cpx<T>* __restrict__ twx_g,
+                 const cpx<T>* __restrict__ twy_g, int split, TrajSegs segs, int jsplit, int64_t gstride) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cpx<T>* s = reinterpret_cast<cpx<T>*>(smem_raw);  // two planes, alternating by term
+  const int plane = plane_lds_elems(g);
+  cpx<T>* twx = s + 2 * plane;
+  cpx<T>* twy = twx + g.nx;
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  for (int i = tid; i < g.nx; i += nthr) twx[i] = twx_g[i];
+  for (int i = tid; i < g.ny; i += nthr) twy[i] = twy_g[i];
+  __syncthreads();
+  const int nxy = g.nx * g.ny;
+  const size_t nr = (size_t)nxy * g.nz;
+  int at[EPT];  // where the thread's values lie in LDS
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const int e = tid + i * nthr;
+    at[i] = e + fdiv(e, g.dnx) * (g.sx - g.nx);
+  }
+  const auto owns = [&](int i) __attribute__((always_inline)) { return tid + i * nthr < nxy; };
+  const ItemMap im = item_map(g.nz, units, split, gridDim.x, blockIdx.x);
+  int par = 0;
+  for (int li = im.first; li < im.total; li += im.step) {
+    const GenItem m = gen_item(im, li, jsplit, role, tri, nk, j0, k0);
+    const int first = first_in && !m.cj0, last = last_in && (m.cj1 || role == 0);
+    cpx<A>* accg = acc + m.gr * gstride + m.t * ld_acc + (size_t)m.z * nxy;
+    cpx<A> a[EPT];
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+      a[i] = cpx<A>{0, 0};
+      if (!first && owns(i)) a[i] = accg[tid + i * nthr];
+    }
+    for (int cj = m.cj0; cj <= (int)m.cj1; ++cj) {
+      const A sgn = cj ? (A)-1 : (A)1;
+      const int m0 = cj ? k0 : j0;
+      int lo, hi;
+      gen_terms(m, cj, jsplit, tri, nj, nk, m0, &lo, &hi);
+      cpx<T> next[EPT];
+      const auto ahead = [&](int l) __attribute__((always_inline)) {
+        const int pl = cj ? plane_of(m.tt, l, nj, tri) : plane_of(l, m.tt, nj, tri);
+        const cpx<T>* p = work + (size_t)pl * nr + (size_t)m.z * nxy;
+#pragma unroll
+        for (int i = 0; i < EPT; ++i)
+          if (owns(i)) next[i] = g_load<true>(p + tid + i * nthr);
+      };
+      if (lo < hi) ahead(lo);
+      for (int l = lo; l < hi; l += jsplit) {
+        cpx<T>* sl = s + (par ? plane : 0);
+#pragma unroll
+        for (int i = 0; i < EPT; ++i)
+          if (owns(i)) sl[at[i]] = next[i];
+        __syncthreads();
+        const cpx<T>* pm = seg_psi<T>(segs, mult, m.t) + (int64_t)(m0 + l) * ld_mult + (size_t)m.z * nxy;
+        cpx<T> vp[EPT];
+#pragma unroll
+        for (int i = 0; i < EPT; ++i)
+          if (owns(i)) vp[i] = pm[tid + i * nthr];
+        if (l + jsplit < hi) ahead(l + jsplit);
+        const Span<T> rows = lds_rows(sl, g), cols = lds_cols(sl, g);
+        for (int st = g.ay.nst - 1; st >= 0; --st) {
+          run_stage<false, false, false, T>(cols, cols, g.ay.st[st], plane_cols(g), twy, tid, nthr);
+          __syncthreads();
+        }
+        for (int st = g.ax.nst - 1; st >= 0; --st) {
+          run_stage<false, false, false, T>(rows, rows, g.ax.st[st], plane_rows(g), twx, tid, nthr);
+          __syncthreads();
+        }
+#pragma unroll
+        for (int i = 0; i < EPT; ++i)
+          if (owns(i)) {
+            const cpx<T> v = sl[at[i]];
+            a[i] = cfma(a[i], cpx<A>{(A)vp[i].x, (A)vp[i].y}, cpx<A>{(A)v.x, sgn * (A)v.y});
+          }
+        par ^= 1;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+      const int e = tid + i * nthr;
+      if (!owns(i)) continue;
+      if (!last)
+        accg[e] = a[i];
+      else
+        gen_store(out, m.t * ld_out + (size_t)m.z * nxy + e, out_c64, a[i]);
+    }
+  }
+}
+
 // ---- host side ------------------------------------------------------------------
 static int round64(int v) { return (v + 63) / 64 * 64; }
 
@@ -318,6 +455,35 @@ static fx_status gen_c_launch(fx_ctx* ctx, hipStream_t st, const PassGeom& g, co
   return FX_OK;
 }
 
+template <typename T, typename A, int EPT>
+static fx_status gen_c_flat_launch(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb,
+                                   const CtBatch<T>& b, const CtAcc<A>& c, int role) {
+  const size_t lds = (2 * (size_t)plane_lds_elems(g) + g.nx + g.ny) * sizeof(cpx<T>);
+  const int nthr = round64((g.nx * g.ny + EPT - 1) / EPT);
+  const int units = (role == 0 ? b.nk : role == 1 ? b.nj : b.tri ? b.nk : b.nk + b.nj) * b.jsplit;
+  const auto kern = k_gen_c_flat<T, A, EPT>;
+  int grid = 0;
+  FX_TRY(gen_grid(ctx, kern, nthr, lds, (int64_t)units * g.nz, &grid));
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(nthr), lds, st, role ? b.phi : b.psi, role ? b.ld_phi : b.ld_psi,
+                     (const cpx<T>*)b.work, b.nj, b.nk, b.tri, role, b.j0, b.k0, units, c.acc, c.ld_acc, c.first, c.out,
+                     c.ld_out, c.out_c64, c.last, g, (const cpx<T>*)tb->tw[0], (const cpx<T>*)tb->tw[1],
+                     item_split(g.nz, units, (b.zsplit >> 1) & 1, grid), role ? TrajSegs{} : b.segs, b.jsplit,
+                     c.gstride);
+  FX_LAUNCH_CHECK();
+  return FX_OK;
+}
+
+// The form with a thread per plane value: planes of at most 12 rows and 108 values
+// (us per apply, 16 orbitals on 64 targets, a butterfly per thread against this
+// one: 8 x 8 x 96 FP64 283 / 219, FP32 with FP64 sums 192 / 161; 12 x 9 x 9 98 / 57
+// and 53 / 46; past 108 values FP32 loses, 8 x 16 x 16 63 / 66, 9 x 18 x 18 84 /
+// 98, and so does FP64, 8 x 24 x 24 131 / 145), and radix-12 rows in FP64 whatever
+// their number (12^3, 32 on 8: 54 / 36; 12 x 36 x 36 598 / 462; 12 x 96 x 4 215 /
+// 168; FP32 keeps the butterfly: 282 / 349, 114 / 123).
+static bool gen_c_flat(const PassGeom& g, size_t real_bytes) {
+  return g.ax.nst == 1 && ((g.ny <= 12 && g.nx * g.ny <= 108) || (real_bytes == 8 && g.nx == 12));
+}
+
 // IT > 1 only where the first x radix of a tuned schedule leaves more
 // butterflies than one per thread of the launch bound.
 template <typename T, typename A, int R, int ITM>
@@ -338,6 +504,13 @@ static fx_status gen_c_radix(fx_ctx* ctx, hipStream_t st, const PassGeom& g, con
 template <typename T, typename A>
 fx_status gen_pass_c(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb, const CtBatch<T>& b,
                      const CtAcc<A>& c, int role) {
+  if (gen_c_flat(g, sizeof(T))) {
+    if constexpr (sizeof(T) == 8) {  // up to 12 x 96 values
+      if (g.nx * g.ny > 2 * kFlatThreads) return gen_c_flat_launch<T, A, 3>(ctx, st, g, tb, b, c, role);
+      if (g.nx * g.ny > kFlatThreads) return gen_c_flat_launch<T, A, 2>(ctx, st, g, tb, b, c, role);
+    }
+    return gen_c_flat_launch<T, A, 1>(ctx, st, g, tb, b, c, role);
+  }
   switch (g.ax.st[0].R) {
     // most butterflies of a stage: 96 rows x 96 / R (radix 9: x 9), so
     // ITM = ceil(9216 / (768 R))

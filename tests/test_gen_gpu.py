@@ -75,3 +75,10 @@ def test_several_butterflies_per_thread(ctx, n3, radix):
         got = host(ctx.apply_vx(dev(psi), n=n3, L=L3, kernel="coulomb", prec=prec))
         ctx.set_vx_config(None, n=n3, prec=prec, phi_is_psi=True)
         assert rel_err(got, ref) <= TOL[prec]
+
+
+# x axes of one stage, a thread per plane value: one, two and three values per thread (FP64), the largest plane of
+# both precisions, and planes just past it
+@pytest.mark.parametrize("n3", [(12, 36, 3), (12, 48, 2), (12, 96, 2), (9, 12, 4), (12, 9, 8), (12, 12, 3), (8, 16, 3)])
+def test_one_stage_x_axes(ctx, n3, monkeypatch):
+    test_square_form_and_groups(ctx, n3, monkeypatch)
