@@ -184,6 +184,10 @@ static int ct_jsplit(const VxArgs& a, const PassGeom& g, bool square) {
   if (a.no_alloc || a.add) return 1;
   if (a.c_split == 1 || a.c_split == 2 || a.c_split == 4 || a.c_split == 8) return a.c_split;
   if (square) return 1;
+  // planes of up to 108 points: eight to eleven terms take no longer than the
+  // launch that adds two groups (8^3, 8 orbitals on 8 targets 24 / 27 us; 12
+  // orbitals 30 / 27)
+  if (a.n_psi < 12 && g.nx * g.ny <= 108) return 1;
   const int waves = (g.ny * g.ax.st[0].nb + 63) / 64;
   const int64_t most = std::min<int64_t>(a.n_psi / 4, 256 * std::max(1, 12 / waves) / (8 * g.nz));
   int s = 1;
