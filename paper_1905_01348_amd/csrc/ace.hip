@@ -101,6 +101,10 @@ fx_status ace_build_impl(fx_ctx* ctx, Workspace* ws, const fx_cell* cell, const 
   if ((s = ace_alloc(a, zsz * n * n, &a->L)) != FX_OK) return fail(s);
   if ((s = ws_get(ctx, ws, "ace_Mraw", zsz * n * n, &Mraw)) != FX_OK) return fail(s);
   if ((s = ws_get(ctx, ws, "ace_scal", 64, &scal)) != FX_OK) return fail(s);
+  // (workspaces first: the split product's partial sums take what memory is left)
+  void *dinv = nullptr, *Linv = nullptr;
+  if ((s = chol_workspace(ctx, ws, n, &dinv)) != FX_OK) return fail(s);
+  if ((s = ws_get(ctx, ws, "ace_Linv", zsz * n * n, &Linv)) != FX_OK) return fail(s);
   if ((s = zgemm(ctx, ws, st, 1, 0, n, n, (int)nr, cpx<double>{1, 0}, psi64, ldp, W, nr, cpx<double>{0, 0}, Mraw, n,
                  1, 0, 0, 0, 0)) != FX_OK)
     return fail(s);
@@ -114,8 +118,6 @@ fx_status ace_build_impl(fx_ctx* ctx, Workspace* ws, const fx_cell* cell, const 
   if (ex_dev_out && hipMemcpyAsync(ex_dev_out, ex_dev, sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess)
     return fail(FX_ERR_DEVICE);
   // -M = L L^H
-  void* dinv = nullptr;
-  if ((s = ws_get(ctx, ws, "chol_dinv", chol_dinv_bytes(n), &dinv)) != FX_OK) return fail(s);
   if ((s = zpotrf(ctx, ws, st, n, a->L, n, dinv, info_dev)) != FX_OK) return fail(s);
   double ex = 0.0;
   int info = 0;
@@ -132,8 +134,6 @@ fx_status ace_build_impl(fx_ctx* ctx, Workspace* ws, const fx_cell* cell, const 
     return fail(FX_ERR_NOT_POSDEF);
   }
   // xi = W Linv^H in place of W: the handle keeps that array
-  void* Linv = nullptr;
-  if ((s = ws_get(ctx, ws, "ace_Linv", zsz * n * n, &Linv)) != FX_OK) return fail(s);
   if (hipMemcpyAsync(Linv, a->L, zsz * n * n, hipMemcpyDeviceToDevice, st) != hipSuccess) return fail(FX_ERR_DEVICE);
   if ((s = ztrinv(ctx, ws, st, n, Linv, n, dinv)) != FX_OK) return fail(s);
   if ((s = zmul_upper_inplace(ctx, st, (int)nr, n, W, nr, Linv, n)) != FX_OK) return fail(s);
@@ -183,6 +183,12 @@ fx_status ace_apply_impl(fx_ctx* ctx, Workspace* ws, const fx_ace* ac, const voi
     }
     void* C = nullptr;
     FX_TRY(ws_get(ctx, ws, "acea_C", zsz * n * nphi, &C));
+    void* y = out;
+    int64_t ldy = ld_out;
+    if (out_dtype == FX_C64) {
+      FX_TRY(ws_get(ctx, ws, "acea_y64", zsz * nr * nphi, &y));
+      ldy = nr;
+    }
     // Split count fixed by N_r and n alone, so that a right-hand side's result
     // does not depend on how many share the call: two workgroups per CU
     // for a single tile column (chunks of at least 128).  A split per 8192 points
@@ -195,12 +201,6 @@ fx_status ace_apply_impl(fx_ctx* ctx, Workspace* ws, const fx_ace* ac, const voi
       FX_TRY(zgemm(ctx, ws, st, 1, 0, n, std::min(rb, nphi - r0), (int)nr, cpx<double>{1, 0}, a->xi, nr,
                    (const cpx<double>*)p64 + r0 * ldp, ldp, cpx<double>{0, 0}, (cpx<double>*)C + (int64_t)r0 * n, n, 1,
                    0, 0, 0, nsplit));
-    void* y = out;
-    int64_t ldy = ld_out;
-    if (out_dtype == FX_C64) {
-      FX_TRY(ws_get(ctx, ws, "acea_y64", zsz * nr * nphi, &y));
-      ldy = nr;
-    }
     FX_TRY(zgemm(ctx, ws, st, 0, 0, (int)nr, nphi, n, cpx<double>{-1, 0}, a->xi, nr, C, n, cpx<double>{0, 0}, y, ldy,
                  1, 0, 0, 0, 1));
     if (out_dtype == FX_C64) FX_TRY(convert_cols(y, FX_C128, nr, out, FX_C64, ld_out, nr, nphi, st));

@@ -184,6 +184,11 @@ fx_status note_capture(fx_ctx* ctx, hipStream_t st);
 // (growth waits for the device before freeing the old buffer).  Under graph
 // capture growth is refused with FX_ERR_INVALID.
 fx_status ws_get(fx_ctx* ctx, Workspace* ws, const char* name, size_t bytes, void** out);
+// Bytes that buffer `name` can have: what the budget leaves beside everything
+// else, or under capture the buffer as it is.  For callers that can do the same
+// with less: decided before the allocation, so that an eager call and its
+// capture agree.
+size_t ws_room(const fx_ctx* ctx, const Workspace* ws, const char* name);
 void ws_release(fx_ctx* ctx, Workspace* ws);
 
 // Plan of an FFT axis: n = R[0] * R[1] * ... (at most 4 radices from

@@ -301,6 +301,20 @@ fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, in
   kchunk = (kchunk + ZK - 1) / ZK * ZK;
   nsplit = (K + kchunk - 1) / kchunk;
   z* part = nullptr;
+  if (nsplit > 1 && batch == 1) {
+    // Partial sums that the budget cannot hold: the product in blocks of columns
+    // with the same splits, and so the same bits.
+    const size_t col = sizeof(z) * (size_t)M * nsplit, room = ws_room(ctx, ws, "zgemm_part");
+    if (col * N > room && N > 1) {
+      const int nc = (int)std::max<size_t>(1, room / col);
+      shape.flags &= ~kZgHermitian;  // (a block's columns do not start at the diagonal: all its tiles)
+      for (int n0 = 0; n0 < N; n0 += nc)
+        FX_TRY(zgemm(ctx, ws, st, opa, opb, M, std::min(nc, N - n0), K, alpha, A, lda,
+                     (const z*)B + (opb ? n0 : n0 * ldb), ldb, beta, (z*)C + n0 * ldc, ldc, 1, 0, 0, 0, nsplit, shape,
+                     res));
+      return FX_OK;
+    }
+  }
   if (nsplit > 1) {
     void* p = nullptr;
     FX_TRY(ws_get(ctx, ws, "zgemm_part", sizeof(z) * (size_t)M * N * nsplit * batch, &p));
@@ -470,6 +484,18 @@ __global__ void k_zero_upper(int n, z* A, int64_t lda) {
   }
 }
 
+// the pairs of a level of ztrinv hold s x s each: never more than n x n together
+static fx_status trinv_workspace(fx_ctx* ctx, Workspace* ws, int n, void** T) {
+  *T = nullptr;
+  return n <= CB ? FX_OK : ws_get(ctx, ws, "trinv_T", sizeof(z) * (size_t)n * n, T);
+}
+
+fx_status chol_workspace(fx_ctx* ctx, Workspace* ws, int n, void** dinv) {
+  void* T = nullptr;
+  FX_TRY(trinv_workspace(ctx, ws, n, &T));
+  return ws_get(ctx, ws, "chol_dinv", sizeof(z) * CB * ((n + CB - 1) / CB * CB), dinv);
+}
+
 fx_status zpotrf(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int64_t lda, void* dinv, int* info_dev) {
   z* a = (z*)A;
   for (int k = 0; k < n; k += CB) {
@@ -518,8 +544,8 @@ fx_status ztrinv(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* Av, in
   hipLaunchKernelGGL(k_place_diag, dim3((n + CB - 1) / CB), dim3(256), 0, st, n, A, lda, (const z*)dinv);
   FX_LAUNCH_CHECK();
   if (n <= CB) return FX_OK;
-  void* T = nullptr;  // the pairs of a level hold s x s each: never more than n x n together
-  FX_TRY(ws_get(ctx, ws, "trinv_T", sizeof(z) * (size_t)n * n, &T));
+  void* T = nullptr;
+  FX_TRY(trinv_workspace(ctx, ws, n, &T));
   for (int s = CB; s < n; s *= 2) {
     const int pairs = (n - s + 2 * s - 1) / (2 * s);
     const int64_t step = (int64_t)2 * s * (1 + lda);

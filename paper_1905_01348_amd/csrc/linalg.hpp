@@ -39,9 +39,9 @@ fx_status zgemm(fx_ctx* ctx, Workspace* ws, hipStream_t st, int opa, int opb, in
 // ztrinv.  *info_dev (device int, must start at 0) receives 1 + the first
 // column whose pivot was not positive, or stays 0.
 constexpr int kCholBlock = 64;
-inline size_t chol_dinv_bytes(int n) {
-  return (size_t)16 * kCholBlock * ((n + kCholBlock - 1) / kCholBlock * kCholBlock);
-}
+// Workspaces of zpotrf (*dinv) and ztrinv; got before a split product, whose
+// partial sums take what memory is left.
+fx_status chol_workspace(fx_ctx* ctx, Workspace* ws, int n, void** dinv);
 fx_status zpotrf(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int64_t lda, void* dinv, int* info_dev);
 
 // In-place inverse of the lower triangular n x n factor of zpotrf.

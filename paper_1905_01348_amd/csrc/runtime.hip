@@ -148,6 +148,12 @@ fx_status ws_get(fx_ctx* ctx, Workspace* ws, const char* name, size_t bytes, voi
   return FX_OK;
 }
 
+size_t ws_room(const fx_ctx* ctx, const Workspace* ws, const char* name) {
+  const auto it = ws->bufs.find(name);
+  const size_t have = it == ws->bufs.end() ? 0 : it->second.bytes;
+  return ctx->capturing ? have : ctx->budget - ctx->in_use + have;
+}
+
 void ws_release(fx_ctx* ctx, Workspace* ws) {
   if (!ws->arena)
     for (auto& kv : ws->bufs) ctx_free(ctx, kv.second.ptr, kv.second.bytes);

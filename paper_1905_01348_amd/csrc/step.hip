@@ -161,15 +161,16 @@ static fx_status pt_residual(fx_ctx* ctx, const fx_cell* cell, const fx_kernel* 
   // S = Psi^H (H Psi), N x N, FP64 (split over N_r with a fixed-order reduction)
   void* S = s_out;
   if (!S) FX_TRY(ws_get(ctx, ws, "pt_S", (size_t)16 * n * n, &S));
-  FX_TRY(zgemm(ctx, ws, st, 1, 0, n, n, (int)nr, cpx<double>{1, 0}, p64, ldp, h64, ldh, cpx<double>{0, 0}, S, n, 1, 0,
-               0, 0, 0));
-  // R = Psi - Psi_half + (i dt/2) (H Psi - Psi S), formed where Psi S ends
+  // (workspaces first: the split product's partial sums take what memory is left)
   void* r64 = r;
   int64_t ldr64 = ldr;
   if (dt == FX_C64) {
     FX_TRY(ws_get(ctx, ws, "pt_r64", (size_t)16 * nr * n, &r64));
     ldr64 = nr;
   }
+  FX_TRY(zgemm(ctx, ws, st, 1, 0, n, n, (int)nr, cpx<double>{1, 0}, p64, ldp, h64, ldh, cpx<double>{0, 0}, S, n, 1, 0,
+               0, 0, 0));
+  // R = Psi - Psi_half + (i dt/2) (H Psi - Psi S), formed where Psi S ends
   const ZgResidual res{(const cpx<double>*)p64, (const cpx<double>*)f64, (const cpx<double>*)h64, ldp, ldf, ldh,
                        0.5 * dtime};
   FX_TRY(zgemm(ctx, ws, st, 0, 0, (int)nr, n, n, cpx<double>{1, 0}, p64, ldp, S, n, cpx<double>{0, 0}, r64, ldr64, 1,
@@ -185,9 +186,10 @@ static fx_status orthonormalize(fx_ctx* ctx, void* psi, int n, int64_t ld, int64
   const void* p64;
   int64_t ldp;
   FX_TRY(as_c128(ctx, ws, "on_psi", psi, ld, dt, nr, n, st, &p64, &ldp));
-  void *L = nullptr, *scal = nullptr;
+  void *L = nullptr, *scal = nullptr, *dinv = nullptr;
   FX_TRY(ws_get(ctx, ws, "on_L", zsz * n * n, &L));
   FX_TRY(ws_get(ctx, ws, "on_scal", 64, &scal));
+  FX_TRY(chol_workspace(ctx, ws, n, &dinv));
   // S = Psi^H Psi: its lower tiles, factored in place (S = L L^H)
   FX_TRY(zgemm(ctx, ws, st, 1, 0, n, n, (int)nr, cpx<double>{1, 0}, p64, ldp, p64, ldp, cpx<double>{0, 0}, L, n, 1, 0,
                0, 0, 0, ZgShape{kZgHermitian}));
@@ -195,8 +197,6 @@ static fx_status orthonormalize(fx_ctx* ctx, void* psi, int n, int64_t ld, int64
   // the info flag must start at zero; this call waits on the host below and
   // is never captured
   FX_HIP(hipMemsetAsync(info_dev, 0, sizeof(int), st));
-  void* dinv = nullptr;
-  FX_TRY(ws_get(ctx, ws, "chol_dinv", chol_dinv_bytes(n), &dinv));
   FX_TRY(zpotrf(ctx, ws, st, n, L, n, dinv, info_dev));
   int info = 0;
   FX_HIP(hipMemcpyAsync(&info, info_dev, sizeof(int), hipMemcpyDeviceToHost, st));

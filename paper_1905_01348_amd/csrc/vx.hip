@@ -505,14 +505,10 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
   // (With less left than the pairs alone need the request stands, and is
   // FX_ERR_OOM: a server then hands back idle workspaces.)
   if (jsplit > 1 && !rounds) {
-    const auto it = ws->bufs.find("vx_work");
-    const size_t have = it == ws->bufs.end() ? 0 : it->second.bytes, left = ctx->budget - ctx->in_use + have;
+    const size_t left = ws_room(ctx, ws, "vx_work");
     const size_t least = (size_t)std::min<int64_t>(pairs_cap, (int64_t)a.n_psi * a.n_phi) * pair_bytes;
     size_t room = ctx->budget / 4;
-    if (ctx->capturing)
-      room = std::min(room, have);
-    else if (least <= left)
-      room = std::min(room, left);
+    if (ctx->capturing || least <= left) room = std::min(room, left);
     if (sum_bytes + pair_bytes > room)
       return run_groups_in_turn<T, A>(ctx, ws, a, pass, tb, psi, ld_psi, phi, ld_phi, jsplit, st, stats);
     shape(room);

@@ -100,3 +100,43 @@ def test_energy_takes_no_memory_of_its_own():
         F.debug_fail_alloc(0)
         ref.close()
         ctx.close()
+
+
+def _within(run, less):
+    """run(ctx) on an ample budget, then within `less` bytes below the memory that took: the same bits."""
+    ctx = Context(0)
+    ref = run(ctx)
+    peak = ctx.memory()[1]
+    ctx.close()
+    say("peak", peak, "less", less)
+    ctx = Context(0, hbm_budget_bytes=peak - less)
+    got = run(ctx)
+    assert ctx.memory()[1] <= peak - less
+    ctx.close()
+    assert np.array_equal(got, ref)
+
+
+def test_split_products_in_less_memory(monkeypatch):
+    """Partial sums of the FP64 products (S of a residual, the overlap of an orthonormalisation, xi^H phi): with
+    three quarters of them beyond the budget the products run in blocks of columns."""
+    monkeypatch.setenv("FX_WORK_MB", "1")
+    N, R, splits = 32, 128, 13824 // 128
+    psi, half, h = (dev(synth.random_grid_vectors(404 + i, N3, N)) for i in range(3))
+    phi = dev(synth.random_grid_vectors(407, N3, R))
+    small = dev(synth.make_orbitals(408, N3, L3, 8))
+
+    def residual(ctx):
+        return host(ctx.pt_residual(psi, half, hpsi=h, n=N3, L=L3, dt=0.3))
+
+    def orthonormalize(ctx):
+        return host(ctx.orthonormalize(psi.clone()))
+
+    def apply_ace(ctx):
+        ace = ctx.build_ace(small, n=N3, L=L3, kernel="hse", omega=0.106)
+        out = host(ace.apply(phi))
+        ace.free()
+        return out
+
+    _within(residual, N * N * splits * 16 * 3 // 4)
+    _within(orthonormalize, N * N * splits * 16 * 3 // 4)
+    _within(apply_ace, 8 * R * splits * 16 * 3 // 4)
