@@ -462,6 +462,7 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
             g.nz);
   if (a.segs.n > 0 && (!use_ct || psi == phi))
     FX_FAIL(FX_ERR_UNSUPPORTED, "multi-trajectory launches need the specialised kernels and phi != psi");
+  if (!use_ct) FX_TRY(gen_check_tile(g, a.xtile, a.nthr_b));
   const PairPasses<T, A> pass{ctx, st, use_ct, g, tb, a.xtile, a.nthr_b};
   const bool square = psi == phi && ld_psi == ld_phi && a.n_psi == a.n_phi;
   if (square && a.halve != 0 && (use_ct || a.halve > 0 || gen_halved(a, g)))

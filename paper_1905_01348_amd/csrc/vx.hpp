@@ -147,8 +147,12 @@ fx_status ct_pass_b(fx_ctx* ctx, hipStream_t st, int n, const CtBatch<T>& b);
 template <typename T, typename A>
 fx_status ct_pass_c(fx_ctx* ctx, hipStream_t st, int n, const CtBatch<T>& b, const CtAcc<A>& c, int role);
 
-// The passes on any grid.  xtile / threads of the z pass: 0 automatic.
+// The passes on any grid.  xtile / threads of the z pass: 0 automatic; a tile of
+// more than 18 points per thread (32 columns where none is asked for, at most 256
+// threads) is FX_ERR_UNSUPPORTED: it need not fit the LDS, and a tuner goes on to
+// its next candidate.
 struct PassGeom;
+fx_status gen_check_tile(const PassGeom& g, int xtile, int most_threads);
 template <typename T>
 fx_status gen_pass_a(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb, const CtBatch<T>& b);
 template <typename T>

@@ -400,6 +400,13 @@ fx_status gen_pass_a(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridT
   return FX_OK;
 }
 
+fx_status gen_check_tile(const PassGeom& g, int xtile, int most_threads) {
+  const int points = g.nz * std::min(g.nx, xtile > 0 ? xtile : 32);
+  if (round64((points + 17) / 18) > (most_threads > 0 ? std::min(most_threads, 256) : 256))
+    FX_FAIL(FX_ERR_UNSUPPORTED, "pencil tile of %d points is too large", points);
+  return FX_OK;
+}
+
 template <typename T>
 fx_status gen_pass_b(fx_ctx* ctx, hipStream_t st, const PassGeom& g, const GridTables* tb, const CtBatch<T>& b,
                      int xtile, int most_threads) {

@@ -82,3 +82,29 @@ def test_several_butterflies_per_thread(ctx, n3, radix):
 @pytest.mark.parametrize("n3", [(12, 36, 3), (12, 48, 2), (12, 96, 2), (9, 12, 4), (12, 9, 8), (12, 12, 3), (8, 16, 3)])
 def test_one_stage_x_axes(ctx, n3, monkeypatch):
     test_square_form_and_groups(ctx, n3, monkeypatch)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32acc64"])
+def test_z_tiles_too_large_are_refused(ctx, prec):
+    """A z-pass tile of more than 18 points per thread (a whole row of 96 pencils of 96 points need not fit the
+    LDS) is FX_ERR_UNSUPPORTED before anything is launched, and the tuner passes over it."""
+    from paper_1905_01348_amd import FockError
+
+    n3, L3, N = (96, 2, 96), (30.0, 1.0, 30.0), 3
+    psi = synth.random_grid_vectors(74, n3, N)
+    ref = oracle.apply_vx(psi, psi, n3, L3, "hse", 0.3)
+    cdt = np.complex128 if prec == "fp64" else np.complex64
+    P, kw = dev(psi.astype(cdt)), dict(n=n3, L=L3, kernel="hse", omega=0.3, prec=prec)
+    for cfg in ({"kernels": 2, "b_xtile": 96}, {"kernels": 2, "b_xtile": 49}, {"kernels": 2, "b_threads": 128}):
+        say("refused", prec, cfg)
+        ctx.set_vx_config(cfg, n=n3, prec=prec, phi_is_psi=True)
+        with pytest.raises(FockError) as ei:
+            ctx.apply_vx(P, **kw)
+        assert ei.value.status == -2, cfg
+    ctx.set_vx_config({"kernels": 2, "b_xtile": 48}, n=n3, prec=prec, phi_is_psi=True)
+    assert rel_err(host(ctx.apply_vx(P, **kw)), ref) <= TOL[prec]
+    say("tune", prec)
+    cfg, _ = ctx.vx_autotune(n=n3, L=L3, n_psi=N, n_phi=N, phi_is_psi=True, prec=prec)
+    assert cfg["b_xtile"] <= 48
+    assert rel_err(host(ctx.apply_vx(P, **kw)), ref) <= TOL[prec]
+    ctx.set_vx_config(None, n=n3, prec=prec, phi_is_psi=True)
