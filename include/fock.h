@@ -248,7 +248,8 @@ typedef struct fx_vx_config {
   int32_t c_split;     /* plane-inverse pass: S sum groups per target (1, 2, 4 or 8;
                           0 automatic: 1 where each unordered pair is solved once, else as
                           many as give eight targets on this grid the resident
-                          workgroups, at least four orbitals each, and two where they
+                          workgroups, at least four orbitals each (and 12 in all on
+                          planes of up to 108 points), and two where they
                           are up to a quarter more than those).  The terms of
                           orbital j go to group j mod S, each group summed in ascending j,
                           the groups added in order at the end: S times the pass's work
@@ -265,10 +266,10 @@ typedef struct fx_vx_config {
  * (n_psi orbitals, n_phi targets, phi_is_psi != 0 for the phi == psi form)
  * on synthetic data it allocates itself, by coordinate descent over the
  * fields above (kernel family; for the specialised kernels the prefetch form,
- * the z-pass tile, the plane-inverse and plane-forward threads and forms, the
- * cache hints and the plane-inverse sum groups; for the generic kernels the
- * radix schedule of each
- * axis, the z-pass tile and threads; then the batch volume), and stores the
+ * the z-pass tile, the plane-inverse and plane-forward threads and forms and
+ * the cache hints; the plane-inverse sum groups; for the generic kernels the
+ * radix schedule of each axis, the z-pass tile and threads; then the batch
+ * volume), and stores the
  * fastest in the context, where every later fx_apply_vx, fx_build_ace and
  * served request of that grid, precision and form uses it.  Each candidate
  * is timed on a probe of at most ~2 full batches of pairs with HIP events on
@@ -298,7 +299,9 @@ fx_status fx_vx_get_config(fx_ctx* ctx, const fx_cell* cell, fx_prec prec, int32
  * this kind of device (architecture and CU count) from one (*n_loaded: how
  * many; nullable).  Lines for other devices are kept on save.  With the
  * environment variable FX_TUNE_CACHE set to a path, fx_init loads that file
- * if it exists and fx_vx_autotune saves to it after tuning.  Errors:
+ * if it exists and fx_vx_autotune saves to it after tuning.  In the file an
+ * automatic c_split is -1; 0 (files saved when automatic was one running sum)
+ * is read as 1.  Errors:
  * FX_ERR_INVALID (NULL argument, unreadable or malformed file). */
 fx_status fx_vx_load_configs(fx_ctx* ctx, const char* path, int32_t* n_loaded);
 fx_status fx_vx_save_configs(fx_ctx* ctx, const char* path);

@@ -70,7 +70,8 @@ static bool is_vx_prec(fx_prec p) { return p == FX_PREC_FP64 || p == FX_PREC_FP3
 //   fxcfg <device> <nx> <ny> <nz> <prec> <phi_is_psi> <kernels> <work_mb> <a_prefetch>
 //         <b_variant> <c_variant> <a_variant> <nt_hint> <b_xtile> <b_threads> <12 radix entries>
 //         [<c_split>]
-// (lines without c_split, written before it existed, read it as 0)
+// (c_split -1 is automatic; 0 and a line without it, both written when automatic
+// was one running sum and the configuration was tuned with that, read as 1)
 // where <device> is the architecture and CU count ("gfx950/256"): a tuned
 // launch shape holds for that kind of device only.  Lines starting with '#'
 // are comments; lines for other devices are kept when the file is rewritten.
@@ -91,7 +92,7 @@ static std::string config_line(const std::string& tag, const std::array<int, 5>&
   for (int v : f) s += " " + std::to_string(v);
   for (int a = 0; a < 3; ++a)
     for (int r = 0; r < 4; ++r) s += " " + std::to_string(c.radix[a][r]);
-  s += " " + std::to_string(c.c_split);
+  s += " " + std::to_string(c.c_split ? c.c_split : -1);
   return s;
 }
 
@@ -116,7 +117,7 @@ static bool parse_config_line(const char* line, std::string* tag, std::array<int
   for (int i = 0; i < 9; ++i) *f[i] = v[5 + i];
   for (int a = 0; a < 3; ++a)
     for (int r = 0; r < 4; ++r) c->radix[a][r] = v[14 + 4 * a + r];
-  c->c_split = v[26];
+  c->c_split = v[26] == 0 ? 1 : v[26] == -1 ? 0 : v[26];
   return true;
 }
 
@@ -322,6 +323,7 @@ static fx_status autotune(fx_ctx* ctx, const fx_cell* cell, const fx_kernel* ker
   cur.c_variant = spec ? (cell->n[0] == 96 || cell->n[0] == 72 ? 5 : 1) : 0;
   cur.a_variant = spec ? (t64 && (cell->n[0] == 96 || cell->n[0] == 72) ? 3 : 1) : 0;
   cur.nt_hint = spec ? 1 : 0;
+  cur.c_split = 1;  // one running sum; the groups are candidates below
   rs = trial(cur);
   if (rs == FX_OK && best == std::numeric_limits<double>::infinity()) {
     cleanup();
@@ -367,6 +369,8 @@ static fx_status autotune(fx_ctx* ctx, const fx_cell* cell, const fx_kernel* ker
       c.nt_hint = 1 - cur.nt_hint;
       rs = trial(c);
     }
+  }
+  if (rs == FX_OK) {
     // sum groups of the plane-inverse pass (pays where targets are few)
     const fx_vx_config sstart = cur;
     for (int sp = 2; sp <= 8 && rs == FX_OK; sp *= 2) {
