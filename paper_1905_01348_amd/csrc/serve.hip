@@ -235,6 +235,7 @@ struct HipExec final : ServeExecutor {
       va.in_dtype = t.dtype;
       va.out_dtype = t.dtype;
       va.prec = t.vx_prec;
+      va.served = true;
       va.work_cap = (size_t)(srv->cfg.vx_work_mb > 0 ? srv->cfg.vx_work_mb : 1024) << 20;
       FX_TRY(vx_apply(ctx, &sl.ws, va, sl.st, nullptr));
     } else {

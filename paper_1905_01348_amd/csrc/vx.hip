@@ -465,7 +465,7 @@ static fx_status run_batches(fx_ctx* ctx, Workspace* ws, const VxArgs& a, const 
   if (!use_ct) FX_TRY(gen_check_tile(g, a.xtile, a.nthr_b));
   const PairPasses<T, A> pass{ctx, st, use_ct, g, tb, a.xtile, a.nthr_b};
   const bool square = psi == phi && ld_psi == ld_phi && a.n_psi == a.n_phi;
-  if (square && a.halve != 0 && (use_ct || a.halve > 0 || gen_halved(a, g)))
+  if (square && a.halve != 0 && (use_ct || a.halve > 0 || (!a.served && gen_halved(a, g))))
     return run_halved<T, A>(ctx, ws, a, pass, tb, psi, ld_psi, pairs_cap, st, stats);
   const bool out_c64 = a.out_dtype == FX_C64;
   const bool out_is_A = (sizeof(A) == 8) == !out_c64;

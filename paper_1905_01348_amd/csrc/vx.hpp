@@ -68,6 +68,10 @@ struct VxArgs {
   // several trajectories' orbital blocks (specialised kernels, phi != psi);
   // psi is then the first block's
   TrajSegs segs;
+  // a served request: one for all orbitals has phi == psi when it is served alone
+  // but not when it is merged, and its result must not tell (the run-time-plan
+  // kernels then never solve each unordered pair once)
+  bool served = false;
   // allocation-free form: `ws` carves from a fixed scratch region, the grid
   // tables are built there on the device, no conversion, no pair halving
   bool no_alloc = false;
