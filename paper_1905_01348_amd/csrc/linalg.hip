@@ -392,11 +392,11 @@ __global__ void __launch_bounds__(64) k_half_trace(int n, const z* __restrict__ 
 // ---------------------------------------------------------------------------
 // Blocked Cholesky, lower: A = L L^H, in blocks of CB columns.  Three launches
 // per block: the diagonal block (factor and inverse, one workgroup), the rows
-// below it (times the inverse) and the trailing update; the inverses are kept
-// for ztrinv.  What bounds it is the chain of small launches, so a block is
+// below it (substitution) and the trailing update; the inverses are kept for
+// ztrinv.  What bounds it is the chain of small launches, so a block is
 // as large as one workgroup holds in registers: with 32-wide blocks solved by
 // one thread per row, factor and inverse of 432 columns took 2.1 ms in 70
-// launches (now 0.5 ms in 29).
+// launches (now 0.5 ms in 27).
 // ---------------------------------------------------------------------------
 constexpr int CB = kCholBlock;
 
@@ -476,6 +476,53 @@ __global__ void __launch_bounds__(256) k_potrf_diag(int n, z* A, int64_t lda, in
     }
 }
 
+// Rows below the diagonal block at (k, k): X L_kk^H = A21 by substitution, column
+// by column.  (The product with the explicit inverse of the block is a matrix
+// product, but its error grows with the block's condition: an orbital that
+// differs from another by 1e-6 left |M - L L^H| at 5e-12 |M| instead of 1e-15.)
+// What bounds it is the chain over the 64 columns, so a row is shared by 16 lanes,
+// lane q with the columns q + 16 i in registers: the lane that owns column c hands
+// x_c to the others, and each takes it off its later columns.  The loop over a
+// lane's columns stays rolled: unrolled over all 64 it is 40 KB of code that runs
+// once, 150 us of instruction fetches; this is 17 us for up to 368 rows, 12 as a
+// product.  L_kk lies in LDS by column.
+__global__ void __launch_bounds__(256) k_potrf_panel(int n, z* A, int64_t lda, int k) {
+  __shared__ z L[CB][CB];
+  for (int e = threadIdx.x; e < CB * CB; e += 256) L[e / CB][e % CB] = A[(k + e % CB) + (int64_t)(k + e / CB) * lda];
+  const int q = threadIdx.x & 15, row = k + CB + blockIdx.x * 16 + (threadIdx.x >> 4);
+  z* const a = A + min(row, n - 1) + (int64_t)(k + q) * lda;
+  z x[CB / 16];
+#pragma unroll
+  for (int i = 0; i < CB / 16; ++i) x[i] = a[(int64_t)16 * i * lda];
+  __syncthreads();
+  // 1 / L(c, c) in the diagonal's imaginary part
+  if (threadIdx.x < CB) L[threadIdx.x][threadIdx.x].y = 1.0 / L[threadIdx.x][threadIdx.x].x;
+  __syncthreads();
+  // v / d for real d: the product with its reciprocal, corrected once
+  const auto over = [](double v, z d) __attribute__((always_inline)) {
+    const double t = v * d.y;
+    return __builtin_fma(__builtin_fma(-t, d.x, v), d.y, t);
+  };
+#pragma unroll
+  for (int i = 0; i < CB / 16; ++i) {
+#pragma unroll 2
+    for (int s = 0; s < 16; ++s) {
+      const int c = 16 * i + s;
+      const z d = L[c][c], v = {over(x[i].x, d), over(x[i].y, d)};
+      const z m = {-__shfl(v.x, s, 16), -__shfl(v.y, s, 16)};
+      // column 16 i + q is x_c itself for lane s and a later one for lanes q > s
+      const z f = zfma(x[i], m, zconj(L[c][16 * i + q]));
+      x[i].x = q == s ? v.x : q > s ? f.x : x[i].x;
+      x[i].y = q == s ? v.y : q > s ? f.y : x[i].y;
+#pragma unroll
+      for (int j = i + 1; j < CB / 16; ++j) x[j] = zfma(x[j], m, zconj(L[c][16 * j + q]));
+    }
+  }
+  if (row < n)
+#pragma unroll
+    for (int i = 0; i < CB / 16; ++i) a[(int64_t)16 * i * lda] = x[i];
+}
+
 __global__ void k_zero_upper(int n, z* A, int64_t lda) {
   const int64_t nn = (int64_t)n * n;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nn; e += (int64_t)gridDim.x * blockDim.x) {
@@ -507,13 +554,8 @@ fx_status zpotrf(fx_ctx* ctx, Workspace* ws, hipStream_t st, int n, void* A, int
     if (rest <= 0) break;
     z* L21 = a + (k + nb) + (int64_t)k * lda;
     z* A22 = a + (k + nb) + (int64_t)(k + nb) * lda;
-    // rows below: L21 = A21 L_kk^{-H}, in place (a workgroup holds all CB
-    // columns of its rows and stores them after its last read)
-    ZgArgs g{rest, nb, nb, L21, lda, 0, di, CB, 0, L21, lda, 0, z{1.0, 0.0}, z{0.0, 0.0}, 1, (nb + ZK - 1) / ZK * ZK,
-             (rest + 31) / 32, 1, nullptr, ZgShape{}};
-    using T = ZgTile<1, 2, 2>;
-    static_assert(T::BN == CB, "a panel row's columns must be one tile");
-    hipLaunchKernelGGL((k_zgemm<0, 1, 1, 2, 2>), dim3((unsigned)g.tiles_m), dim3(T::NT), T::kLds, st, g);
+    // rows below: L21 = A21 L_kk^{-H}, in place (rows are left only below whole blocks)
+    hipLaunchKernelGGL(k_potrf_panel, dim3((unsigned)((rest + 15) / 16)), dim3(256), 0, st, n, a, lda, k);
     FX_LAUNCH_CHECK();
     // trailing update A22 -= L21 L21^H, lower part
     FX_TRY(zgemm(ctx, ws, st, 0, 1, rest, rest, nb, z{-1.0, 0.0}, L21, lda, L21, lda, z{1.0, 0.0}, A22, lda, 1, 0,
