@@ -109,7 +109,6 @@ __global__ void __launch_bounds__(128 * WNW, WM * WN <= 4 ? 4 : 2) k_zgemm(const
   const z* A = g.A + batch * g.sA;
   const z* B = g.B + batch * g.sB;
   int kbeg = split * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
-  if (g.shape.flags & kZgBUpper) kend = min(kend, n0 + BN);
   if (g.shape.flags & kZgALower) kend = min(kend, min(M, m0 + BM));
   if (g.shape.flags & kZgBLower) kbeg = max(kbeg, n0);
   // staged loads: UA elements of the A tile and UB of the B tile per thread;

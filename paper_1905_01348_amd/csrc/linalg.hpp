@@ -7,10 +7,10 @@ namespace fx {
 
 // What a product may leave out: output tiles strictly above the diagonal of a
 // Hermitian C (the strict upper part is then undefined), and the zeros of a
-// triangular operand (B upper: B(k, n) = 0 for k > n; B lower, A lower).  With
+// triangular operand (A or B lower).  With
 // mlim > 0, product b of the batch has min(M, mlim - b * mstep) rows (and, with
 // A lower, as many k).
-constexpr int kZgHermitian = 1, kZgBUpper = 2, kZgALower = 4, kZgBLower = 8;
+constexpr int kZgHermitian = 1, kZgALower = 2, kZgBLower = 4;
 struct ZgShape {
   int flags = 0, mlim = 0, mstep = 0;
 };

@@ -408,10 +408,6 @@ constexpr size_t pair_lds_bytes() {
   return std::max<size_t>((size_t)(REFINE ? 2 : 1) * (kPairA + kPairB), (size_t)4 * 16 * 33 * sizeof(double2));
 }
 
-__device__ inline void lds_load16(const void* g, unsigned char* lds_wave_base) {
-  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds_wave_base, 16, 0, 0);
-}
-
 template <typename S>
 __device__ inline floatx16 mfma16(u32x4 a, u32x4 b, floatx16 c) {
   if constexpr (std::is_same<S, _Float16>::value)
@@ -613,9 +609,10 @@ __global__ void __launch_bounds__(256, 2) k_tn_pair(int M, int R, int K, int kch
 // uses whole 128-byte lines over a step, A three steps ahead (one for two
 // column tiles and for the short reductions of MODE 1), B, a few rows in L2,
 // one.  CT: 32-wide column tiles (1 or 2).
-// The k terms of an element run in the order of k_tn_mfma over the same split
+// The k terms of an element run in the order of the tile kernels (k_tn_mfma in
+// FP32, k_tn_pair in the 2-byte types) over the same split
 // chunks, so a right-hand side's bits do not depend on which kernel ran.
-// MODE 0 as k_tn_mfma.  MODE 1 gives the matrix instruction B as its rows: lane
+// MODE 0 as theirs.  MODE 1 gives the matrix instruction B as its rows: lane
 // l then holds y(r = l % 32) of several targets, and stores run along r.
 // ---------------------------------------------------------------------------
 template <typename S>
@@ -643,8 +640,8 @@ __global__ void __launch_bounds__(64, (MODE == 1 ? 3 : 2)) k_tn_skinny(int M, in
   const int tm = blockIdx.x % tiles_m, split = blockIdx.x / tiles_m;
   const int m0 = tm * 32;
   const int kbeg = split * kchunk, kend = min(K, kbeg + kchunk);
-  // piece v of a step: bytes [off(v), off(v) + 16) of the row's 128 (k_tn_mfma's
-  // lane layout: 2-byte types k = 16 v + 8 half, FP32 k = 16 half + 4 v)
+  // piece v of a step: bytes [off(v), off(v) + 16) of the row's 128 (the tile
+  // kernels' lane layout: 2-byte types k = 16 v + 8 half, FP32 k = 16 half + 4 v)
   const auto off = [half](int v) { return sizeof(S) == 4 ? 16 * half + 4 * v : 16 * v + 8 * half; };
   const int64_t arow = (int64_t)min(m0 + l32, M - 1) * lda;
   const S* ap = Ap + arow;
@@ -1156,7 +1153,7 @@ static fx_status apply_t(fx_ctx* ctx, Workspace* ws, fx_ace* a, AceSplit* sp, co
     FX_TRY(prof_begin(ctx, st, FX_K_GEMM_NN, (REFINE ? 3.0 : 1.0) * 2.0 * (double)nr * 2.0 * R * (double)sp->kn, &slot));
     // FP32, up to 32 right-hand sides: by waves too (8 right-hand sides with 432
     // factors at 72^3 2233 -> 1020 us, 32 of them 2296 -> 1980); the 2-byte types
-    // keep the direct-to-LDS tiles (8: 303 against 417 us)
+    // keep the tiles (8, FP16 with the residual: 281 against 417 us)
     bool waves_out = false;
     if constexpr (sizeof(S) == 4) {
       waves_out = R <= 32;

@@ -151,21 +151,15 @@ static int ct_c_variant(const VxArgs& a) {
   return a.cell->n[0] == 96 || a.cell->n[0] == 72 ? 5 : 1;
 }
 
-// How the XCDs share the items of the persistent plane passes (bit 0: the
-// plane-forward pass, bit 1: the plane-inverse pass; set: each XCD takes a
-// contiguous range of z planes of every unit, clear: a contiguous range of
-// units at every z).  The plane-forward pass reads each orbital and target
-// plane once per XCD with the z split instead of once per XCD per chunk of
-// pairs (3.05 -> 2.82 ms per launch of 1170 pairs at 96^3); the plane-inverse
-// pass measured slower with it (3.13 -> 3.30 ms), so it keeps the unit split.
-// Sum groups of the specialised plane-inverse pass: the terms of orbital j
+// Sum groups of the plane-inverse pass: the terms of orbital j
 // go to partial sum j mod S of their target, each in ascending j, and the S
 // partial sums are added in order of the group at the end.  With few targets
 // the pass has few items (targets x planes); S times as many balance the
 // CUs.  The grouping depends on the orbital index only, so a column's result
 // is the same whatever the batch size and whichever targets share a launch.
 // Automatic: as many groups as give the eight targets of a request the
-// workgroups that are resident at once (256 CUs of 12 waves; a plane has about
+// workgroups that are resident at once (256 CUs of 12 waves, also in FP32, where
+// some kernels hold 16: the precisions then group alike; a plane has about
 // ny nx / R butterflies in its last stage, R the first x radix), with at least
 // four terms each.  The count of targets must not enter, since served requests
 // are merged; the phi == psi form keeps one running sum (its partial sums then
@@ -176,7 +170,8 @@ static int ct_c_variant(const VxArgs& a) {
 // terms one after the other, 182 us, four groups 71 and 7 to add them; at 64^3
 // two groups gain nothing and their partial sums cost the other passes 130 of
 // 2440 us.  Two groups also where eight targets are up to a quarter more than
-// the resident workgroups, so that the second round is a short one (96 orbitals
+// the resident workgroups, so that the second round is a short one (planes of 5 or
+// 6 waves on 72 planes, of 7 or more on 36; 96 orbitals
 // at 48 x 64 x 72 in FP64, 512 resident: 8 targets 4423 -> 4133 us, 16 8107 ->
 // 7739, 32 14630 -> 14920; at half more, 96 x 96 x 48, the partial sums cost as
 // much as they save).
@@ -237,11 +232,15 @@ static fx_status combine_groups(fx_ctx* ctx, hipStream_t st, const cpx<A>* acc, 
   return FX_OK;
 }
 
-// Work order of the specialised plane passes: bit 0 splits the plane-forward
-// pass over the XCDs by z, bit 1 the plane-inverse pass (slower: 2.76 against
-// 2.71 ms per launch at 96^3), bit 2 walks the plane-forward pass's pairs in
-// blocks of 4 orbitals x 16 targets (unit_plane).  Only the order changes,
-// never a result.
+// Work order of the persistent plane passes: how the XCDs share their items (bit
+// 0 the plane-forward pass, bit 1 the plane-inverse pass; set: each XCD takes a
+// contiguous range of z planes of every unit, clear: a contiguous range of units
+// at every z), and with bit 2 the plane-forward pass walks its pairs in blocks of
+// 4 orbitals x 16 targets (unit_plane).  With the z split the plane-forward pass
+// reads each orbital and target plane once per XCD instead of once per XCD per
+// chunk of pairs (3.05 -> 2.82 ms per launch of 1170 pairs at 96^3); the
+// plane-inverse pass is slower with it (2.76 against 2.71) and keeps the unit
+// split.  Only the order changes, never a result.
 static int ct_zsplit() {
   const char* e = getenv("FX_VX_ZSPLIT");
   return e ? atoi(e) : 5;

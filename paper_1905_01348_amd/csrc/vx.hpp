@@ -62,7 +62,7 @@ struct VxArgs {
   int a_var = 0;    // specialised plane-forward threads: 1 default, 2 second count, 3 that with the
                     // wave-level x transform (72 and 96), 0 automatic
   int nt_hint = -1;  // specialised kernels: non-temporal hints on the pair volume (1, 0, -1 automatic = 1)
-  int c_split = 0;   // specialised plane-inverse pass: j-sum groups (1, 2, 4 or 8; 0 automatic = 1)
+  int c_split = 0;   // plane-inverse pass: j-sum groups (1, 2, 4 or 8; 0 automatic by grid and orbital count)
   bool plans_set = false;  // generic kernels: radix schedules in `plans`
   PlanSet plans;
   // several trajectories' orbital blocks (specialised kernels, phi != psi);

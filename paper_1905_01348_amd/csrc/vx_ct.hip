@@ -1,6 +1,6 @@
 // V_X pair passes specialised at compile time for the cubic grids of the
 // workloads (edges 24, 48, 72, 96).  Same three passes and data layout as the
-// generic kernels in vx.hip (see vx_passes.hpp); every shape is a constant.
+// kernels of any grid in vx_gen.hip (see vx_passes.hpp); every shape is a constant.
 #include <algorithm>
 #include <cstdlib>
 
