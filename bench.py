@@ -31,7 +31,7 @@ HBM_PEAK_GBS = 8000.0
 KSRC = ["paper_1905_01348_amd/csrc/vx.hip", "paper_1905_01348_amd/csrc/vx_passes.hpp",
         "paper_1905_01348_amd/csrc/fft.hpp", "paper_1905_01348_amd/csrc/vx_ct.hip",
         "paper_1905_01348_amd/csrc/fft_ct.hpp", "paper_1905_01348_amd/csrc/pair_order.hpp",
-        "paper_1905_01348_amd/csrc/item_map.hpp"]
+        "paper_1905_01348_amd/csrc/item_map.hpp", "paper_1905_01348_amd/csrc/vx_gen.hip"]
 
 
 def _code_tokens(text):
