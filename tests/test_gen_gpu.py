@@ -108,3 +108,18 @@ def test_z_tiles_too_large_are_refused(ctx, prec):
     assert cfg["b_xtile"] <= 48
     assert rel_err(host(ctx.apply_vx(P, **kw)), ref) <= TOL[prec]
     ctx.set_vx_config(None, n=n3, prec=prec, phi_is_psi=True)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp32acc64"])
+def test_automatic_halving(ctx, prec, monkeypatch):
+    """phi == psi off the specialised grids: FP64 and FP32 solve each unordered pair once from 512 planes of targets
+    on (8 to 12 waves per plane here), FP32 with FP64 sums never; bitwise what asking for it gives."""
+    n3, L3 = (96, 64, 36), (41.0, 27.0, 15.0)
+    for N, halved in ((14, False), (15, prec != "fp32acc64")):
+        psi = dev(synth.random_grid_vectors(75, n3, N).astype(np.complex128 if prec == "fp64" else np.complex64))
+        call = lambda: host(ctx.apply_vx(psi, n=n3, L=L3, kernel="hse", omega=0.3, prec=prec))
+        auto = call()
+        for h in (False, True):
+            monkeypatch.setenv("FX_VX_HALVE", str(int(h)))
+            assert np.array_equal(call(), auto) == (h == halved), (N, h)
+            monkeypatch.delenv("FX_VX_HALVE")
